@@ -1,4 +1,4 @@
-"""The workloads that performance is judged on: what a serving program has this library do.
+"""The workloads that performance is measured on: what a serving program has this library do.
 
 A case is one pass of one attention path through the public entry points, over `layers` layers that
 each keep a KV pool of their own, as in a model.  The sizes are those of the repository's named
