@@ -27,6 +27,13 @@
 //     launch combines (Opt-Pa Eq. 10 over the parts).
 // The only difference from decode in the arithmetic is that the visible-token limit is per column
 // (causal).
+//
+// The launch's order.  A causal stream is as long as its last row needs and one workgroup holds a
+// CU, so how long a launch takes is decided by which rows a workgroup takes and in which order the
+// workgroups start: tiles by row, the longest streams first, whole and split streams in one launch
+// (TileOrder and the start of the kernel).  Three fresh prompts of 301, 1039 and 1777 rows (40 over
+// 8 heads, d = 128): 156 us a pass with tiles by head, first rows first and the split streams in a
+// launch behind the whole ones, 100 us so; 8 x 512 rows over 8192 tokens 763 -> 744 us.
 #include "attn_tile.hpp"
 
 namespace coopt {
@@ -42,16 +49,50 @@ struct PrefillArgs {
     int32_t max_blocks;
     int32_t pool_tiles;
     int32_t num_pairs;        // num_seqs * H_k
-    int32_t wgs_per_pair;
-    int32_t tile_base;        // this launch covers tiles [tile_base, tile_limit) of every pair
+    int32_t xcd_pairs;        // pairs per XCD: num_pairs rounded up to a multiple of 8, over 8
+    int32_t by_pair;          // order of an XCD's workgroups (see the kernel)
+    int32_t blocks_per_pair;  // workgroups per pair over tiles [tile_base, tile_limit): whole streams
+    int32_t tile_base;
     int32_t tile_limit;
     float scale_log2e;
-    // split launch (the last tiles of every pair, `split` workgroups per 16 tiles: workgroup p of
-    // them streams the p-th of `split` equal runs of the pair's stages and leaves per tile 16 x
-    // (m, l) and the 16 x HEAD_DIM unnormalised sums in `part`, which a merge launch combines)
+    // split workgroups, behind the whole-stream ones in the grid (the tiles from tile_limit on of
+    // every pair, `split` workgroups per 16 tiles: workgroup p of them streams the p-th of `split`
+    // equal runs of the pair's stages and leaves per tile 16 x (m, l) and the 16 x HEAD_DIM
+    // unnormalised sums in `part`, which a merge launch combines)
     float* part;
-    int32_t split;            // 0: whole streams, rows written to out;  >= 2: that many parts, partials
-    int32_t tail_cap;         // tiles per pair the split launch covers (sizes `part`)
+    int32_t split;            // parts, >= 2 (0: no such workgroups)
+    int32_t split_blocks;     // runs of 16 tiles per pair they cover
+    int32_t tail_cap;         // tiles per pair they cover (sizes `part`)
+};
+
+// The tiles [base, end) of a pair -- tile h T + i is rows 16i .. of head h, T tiles a head -- in the
+// order in which workgroups take them: by row, then by head.  A causal stream is as long as its
+// last row needs, so the 16 tiles of a workgroup should lie at neighbouring rows: by head, a
+// workgroup of 256 rows streams up to 240 tokens too far for most of them.
+struct TileOrder {
+    int T, base, end, hb, ib, he, ie;
+    __device__ __forceinline__ TileOrder(int tiles_per_head, int b, int e) : T(tiles_per_head), base(b), end(e)
+    {
+        // (wave_uniform: the quotients are made on the vector ALU; this keeps them out of its registers)
+        hb = wave_uniform(b / T);
+        ib = b - hb * T;
+        he = wave_uniform(e / T);
+        ie = e - he * T;
+    }
+    __device__ __forceinline__ int count() const { return end - base; }
+    // Position p (0 .. count-1) -> first row / 16 and head.  Row i has he - hb tiles of this range,
+    // one more from ib .. or up to ie (whichever of the two partial heads reaches it).
+    __device__ __forceinline__ void at(int p, int& i, int& h) const
+    {
+        const int N = he - hb, b1 = min(ib, ie), b2 = max(ib, ie);
+        const int c2 = ie > ib ? N + 1 : N - 1;                  // tiles per row between b1 and b2
+        const int n1 = b1 * N, n2 = n1 + (b2 - b1) * c2;
+        if (p < n1) i = p / N;
+        else if (p < n2) i = b1 + (p - n1) / c2;
+        else i = b2 + (p - n2) / max(N, 1);
+        i = wave_uniform(i);
+        h = p - (i * N + min(i, ie) - min(i, ib)) + hb + (i < ib ? 1 : 0);
+    }
 };
 
 constexpr int kPrefillWaves = 8;                // two teams of four producer roles
@@ -60,6 +101,7 @@ constexpr int kPrefillGroupsPerStage = 4;      // two-block groups between two b
 constexpr int kPrefillFirstTeamGroups = 3;
 constexpr float kNoReference = -1.0e30f;        // a running reference below every score
 constexpr int kPrefillMaxParts = 8;            // runs a split launch cuts a stream into, at most
+constexpr long long kPrefillXcdL2 = 4LL << 20;   // bytes of L2 per XCD
 constexpr int kPrefillCUs = 256;               // MI355X: the launch shape is planned for its CU count
 
 // Byte offsets inside one LDS stage (one group = blocks A and B of one KV head).
@@ -191,11 +233,26 @@ prefill_chunk_kernel(const PrefillArgs a)
     const int wave = wave_id & 3;                      // producer role inside its team
     const int team = wave_id >> 2;                     // which groups of a stage it produces: below
     const int n = lane & 15, grp = lane >> 4;
-    // all workgroups of a (sequence, KV head) pair on one XCD (ids go round-robin over 8 XCDs)
+    // all workgroups of a (sequence, KV head) pair on one XCD (ids go round-robin over 8 XCDs).
+    // `turn` = which of the pair's workgroups this is, longest stream first (below).  By pair: an
+    // XCD's whole-stream workgroups pair after pair, then its split ones; otherwise turn after turn
+    // of all its pairs.
     const int k8 = blockIdx.x >> 3;
-    const int pair = (k8 / a.wgs_per_pair) * 8 + (blockIdx.x & 7);
+    const int whole = a.xcd_pairs * a.blocks_per_pair;           // whole-stream workgroups per XCD
+    const int num_split = a.split * a.split_blocks;              // split ones per pair
+    int turn, xcd_pair;
+    if (a.by_pair) {
+        const int k = k8 < whole ? k8 : k8 - whole;
+        const int per = k8 < whole ? a.blocks_per_pair : num_split;
+        xcd_pair = wave_uniform(k / per);
+        turn = k - xcd_pair * per + (k8 < whole ? 0 : a.blocks_per_pair);
+    } else {
+        turn = wave_uniform(k8 / a.xcd_pairs);
+        xcd_pair = k8 - turn * a.xcd_pairs;
+    }
+    const int pair = xcd_pair * 8 + (blockIdx.x & 7);
     if (pair >= a.num_pairs) return;
-    const int seq = pair / a.H_k;
+    const int seq = wave_uniform(pair / a.H_k);
     const int g = pair - seq * a.H_k;
 
     const int qs = a.query_start[seq];
@@ -205,89 +262,56 @@ prefill_chunk_kernel(const PrefillArgs a)
     if (C <= 0) return;
     const int tiles_per_head = (C + 15) / 16;
     const int total_tiles = a.G * tiles_per_head;
-    const int end_tile = min(total_tiles, a.tile_limit);
-    const int in_pair = k8 % a.wgs_per_pair;
-    const int parts = max(a.split, 1);
-    const int part = in_pair % parts;                  // which run of the pair's stages is mine
-    const int wg_first_tile = a.tile_base + (in_pair / parts) * (kPrefillWaves * NR);
-    if (wg_first_tile >= end_tile) return;             // the whole workgroup leaves together
-    const int first_tile = wg_first_tile + wave_id * NR;
-    const bool active = first_tile < end_tile;         // a wave without tiles still produces
+    // The pair's workgroups by the length of their streams: whole streams from the last rows down,
+    // and the split ones (about (t_ctx + C) / split tokens each) where that length has its place --
+    // behind all whole ones once the history is longer than that, in front of the first rows of a
+    // fresh prompt.
+    int ahead = a.blocks_per_pair;                     // whole-stream workgroups before the split ones
+    if (num_split > 0 && !a.by_pair) {
+        const int shorter = wave_uniform((int)(((long long)t / a.split - t_ctx) * a.blocks_per_pair / C));
+        ahead -= min(max(shorter, 0), a.blocks_per_pair);
+    }
+    const bool tail_wg = turn >= ahead && turn < ahead + num_split;
+    const int nth = tail_wg ? turn - ahead : (turn < ahead ? turn : turn - num_split);
+    const int parts = tail_wg ? a.split : 1;
+    const int split_block = wave_uniform(nth / parts);
+    const int part = nth - split_block * parts;        // which run of the pair's stages is mine
+    const int block = (tail_wg ? a.split_blocks : a.blocks_per_pair) - 1 - split_block;
+    const int base_tile = tail_wg ? a.tile_limit : a.tile_base;
+    const int end_tile = tail_wg ? total_tiles : min(total_tiles, a.tile_limit);
+    if (base_tile + block * (kPrefillWaves * NR) >= end_tile) return;  // the whole workgroup leaves together
+    const TileOrder order(tiles_per_head, base_tile, end_tile);
+    const int first = block * (kPrefillWaves * NR) + wave_id * NR;     // position of my first tile
+    const int count = order.count();
+    const bool active = first < count;                 // a wave without tiles still produces
 
     half8_t qop[NR][HEAD_DIM / 32];
     int limit[NR];          // tokens visible to column n of tile r
-    int row0[NR], head[NR];
+    int tile_of[NR];        // head of the group * tiles_per_head + row / 16
     int my_max = 0, min_row = 0x7fffffff;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const int tile = min(first_tile + r, end_tile - 1);      // surplus tiles repeat the last
-        const int hh = tile / tiles_per_head;
-        const int i0 = (tile - hh * tiles_per_head) * 16;
+        int hh, i0;
+        order.at(min(first + r, count - 1), i0, hh);             // surplus tiles repeat the last
+        i0 *= 16;
         const int row = min(i0 + n, C - 1);                      // surplus rows repeat row C-1
-        head[r] = g * a.G + hh;
-        row0[r] = i0;
+        tile_of[r] = hh * tiles_per_head + i0 / 16;
         limit[r] = t_ctx + row + 1;
         my_max = max(my_max, t_ctx + min(i0 + 15, C - 1) + 1);
         min_row = min(min_row, i0);
-        load_q_operand<HEAD_DIM, KV>(qop[r], a.q + ((size_t)(qs + row) * a.H_q + head[r]) * HEAD_DIM,
+        load_q_operand<HEAD_DIM, KV>(qop[r], a.q + ((size_t)(qs + row) * a.H_q + g * a.G + hh) * HEAD_DIM,
                                      true, grp);
     }
     if (!active) my_max = 0;
     // the workgroup streams as far as its longest column needs
-    int wg_max = 0;
-    for (int i = 0; i < kPrefillWaves * NR; ++i) {
-        const int tile = min(wg_first_tile + i, end_tile - 1);
-        const int i0 = (tile % tiles_per_head) * 16;
-        wg_max = max(wg_max, t_ctx + min(i0 + 15, C - 1) + 1);
-    }
+    int wg_row, wg_head;
+    order.at(min((block + 1) * (kPrefillWaves * NR), count) - 1, wg_row, wg_head);
+    const int wg_max = t_ctx + min(16 * wg_row + 15, C - 1) + 1;
     const int nblk = (wg_max + kBlock - 1) / kBlock;
     const int num_groups = (nblk + 1) >> 1;
     const int32_t* bt = a.block_tables + (size_t)seq * a.max_blocks;
 
-    // ---- the pair's largest v_scale as a power of two.  The weights P * v_scale enter the second
-    // product as fp16 (5 exponent bits); value rows can be of any magnitude (an E5M2 cache's scales
-    // are 2^-7 of an E4M3 cache's, small value rows' smaller still), so every v_scale is divided by
-    // the power of two just above the largest one among the tokens this workgroup reads: the
-    // weights of the rows that matter then sit at fp16's upper end whatever the rows' magnitude.
-    // The row sum divides each weight by the same normalised scale, so the factor stays in the
-    // numerator alone and is taken out, exactly, in the final division.  One pass over the pair's
-    // scales (64 bytes per block) before the stream starts.
-    float vnorm = 1.0f, vdenorm = 1.0f;
-    if constexpr (FP8) {
-        __shared__ float vmax_of_wave[kPrefillWaves];
-        float mx = 0.0f;
-        constexpr int kBatch = 8;                          // loads in flight per lane
-        for (int b0 = 0; b0 < nblk; b0 += 4 * kPrefillWaves * kBatch) {
-            int id[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {             // lane group grp takes block b, all 16 tokens
-                const int b = b0 + (u * kPrefillWaves + wave_id) * 4 + grp;
-                id[u] = b < nblk ? bt[b] : -1;
-            }
-            float sc[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int b = b0 + (u * kPrefillWaves + wave_id) * 4 + grp;
-                const bool in = id[u] >= 0 && b * kBlock + n < min(wg_max, t);
-                sc[u] = in ? a.cv.v_scale[((size_t)id[u] * a.H_k + g) * kBlock + n] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) mx = fmaxf(mx, sc[u]);      // (fmaxf drops a NaN)
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        if (lane == 0) vmax_of_wave[wave_id] = mx;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kPrefillWaves; ++i) mx = fmaxf(mx, vmax_of_wave[i]);
-        // mx = f * 2^e with f in [1, 2): vnorm = 2^-(e+1), exact; nothing to normalise if no scale is positive
-        const uint32_t ebits = (__builtin_bit_cast(uint32_t, mx) >> 23) & 0xffu;
-        if (mx > 0.0f && ebits > 0u && ebits < 253u) {
-            vnorm = __builtin_bit_cast(float, (253u - ebits) << 23);
-            vdenorm = __builtin_bit_cast(float, (ebits + 1u) << 23);
-        }
-    }
-
+    float vnorm = 1.0f, vdenorm = 1.0f;                       // set by the pass over the v_scales below
 
     float m[NR];
     floatx4 lacc[NR];       // rows 0 and 1 (lanes of group 0, registers 0 and 1): the row sums / 2^8
@@ -528,17 +552,78 @@ prefill_chunk_kernel(const PrefillArgs a)
     // s_lo .. s_hi-1: all of them, or one of `parts` equal runs in a split launch (an empty run
     // leaves the neutral partial m = kNoReference, l = 0).
     const int num_stages = (num_groups + GPS - 1) / GPS;
-    const int s_lo = (int)((long long)num_stages * part / parts);
-    const int s_hi = (int)((long long)num_stages * (part + 1) / parts);
+    const int s_lo = wave_uniform((int)((long long)num_stages * part / parts));
+    const int s_hi = wave_uniform((int)((long long)num_stages * (part + 1) / parts));
     const int g_end = min(num_groups, s_hi * GPS);            // groups below this one are mine
     auto slot = [&](int si, int sub) { return lds + ((si & 1) * GPS + sub) * St::kBytes; };
     // (a wave keeps registers for the sub-groups of its own team)
-    uint32_t ids = load_ids(s_lo);
+    uint32_t ids;
+    auto issue_first_stage = [&]() {
 #pragma unroll
-    for (int sub = 0; sub < GPS; ++sub)
-        if (owner(sub) == team && s_lo * GPS + sub < g_end)
-            produce_issue(s_lo * GPS + sub, id_of(ids, own_index(sub), 0), id_of(ids, own_index(sub), 1),
-                          prs[own_index(sub)], pscs[own_index(sub)]);
+        for (int sub = 0; sub < GPS; ++sub)
+            if (owner(sub) == team && s_lo * GPS + sub < g_end)
+                produce_issue(s_lo * GPS + sub, id_of(ids, own_index(sub), 0), id_of(ids, own_index(sub), 1),
+                              prs[own_index(sub)], pscs[own_index(sub)]);
+    };
+    // ---- the pair's largest v_scale as a power of two.  The weights P * v_scale enter the second
+    // product as fp16 (5 exponent bits); value rows can be of any magnitude (an E5M2 cache's scales
+    // are 2^-7 of an E4M3 cache's, small value rows' smaller still), so every v_scale is divided by
+    // the power of two just above the largest one among the tokens this workgroup reads: the
+    // weights of the rows that matter then sit at fp16's upper end whatever the rows' magnitude.
+    // The row sum divides each weight by the same normalised scale, so the factor stays in the
+    // numerator alone and is taken out, exactly, in the final division.  One pass over the pair's
+    // scales (64 bytes per block) before the first stage is stored; its two dependent round trips
+    // (block numbers, scales) run beside the first stage's own two (block numbers, tiles), and a
+    // later batch's block numbers beside the scales of the one before.
+    constexpr bool kIssueEarly = FP8 && !BIG && KV != COOPT_KV_E5M2;
+    if constexpr (kIssueEarly) ids = load_ids(s_lo);
+    if constexpr (FP8) {
+        __shared__ float vmax_of_wave[kPrefillWaves];
+        float mx = 0.0f;
+        constexpr int kBatch = 8;                          // loads in flight per lane
+        constexpr int kPass = 4 * kPrefillWaves * kBatch;  // blocks per pass of the workgroup
+        int id[kBatch];
+        auto batch_ids = [&](int b0) {
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {             // lane group grp takes block b, all 16 tokens
+                const int b = b0 + (u * kPrefillWaves + wave_id) * 4 + grp;
+                id[u] = b < nblk ? bt[b] : -1;
+            }
+        };
+        const int in_cache = min(wg_max, t);
+        batch_ids(0);
+        for (int b0 = 0; b0 < nblk; b0 += kPass) {
+            float sc[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int b = b0 + (u * kPrefillWaves + wave_id) * 4 + grp;
+                const bool in = id[u] >= 0 && b * kBlock + n < in_cache;
+                sc[u] = in ? a.cv.v_scale[((size_t)id[u] * a.H_k + g) * kBlock + n] : 0.0f;
+            }
+            if (b0 + kPass < nblk) batch_ids(b0 + kPass);
+            if constexpr (kIssueEarly) {
+                if (b0 == 0) issue_first_stage();
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) mx = fmaxf(mx, sc[u]);      // (fmaxf drops a NaN)
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        if (lane == 0) vmax_of_wave[wave_id] = mx;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPrefillWaves; ++i) mx = fmaxf(mx, vmax_of_wave[i]);
+        // mx = f * 2^e with f in [1, 2): vnorm = 2^-(e+1), exact; nothing to normalise if no scale is positive
+        const uint32_t ebits = (__builtin_bit_cast(uint32_t, mx) >> 23) & 0xffu;
+        if (mx > 0.0f && ebits > 0u && ebits < 253u) {
+            vnorm = __builtin_bit_cast(float, (253u - ebits) << 23);
+            vdenorm = __builtin_bit_cast(float, (ebits + 1u) << 23);
+        }
+    }
+    if constexpr (!kIssueEarly) {
+        ids = load_ids(s_lo);
+        issue_first_stage();
+    }
     ids = load_ids(s_lo + 1);
     uint32_t ids_next = load_ids(s_lo + 2);
 #pragma unroll
@@ -591,11 +676,11 @@ prefill_chunk_kernel(const PrefillArgs a)
         // column n's sum sits in rows 0 and 1 of lacc: lane (n, 0), registers 0 and 1
         const float L = __shfl(lacc[r][0] + lacc[r][1], n) * 256.0f;
         // (the 2^kPShift common to acc and l cancels; the normaliser of the v_scales is in acc alone)
-        if (a.split) {
+        if (tail_wg) {
             // this run's share of the tile: reference, row sum and unnormalised sums per column
-            if (first_tile + r < end_tile) {
-                float* dst = a.part + (((size_t)pair * a.tail_cap + (first_tile + r - a.tile_base)) * parts + part) *
-                                          (16 * (HEAD_DIM + 2));
+            if (first + r < count) {
+                const int tile = tile_of[r] - base_tile;
+                float* dst = a.part + (((size_t)pair * a.tail_cap + tile) * parts + part) * (16 * (HEAD_DIM + 2));
                 if (grp == 0) {
                     dst[n] = m[r];
                     dst[16 + n] = L;
@@ -607,9 +692,10 @@ prefill_chunk_kernel(const PrefillArgs a)
             continue;
         }
         const float inv = (1.0f / L) * vdenorm;
-        const int row = row0[r] + n;
-        if (first_tile + r < end_tile && row < C) {
-            half_t* dst = a.out + ((size_t)(qs + row) * a.H_q + head[r]) * HEAD_DIM + 4 * grp;
+        const int hh = wave_uniform(tile_of[r] / tiles_per_head);
+        const int row = (tile_of[r] - hh * tiles_per_head) * 16 + n;
+        if (first + r < count && row < C) {
+            half_t* dst = a.out + ((size_t)(qs + row) * a.H_q + g * a.G + hh) * HEAD_DIM + 4 * grp;
 #pragma unroll
             for (int c = 0; c < HEAD_DIM / 16; ++c) {
                 half4_t h;
@@ -640,7 +726,7 @@ prefill_split_merge_kernel(const PrefillArgs a)
     const int n = (blockIdx.x % BPT) * RPB + threadIdx.x / LPR;      // row of the tile
     const int piece = threadIdx.x % LPR;
     const int pair = (int)(id / a.tail_cap);
-    const int tile = a.tile_base + (int)(id - (long long)pair * a.tail_cap);
+    const int tile = a.tile_limit + (int)(id - (long long)pair * a.tail_cap);
     const int seq = pair / a.H_k;
     const int g = pair - seq * a.H_k;
     const int parts = a.split;
@@ -834,6 +920,14 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     const int pairs8 = lp.pairs8, a_per_pair = lp.a_per_pair, b_per_pair = lp.b_per_pair;
     const bool split = lp.parts >= 2;
     const int split_per_pair = lp.split_per_pair();
+    a.xcd_pairs = pairs8 / 8;
+    // Turn by turn, so that the longest streams of all pairs start first and the launch ends evenly,
+    // while the streams of all of an XCD's pairs can share its 4 MB L2; else pair after pair, whose
+    // workgroups then read their stream together.  (8 pairs of 2.3 MB an XCD: 760 us a pass by
+    // pair, 770 turn by turn.  The table's width bounds what the host does not see, the lengths.)
+    const long long token_bytes = (sh->kv_dtype == COOPT_KV_FP16 ? 4LL : 2LL) * sh->head_dim +
+                                  (sh->kv_dtype == COOPT_KV_FP16 ? 0 : 8);
+    a.by_pair = a.xcd_pairs * (long long)sh->max_blocks_per_seq * kBlock * token_bytes > kPrefillXcdL2;
     if ((long long)pairs8 * (a_per_pair + b_per_pair + split_per_pair) > 0x7fffffffLL) return COOPT_ERR_SHAPE;
     // 256 / (d/4) rows per workgroup of the merge: two workgroups per tile at d = 128, one at 64
     const long long merge_wgs = (long long)a.num_pairs * lp.rest * (sh->head_dim == 128 ? 2 : 1);
@@ -847,22 +941,19 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     do {                                                                                            \
         a.tile_base = 0;                                                                            \
         a.tile_limit = (b_per_pair || split) ? a_per_pair * lp.wg_tiles : 0x7fffffff;               \
-        a.wgs_per_pair = a_per_pair;                                                                \
-        if (a_per_pair > 0)                                                                         \
-            hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, NR, BIG>),                              \
-                               dim3((unsigned)((long long)pairs8 * a_per_pair)), block, lds, stream, a); \
-        a.tile_base = a.tile_limit;                                                                 \
-        a.tile_limit = 0x7fffffff;                                                                  \
+        a.blocks_per_pair = a_per_pair;                                                             \
         if (split) {                                                                                \
-            a.wgs_per_pair = split_per_pair;                                                        \
             a.part = (float*)workspace;                                                             \
             a.split = lp.parts;                                                                     \
+            a.split_blocks = split_per_pair / lp.parts;                                             \
             a.tail_cap = lp.rest;                                                                   \
-            hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, NR, BIG>),                              \
-                               dim3((unsigned)((long long)pairs8 * split_per_pair)), block, lds, stream, a); \
+        }                                                                                           \
+        hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, NR, BIG>),                                  \
+                           dim3((unsigned)((long long)pairs8 * (a_per_pair + split_per_pair))), block, lds, \
+                           stream, a);                                                              \
+        if (split)                                                                                  \
             hipLaunchKernelGGL((prefill_split_merge_kernel<D>), dim3((unsigned)merge_wgs), dim3(256), \
                                0, stream, a);                                                       \
-        }                                                                                           \
     } while (0)
 #define COOPT_PREFILL(D, KV, BIG)                                                                   \
     do {                                                                                            \
@@ -871,7 +962,9 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
         } else {                                                                                    \
             COOPT_PREFILL_FULL(D, KV, BIG, 2);                                                      \
             if (!split && b_per_pair) {                                                             \
-                a.wgs_per_pair = b_per_pair;                                                        \
+                a.tile_base = a.tile_limit;                                                         \
+                a.tile_limit = 0x7fffffff;                                                          \
+                a.blocks_per_pair = b_per_pair;                                                     \
                 hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, 1, BIG>),                           \
                                    dim3((unsigned)((long long)pairs8 * b_per_pair)), block, lds, stream, a); \
             }                                                                                       \

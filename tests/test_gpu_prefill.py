@@ -119,6 +119,33 @@ def test_two_launch_split_every_row(oracle_mod, kv_dtype, chunks, with_workspace
     assert_close(out.cpu().numpy().astype(np.float64), ref, f"two launches {kv_dtype} {chunks}")
 
 
+@pytest.mark.parametrize("with_workspace", [False, True])
+@pytest.mark.parametrize("kv_dtype,max_blocks", [("e4m3", 32), ("e4m3", 400), ("fp16", 32)])
+def test_order_of_tiles_and_workgroups(oracle_mod, kv_dtype, max_blocks, with_workspace):
+    """48 pairs of up to 95 tiles: with a workspace 80 of them whole and 15 split, so the cut lies
+    inside the fifth head (tile 80 = head 4, rows 64..79), and every sequence has its own number of
+    tiles: none of the split ones, some, all.  The 32-block table keeps an XCD's streams within its
+    L2 (workgroups turn by turn), the 400-block one does not (pair by pair); histories longer and
+    shorter than a third of the chunk put the split workgroups behind, among or ahead of the rest."""
+    chunks, history = [300, 299, 33, 1, 150, 290], [0, 210, 16, 130, 40, 3]
+    S, H_q, H_k, d = len(chunks), 40, 8, 128
+    w = workloads.make_custom("order", seed=91, S=S, H_q=H_q, H_k=H_k, d=d, B=16, NB=160, max_blocks=max_blocks,
+                              context_lens=[h + c for h, c in zip(history, chunks)], kv_dtype=kv_dtype)
+    query_start = np.zeros(S + 1, dtype=np.int32)
+    query_start[1:] = np.cumsum(chunks)
+    rows = int(query_start[-1])
+    q = np.random.default_rng(92).standard_normal((rows, H_q, d), dtype=np.float32).astype(np.float16)
+    cache = oracle_fill(oracle_mod, w)
+    ref = oracle_mod.paged_gqa_prefill_chunk(q, *cache, w.block_tables, w.context_lens, query_start, H_q=H_q,
+                                             H_k=H_k, d=d, B=16, softmax_scale=w.softmax_scale)
+    out = torch.full((rows, H_q, d), -7.0, dtype=torch.float16, device="cuda")
+    need = _prefill_call(with_workspace, dev(q.view(np.uint16)), cache_to_dev(cache), dev(w.block_tables),
+                         dev(w.context_lens), dev(query_start), rows, max(chunks), out, shape_of(w))
+    torch.cuda.synchronize()
+    assert not with_workspace or need == S * H_k * 15 * 5 * 16 * 130 * 4
+    assert_close(out.cpu().numpy().astype(np.float64), ref, f"order {kv_dtype} {max_blocks}")
+
+
 def test_chunked_prefill_full_size(oracle_mod, record_property):
     """Full configuration in the launch shape the benchmark times.  The oracle computes every row
     of one whole sequence (512 rows x 40 heads over 8192 + 512 tokens: the stage pipeline 136
