@@ -80,28 +80,59 @@ kv_write_fp8_kernel(const half_t* __restrict__ k, const half_t* __restrict__ v,
 
 // ---- bulk form (prefill chunks, cache fills): many tokens per call.
 //
-// The row-per-wavefront kernel above stores a row's V codes one byte at a time (the V tile keeps
-// four tokens of one dim in a dword), which is fine for one token per sequence and slow for
-// thousands.  Here 16 dims (one 16-byte K chunk) belong to a lane, d/16 lanes make a row and a
-// wavefront takes 64/(d/16) CONSECUTIVE tokens of one KV head: K is one 16-byte store per lane;
-// and wherever four consecutive tokens sit in four consecutive slots of one block, starting at a
-// multiple of four -- the usual case of a chunk written into fresh blocks -- their V codes are
-// exchanged between the four rows' lanes and leave as whole dwords.  Any other slot pattern
-// (skipped tokens, scattered slots) falls back to byte stores, row by row.  Same arithmetic as the
-// row kernel, hence the same bytes.
+// The row-per-wavefront kernel above stores a row's V codes one by one (the V tile keeps four tokens
+// of one dim side by side), which is fine for one token per sequence and slow for thousands.  A cache
+// fill reads and writes each byte once and is bound by HBM if its stores are whole lines, so here a
+// workgroup takes a window of consecutive tokens of one KV head:
+//   * one 16-byte K chunk (16 dims of a one-byte cache, 8 of fp16) belongs to a lane, which asks for
+//     all its rows before anything depends on a slot, and stores its K chunks as they are;
+//   * the V rows meet in LDS, from where every QUAD -- four consecutive tokens in four consecutive
+//     slots from a multiple of four on -- leaves as whole 16-byte pieces of the V tile, 256 bytes
+//     side by side per 16-dim group set;
+//   * quads are found in the slots, not by the tokens' place in the call: in a batch of ragged
+//     sequences most sequences start at a token index that is no multiple of four.  The quads whose
+//     first token lies among a window's first kOwn tokens are the window's own, and the three rows
+//     behind those (the overhang: 5 % more V rows read) are there to complete the last of them.
+// A token outside any quad (skipped neighbours, scattered slots, ragged ends) is stored element by
+// element from the registers.  Same arithmetic as the row kernel, hence the same bytes.
+//
+// Measured, 65 504 tokens x 8 heads x 128 dims to E4M3 in 32 ragged sequences (407 MB, 5.5 TB/s; a
+// large copy reaches 5.0): 131 us with quads at multiples of four of the call and a division per
+// element, 92 us with quads from the slots, staged V and the quotients below, 74 us with the cache
+// stores non-temporal (they pass the L2, where the rows' second readers find theirs; with the loads
+// non-temporal too: 108 us).
 
-// max over the groups of CH neighbouring lanes (CH a power of two)
-template <int CH>
-__device__ __forceinline__ float group_max(float a)
-{
-#pragma unroll
-    for (int o = CH / 2; o > 0; o >>= 1) a = fmaxf(a, __shfl_xor(a, o));
-    return a;
-}
+constexpr int kWindow = 64;                     // rows a workgroup holds
+constexpr int kOwn = kWindow - 3;               // ... of which this many are its own
 
 typedef unsigned int wu32x4 __attribute__((ext_vector_type(4)));
 
-// 16 fp16 values (two 16-byte words) -> their group's scale and 16 one-byte codes, element e in byte e
+// max over the groups of CH neighbouring lanes (CH = 4 or 8), on the vector ALU
+template <int CH>
+__device__ __forceinline__ float group_max(float a)
+{
+    static_assert(CH == 4 || CH == 8, "DPP steps below");
+    auto step = [&](auto ctrl) {
+        const int v = __builtin_bit_cast(int, a);
+        a = fmaxf(a, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, 0xf,
+                                                                           0xf, false)));
+    };
+    step(std::integral_constant<int, 0xb1>{});                       // quad_perm: lane ^ 1
+    step(std::integral_constant<int, 0x4e>{});                       // quad_perm: lane ^ 2
+    if constexpr (CH == 8) step(std::integral_constant<int, 0x141>{});   // row_half_mirror: the other quad
+    return a;
+}
+
+// 16 fp16 values (two 16-byte words) -> their group's scale and 16 one-byte codes, element e in byte e.
+//
+// The codes are defined through the correctly rounded quotient x / scale, one division per element:
+// some ten instructions each, which kept a fill busier than its memory traffic.  With r = RN(1 / scale)
+// (one division per row) and q0 = RN(x * r), the corrected q0 - RN(q0 * scale - x) * r is the correctly
+// rounded quotient itself (Markstein's theorem, 1990: r correctly rounded, q0 within one unit in the
+// last place; nothing here leaves the normal range), in three instructions.  tests/test_quotient.py
+// compares it with division over every absmax and element that fp16 has.  The signs make a zero keep
+// its sign, and an infinite scale (an infinity in the row) corrects by nothing: x * 0 is what x / infinity
+// is.
 template <int CH, int KV>
 __device__ __forceinline__ wu32x4 quantise_chunk(wu32x4 lo, wu32x4 hi, float& scale)
 {
@@ -121,13 +152,18 @@ __device__ __forceinline__ wu32x4 quantise_chunk(wu32x4 lo, wu32x4 hi, float& sc
     for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(x[e]));
     amax = group_max<CH>(amax);
     scale = scale_of_absmax<KV>(amax);
+    const float r = __fdiv_rn(1.0f, scale), minus_r = -r;
+    const float s = scale == INFINITY ? 0.0f : scale;
     wu32x4 codes;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         float y[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            y[e] = fminf(fmaxf(__fdiv_rn(x[4 * d + e], scale), -kFp8Max<KV>), kFp8Max<KV>);
+        for (int e = 0; e < 4; ++e) {
+            const float q0 = x[4 * d + e] * r;
+            const float off = __builtin_fmaf(q0, s, -x[4 * d + e]);
+            y[e] = fminf(fmaxf(__builtin_fmaf(off, minus_r, q0), -kFp8Max<KV>), kFp8Max<KV>);
+        }
         int w;
         if constexpr (KV == COOPT_KV_E5M2) {
             w = __builtin_amdgcn_cvt_pk_bf8_f32(y[0], y[1], 0, false);
@@ -143,97 +179,138 @@ __device__ __forceinline__ wu32x4 quantise_chunk(wu32x4 lo, wu32x4 hi, float& sc
 
 template <int HEAD_DIM, int KV>
 __global__ void __launch_bounds__(256)
-kv_write_fp8_bulk_kernel(const half_t* __restrict__ k, const half_t* __restrict__ v,
-                         const int64_t* __restrict__ slot_mapping,
-                         const uint32_t* __restrict__ skip_set, int num_tokens, int H_k,
-                         uint8_t* __restrict__ k_cache, uint8_t* __restrict__ v_cache,
-                         float* __restrict__ k_scale, float* __restrict__ v_scale)
+kv_write_bulk_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                     const int64_t* __restrict__ slot_mapping, const uint32_t* __restrict__ skip_set,
+                     int num_tokens, int H_k, uint8_t* __restrict__ k_cache,
+                     uint8_t* __restrict__ v_cache, float* __restrict__ k_scale,
+                     float* __restrict__ v_scale)
 {
-    constexpr int CH = HEAD_DIM / 16;           // lanes per row
-    constexpr int R = 64 / CH;                  // rows (consecutive tokens) per wavefront
-    const int lane = threadIdx.x & 63;
-    const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);       // token group * H_k + head
-    const int tg = unit / H_k, head = unit - tg * H_k;
-    if (tg * R >= num_tokens) return;
-    const int r = lane / CH, c = lane % CH;
-    const int tok = tg * R + r;
-    const bool in_range = tok < num_tokens;
-    const int64_t slot = in_range ? slot_mapping[tok] : -1;
-    const bool valid = slot >= 0 && !in_skip_set(skip_set, in_range ? tok : 0);   // Eq. 5
-    const int64_t blk = valid ? slot / kBlock : 0;
-    const int off = valid ? (int)(slot - blk * kBlock) : 0;
-    const size_t tile = (size_t)(blk * H_k + head);
+    constexpr bool FP8 = kIsFp8<KV>;
+    constexpr int ES = FP8 ? 1 : 2;             // bytes per cache element
+    constexpr int DPL = 16 / ES;                // dims per lane: one 16-byte cache chunk
+    constexpr int NW = FP8 ? 2 : 1;             // 16-byte words of fp16 that those are
+    constexpr int CH = HEAD_DIM / DPL;          // lanes per row
+    constexpr int RPP = 256 / CH;               // rows per pass of the workgroup
+    constexpr int NP = kWindow / RPP;           // passes
+    constexpr int RB = HEAD_DIM * ES + 16;      // a staged V row, skewed so that quads differ in bank
+    constexpr int NCQ = HEAD_DIM * ES / 64;     // 16-byte pieces per quad and n
+    __shared__ __attribute__((aligned(16))) unsigned char rows[kWindow * RB];
+    __shared__ int64_t slots[kWindow + 6];      // of rows -3 .. kWindow+2 (-1: no token, or filtered)
 
-    // ---- the quad (rows 4q .. 4q+3) stores V as dwords if its four tokens fill slots s, s+1, s+2,
-    // s+3 with s a multiple of four (then they share a block and a token quad of the tile)
-    const int j = r & 3;                                        // row inside its quad
-    const int64_t slot0 = __shfl(slot, (lane & ~(3 * CH)) | 0, 64);   // the quad's first row, same c
-    int fits = (valid && slot == slot0 + j && (slot0 & 3) == 0) ? 1 : 0;
-    fits &= __shfl_xor(fits, CH);                 // every lane takes part in both exchanges
-    fits &= __shfl_xor(fits, 2 * CH);
-    const bool quad = fits != 0;
-
-    const size_t row_at = ((size_t)(in_range ? tok : 0) * H_k + head) * HEAD_DIM + 16 * c;
-    const wu32x4* kp = reinterpret_cast<const wu32x4*>(k + row_at);
-    const wu32x4* vp = reinterpret_cast<const wu32x4*>(v + row_at);
-    const wu32x4 k_lo = kp[0], k_hi = kp[1], v_lo = vp[0], v_hi = vp[1];
-
-    float ks, vs;
-    const wu32x4 kc = quantise_chunk<CH, KV>(k_lo, k_hi, ks);
-    const wu32x4 vc = quantise_chunk<CH, KV>(v_lo, v_hi, vs);
-
-    uint8_t* ktile = k_cache + tile * (kBlock * HEAD_DIM);
-    uint8_t* vtile = v_cache + tile * (kBlock * HEAD_DIM);
-    if (valid) {
-        // K tile [d/16][16 tokens][16]
-        *reinterpret_cast<wu32x4*>(ktile + (c * kBlock + off) * 16) = kc;
-        if (c == 0) {
-            k_scale[tile * kBlock + off] = ks;
-            v_scale[tile * kBlock + off] = vs;
+    const int tid = threadIdx.x;
+    const int window = blockIdx.x / H_k, head = blockIdx.x - window * H_k;
+    const int base = window * kOwn;
+    const int c = tid % CH;
+    if (tid < kWindow + 6) {
+        const int tok = base - 3 + tid;
+        int64_t s = -1;
+        if (tid < kWindow + 3 && tok >= 0 && tok < num_tokens && !in_skip_set(skip_set, tok))   // Eq. 5
+            s = slot_mapping[tok];
+        slots[tid] = s;
+    }
+    wu32x4 kx[NP][NW], vx[NP][NW];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int tok = min(base + p * RPP + tid / CH, num_tokens - 1);
+        const size_t at = ((size_t)tok * H_k + head) * HEAD_DIM + DPL * c;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            kx[p][i] = reinterpret_cast<const wu32x4*>(k + at)[i];
+            vx[p][i] = reinterpret_cast<const wu32x4*>(v + at)[i];
         }
     }
+    __syncthreads();
 
-    // ---- V: lane j of a quad collects dword j (dims 4j .. 4j+3 of the chunk) of all four rows
-    uint32_t got[4];
-    got[0] = vc[0];
+    // is row r's token one of a quad?  The first token's row then is r - (its slot & 3).
+    auto in_quad = [&](int r, int64_t slot) {
+        const int j = (int)(slot & 3);
+        bool full = slot >= 0;
 #pragma unroll
-    for (int x = 1; x < 4; ++x) {
-        // send the partner (row j ^ x) its dword, receive mine from it
-        const int want = j ^ x;
-        const uint32_t send = want == 0 ? vc[0] : want == 1 ? vc[1] : want == 2 ? vc[2] : vc[3];
-        got[x] = (uint32_t)__shfl_xor((int)send, x * CH);
+        for (int m = 0; m < 4; ++m) full = full && slots[r + 3 - j + m] == slot - j + m;
+        return full;
+    };
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int r = p * RPP + tid / CH;
+        const int64_t slot = slots[r + 3];
+        float ks = 0.0f, vs = 0.0f;
+        wu32x4 kc, vc;
+        if constexpr (FP8) {
+            kc = quantise_chunk<CH, KV>(kx[p][0], kx[p][1], ks);
+            vc = quantise_chunk<CH, KV>(vx[p][0], vx[p][1], vs);
+        } else {
+            kc = kx[p][0];
+            vc = vx[p][0];
+        }
+        *reinterpret_cast<wu32x4*>(rows + r * RB + 16 * c) = vc;
+        if (slot >= 0 && r < kOwn) {
+            const int64_t blk = slot / kBlock;
+            const int off = (int)(slot - blk * kBlock);
+            const size_t tile = (size_t)(blk * H_k + head);
+            // K tile [chunks][16 tokens][16 bytes]
+            __builtin_nontemporal_store(kc, reinterpret_cast<wu32x4*>(
+                k_cache + tile * (kBlock * HEAD_DIM * ES) + (c * kBlock + off) * 16));
+            if (FP8 && c == 0) {
+                k_scale[tile * kBlock + off] = ks;
+                v_scale[tile * kBlock + off] = vs;
+            }
+            if (!in_quad(r, slot)) {
+                uint8_t* vtile = v_cache + tile * (kBlock * HEAD_DIM * ES);
+#pragma unroll
+                for (int n = 0; n < DPL; ++n) {
+                    if constexpr (FP8)
+                        vtile[v_tile_index<1>(off, DPL * c + n)] = (uint8_t)(vc[n >> 2] >> (8 * (n & 3)));
+                    else
+                        reinterpret_cast<uint16_t*>(vtile)[v_tile_index<2>(off, DPL * c + n)] =
+                            (uint16_t)(vc[n >> 1] >> (16 * (n & 1)));
+                }
+            }
+        }
     }
-    got[0] = j == 0 ? vc[0] : j == 1 ? vc[1] : j == 2 ? vc[2] : vc[3];
-    // got[x] = dword j of row j ^ x; order them by row
-    uint32_t g4[4];
-    {
-        const bool s1 = (j & 1) != 0, s2 = (j & 2) != 0;
-        const uint32_t a0 = s1 ? got[1] : got[0], a1 = s1 ? got[0] : got[1];
-        const uint32_t a2 = s1 ? got[3] : got[2], a3 = s1 ? got[2] : got[3];
-        g4[0] = s2 ? a2 : a0;
-        g4[1] = s2 ? a3 : a1;
-        g4[2] = s2 ? a0 : a2;
-        g4[3] = s2 ? a1 : a3;
+    __syncthreads();
+
+    // ---- V quads.  Their first tokens are at least four rows apart: at most one in rows 4b .. 4b+3.
+    // Sixteen lanes (n) take the quad of one b; four neighbouring quads of a block are 1 KB.
+    const int n = tid & 15, b = tid >> 4;
+    int lead = -1;
+    int64_t slot0 = 0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int r = 4 * b + m;
+        const int64_t s = slots[r + 3];
+        if ((s & 3) == 0 && r < kOwn && in_quad(r, s)) {
+            lead = r;
+            slot0 = s;
+        }
     }
-    if (quad) {
-        // byte b of g4[t] = code of dim 16c + 4j + b, token t of the quad: transpose to dwords of
-        // four tokens
-        const uint32_t lo01 = __builtin_amdgcn_perm(g4[1], g4[0], 0x05010400u);
-        const uint32_t hi01 = __builtin_amdgcn_perm(g4[1], g4[0], 0x07030602u);
-        const uint32_t lo23 = __builtin_amdgcn_perm(g4[3], g4[2], 0x05010400u);
-        const uint32_t hi23 = __builtin_amdgcn_perm(g4[3], g4[2], 0x07030602u);
-        const uint32_t out[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u),
-                                 __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
-                                 __builtin_amdgcn_perm(hi23, hi01, 0x05040100u),
-                                 __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
-        const int off0 = off - j;                                // the quad's first token
+    if (lead < 0) return;
+    const int64_t blk = slot0 / kBlock;
+    const int tq = (int)(slot0 - blk * kBlock) >> 2;
+    uint8_t* vtile = v_cache + (size_t)(blk * H_k + head) * (kBlock * HEAD_DIM * ES);
+    const unsigned char* src = rows + lead * RB + (n & ~(4 / ES - 1)) * ES;
+    // the element's place inside the aligned dword that holds it picks the shuffle's selector
+    const uint32_t e = (uint32_t)(n & (4 / ES - 1));
+    const uint32_t sel_lo = FP8 ? (0x0c0c0000u | ((4u + e) << 8) | e) : (e ? 0x07060302u : 0x05040100u);
+    const uint32_t sel_hi = FP8 ? (0x00000c0cu | ((4u + e) << 24) | (e << 16)) : sel_lo;
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-            *reinterpret_cast<uint32_t*>(vtile + v_tile_index<1>(off0, 16 * c + 4 * j + b)) = out[b];
-    } else if (valid) {
+    for (int cq = 0; cq < NCQ; ++cq) {
+        wu32x4 out;
 #pragma unroll
-        for (int n = 0; n < 16; ++n)
-            vtile[v_tile_index<1>(off, 16 * c + n)] = (uint8_t)(vc[n >> 2] >> (8 * (n & 3)));
+        for (int cc = 0; cc < 4 / ES; ++cc) {
+            const int at = 16 * ES * (cq * (4 / ES) + cc);
+            uint32_t d[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d[t] = *reinterpret_cast<const uint32_t*>(src + t * RB + at);
+            const uint32_t lo = __builtin_amdgcn_perm(d[1], d[0], sel_lo);
+            const uint32_t hi = __builtin_amdgcn_perm(d[3], d[2], sel_hi);
+            if constexpr (FP8) {
+                out[cc] = lo | hi;
+            } else {
+                out[2 * cc] = lo;
+                out[2 * cc + 1] = hi;
+            }
+        }
+        __builtin_nontemporal_store(out, reinterpret_cast<wu32x4*>(vtile + ((cq * 4 + tq) * 16 + n) * 16));
     }
 }
 
@@ -262,89 +339,23 @@ kv_write_fp16_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict_
     }
 }
 
-// The bulk form for fp16 caches: a pure scatter.  8 dims (one 16-byte K chunk) per lane, d/8 lanes
-// per row, 64/(d/8) consecutive tokens of one KV head per wavefront.  K is one 16-byte store per
-// lane.  The V tile keeps four tokens of one dim in 8 bytes: the lanes of an aligned run of four
-// tokens exchange their halves and store 8 bytes per dim, else 2 bytes each.
-template <int HEAD_DIM>
-__global__ void __launch_bounds__(256)
-kv_write_fp16_bulk_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                          const int64_t* __restrict__ slot_mapping,
-                          const uint32_t* __restrict__ skip_set, int num_tokens, int H_k,
-                          uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache)
-{
-    constexpr int CH = HEAD_DIM / 8;            // lanes per row
-    constexpr int R = 64 / CH;                  // rows (consecutive tokens) per wavefront: 4 or 8
-    const int lane = threadIdx.x & 63;
-    const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);       // token group * H_k + head
-    const int tg = unit / H_k, head = unit - tg * H_k;
-    if (tg * R >= num_tokens) return;
-    const int r = lane / CH, c = lane % CH;
-    const int tok = tg * R + r;
-    const bool in_range = tok < num_tokens;
-    const int64_t slot = in_range ? slot_mapping[tok] : -1;
-    const bool valid = slot >= 0 && !in_skip_set(skip_set, in_range ? tok : 0);   // Eq. 5
-    const int64_t blk = valid ? slot / kBlock : 0;
-    const int off = valid ? (int)(slot - blk * kBlock) : 0;
-    const size_t tile = (size_t)(blk * H_k + head);
-
-    const int j = r & 3;                                        // row inside its quad
-    const int64_t slot0 = __shfl(slot, lane & ~(3 * CH), 64);   // the quad's first row, same c
-    int fits = (valid && slot == slot0 + j && (slot0 & 3) == 0) ? 1 : 0;
-    fits &= __shfl_xor(fits, CH);                 // every lane takes part in both exchanges
-    fits &= __shfl_xor(fits, 2 * CH);
-    const bool quad = fits != 0;
-
-    const size_t row_at = ((size_t)(in_range ? tok : 0) * H_k + head) * HEAD_DIM + 8 * c;
-    const wu32x4 kc = *reinterpret_cast<const wu32x4*>(k + row_at);   // dims 8c .. 8c+7
-    const wu32x4 vc = *reinterpret_cast<const wu32x4*>(v + row_at);
-    uint16_t* ktile = k_cache + tile * (kBlock * HEAD_DIM);
-    uint16_t* vtile = v_cache + tile * (kBlock * HEAD_DIM);
-    // K tile [d/8][16 tokens][8]
-    if (valid) *reinterpret_cast<wu32x4*>(ktile + (c * kBlock + off) * 8) = kc;
-
-    // ---- V: lane j of a quad collects dword j (dims 8c + 2j, 8c + 2j + 1) of all four rows
-    uint32_t got[4];
-#pragma unroll
-    for (int x = 1; x < 4; ++x) {
-        const int want = j ^ x;
-        const uint32_t send = want == 0 ? vc[0] : want == 1 ? vc[1] : want == 2 ? vc[2] : vc[3];
-        got[x] = (uint32_t)__shfl_xor((int)send, x * CH);
-    }
-    got[0] = j == 0 ? vc[0] : j == 1 ? vc[1] : j == 2 ? vc[2] : vc[3];
-    uint32_t g4[4];                                              // g4[t] = dword j of row t
-    {
-        const bool s1 = (j & 1) != 0, s2 = (j & 2) != 0;
-        const uint32_t a0 = s1 ? got[1] : got[0], a1 = s1 ? got[0] : got[1];
-        const uint32_t a2 = s1 ? got[3] : got[2], a3 = s1 ? got[2] : got[3];
-        g4[0] = s2 ? a2 : a0;
-        g4[1] = s2 ? a3 : a1;
-        g4[2] = s2 ? a0 : a2;
-        g4[3] = s2 ? a1 : a3;
-    }
-    if (quad) {
-        const int off0 = off - j;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {           // dim 8c + 2j + h: the four tokens' halves
-            const uint32_t sel = h == 0 ? 0x05040100u : 0x07060302u;
-            const uint32_t t01 = __builtin_amdgcn_perm(g4[1], g4[0], sel);
-            const uint32_t t23 = __builtin_amdgcn_perm(g4[3], g4[2], sel);
-            typedef unsigned int wu32x2 __attribute__((ext_vector_type(2)));
-            *reinterpret_cast<wu32x2*>(vtile + v_tile_index<2>(off0, 8 * c + 2 * j + h)) = wu32x2{t01, t23};
-        }
-    } else if (valid) {
-#pragma unroll
-        for (int n = 0; n < 8; ++n)
-            vtile[v_tile_index<2>(off, 8 * c + n)] = (uint16_t)(vc[n >> 1] >> (16 * (n & 1)));
-    }
-}
-
 }  // namespace coopt
 
 using namespace coopt;
 
 // From this many tokens per call on, the bulk kernel (a call of a decode step has one per sequence).
 constexpr int kBulkWriteTokens = 64;
+
+template <int HEAD_DIM, int KV>
+static void launch_write_bulk(const void* k, const void* v, const int64_t* slot_mapping,
+                              const uint32_t* skip_set, int32_t num_tokens, int H_k, uint8_t* k_cache,
+                              uint8_t* v_cache, float* k_scale, float* v_scale, hipStream_t stream)
+{
+    const long long wgs = (long long)((num_tokens - 1) / kOwn + 1) * H_k;      // one per window and head
+    hipLaunchKernelGGL((kv_write_bulk_kernel<HEAD_DIM, KV>), dim3((unsigned)wgs), dim3(256), 0, stream,
+                       (const uint16_t*)k, (const uint16_t*)v, slot_mapping, skip_set, num_tokens, H_k,
+                       k_cache, v_cache, k_scale, v_scale);
+}
 
 template <int HEAD_DIM, int KV>
 static void launch_write_fp8(const void* k, const void* v, const int64_t* slot_mapping,
@@ -355,13 +366,8 @@ static void launch_write_fp8(const void* k, const void* v, const int64_t* slot_m
 {
     const dim3 block(256);
     if (num_tokens >= kBulkWriteTokens && scale_mode == COOPT_SCALE_TOKEN) {
-        // 64 / (d/16) consecutive tokens of one head per wavefront
-        constexpr int per_wave = 64 / (HEAD_DIM / 16);
-        const long long units = (long long)((num_tokens + per_wave - 1) / per_wave) * H_k;
-        const dim3 grid((unsigned)((units + 3) / 4));
-        hipLaunchKernelGGL((kv_write_fp8_bulk_kernel<HEAD_DIM, KV>), grid, block, 0, stream,
-                           (const half_t*)k, (const half_t*)v, slot_mapping, skip_set, num_tokens, H_k,
-                           k_cache, v_cache, k_scale, v_scale);
+        launch_write_bulk<HEAD_DIM, KV>(k, v, slot_mapping, skip_set, num_tokens, H_k, k_cache, v_cache,
+                                        k_scale, v_scale, stream);
         return;
     }
     const long long rows = (long long)num_tokens * H_k;
@@ -420,17 +426,14 @@ static int write_fp16(const void* k, const void* v, const int64_t* slot_mapping,
     hipStream_t stream = (hipStream_t)hip_stream;
     const dim3 block(256);
     if (num_tokens >= kBulkWriteTokens) {
-        const int per_wave = shape->head_dim == 128 ? 4 : 8;     // 64 / (d/8) tokens per wavefront
-        const long long units = (long long)((num_tokens + per_wave - 1) / per_wave) * shape->num_kv_heads;
-        const dim3 grid((unsigned)((units + 3) / 4));
         if (shape->head_dim == 128)
-            hipLaunchKernelGGL(kv_write_fp16_bulk_kernel<128>, grid, block, 0, stream, (const uint16_t*)k,
-                               (const uint16_t*)v, slot_mapping, skip_set, num_tokens,
-                               shape->num_kv_heads, (uint16_t*)k_cache, (uint16_t*)v_cache);
+            launch_write_bulk<128, COOPT_KV_FP16>(k, v, slot_mapping, skip_set, num_tokens,
+                                                  shape->num_kv_heads, (uint8_t*)k_cache, (uint8_t*)v_cache,
+                                                  nullptr, nullptr, stream);
         else
-            hipLaunchKernelGGL(kv_write_fp16_bulk_kernel<64>, grid, block, 0, stream, (const uint16_t*)k,
-                               (const uint16_t*)v, slot_mapping, skip_set, num_tokens,
-                               shape->num_kv_heads, (uint16_t*)k_cache, (uint16_t*)v_cache);
+            launch_write_bulk<64, COOPT_KV_FP16>(k, v, slot_mapping, skip_set, num_tokens,
+                                                 shape->num_kv_heads, (uint8_t*)k_cache, (uint8_t*)v_cache,
+                                                 nullptr, nullptr, stream);
         return launch_status();
     }
     const dim3 grid((unsigned)((rows + 3) / 4));

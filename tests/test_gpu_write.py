@@ -185,3 +185,50 @@ def test_bulk_calls_with_every_slot_pattern(oracle_mod, d, H_k, kv_dtype):
             d_write(dk[i:i + 40], dv[i:i + 40], ds[i:i + 40], *(devr if fp8 else devr[:2]), shape)
         torch.cuda.synchronize()
         _compare_caches(w, host, devr, f"rows {kv_dtype} d={d}: {name}")
+
+
+@pytest.mark.parametrize("kv_dtype", ["e4m3", "e5m2", "fp16"])
+@pytest.mark.parametrize("d,H_k", [(128, 3), (64, 2)])
+def test_bulk_windows_equal_rows(d, H_k, kv_dtype):
+    """The bulk kernel takes windows of 61 tokens and completes the last quad of a window from the next
+    one's rows; its quotients come from a reciprocal.  Call lengths around the window's edges, runs
+    from every slot offset in ragged pieces, over every kind of fp16 pattern (zeros of both signs,
+    subnormals, infinities, NaN): the bytes of the row kernel, and nothing written beside them."""
+    import paper_2602_09323_amd as coopt
+    from gpu_utils import dev
+    kv = {"e4m3": coopt.COOPT_KV_E4M3, "e5m2": coopt.COOPT_KV_E5M2, "fp16": coopt.COOPT_KV_FP16}[kv_dtype]
+    es, fp8 = (2, False) if kv_dtype == "fp16" else (1, True)
+    NB = 64
+    shape = coopt.Shape(1, H_k, H_k, d, 16, NB, NB, kv, 1.0)
+    write = coopt.kv_cache_write_fp8 if fp8 else coopt.kv_cache_write_fp16
+    rng = np.random.default_rng(17 * d + H_k)
+    for T in (64, 65, 121, 122, 123, 183, 186, 247):
+        for start in (0, 1, 2, 3):
+            # ragged pieces, each in fresh blocks from an offset of its own
+            slots, block = [], 1
+            while len(slots) < T:
+                n = int(min(rng.integers(3, 90), T - len(slots)))
+                first = block * 16 + (start if not slots else int(rng.integers(0, 16)))
+                slots += range(first, first + n)
+                block = (first + n + 15) // 16
+            slots = np.array(slots, np.int64)
+            assert slots.max() < NB * 16 and len(np.unique(slots)) == T
+            slots[rng.random(T) < 0.02] = -1
+            rows = [rng.integers(0, 1 << 16, (T, H_k, d)).astype(np.uint16) for _ in range(2)]
+            for r in rows:
+                r[0::5] &= 0xbfff                   # rows with neither infinity nor NaN
+                r[1::5] &= 0x8fff                   # ... of small values, subnormals among them
+                r[2::5, :, ::3] = 0x8000
+                r[3] = 0x8000                       # ... of nothing but zeros
+            k, v, ds = dev(rows[0]), dev(rows[1]), dev(slots)
+            got = []
+            for step in (T, 40):                    # one bulk call; calls that take the row kernel
+                c = [torch.full((NB, H_k, 16 * d * es), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(2)]
+                if fp8:
+                    c += [torch.full((NB, H_k, 16), -1.0, device="cuda") for _ in range(2)]
+                for i in range(0, T, step):
+                    write(k[i:i + step], v[i:i + step], ds[i:i + step], *c, shape)
+                torch.cuda.synchronize()
+                got.append([x.view(torch.uint8) for x in c])
+            for name, a, b in zip(("k", "v", "k_scale", "v_scale"), *got):
+                assert torch.equal(a, b), f"T={T} start={start}: {name}"
