@@ -46,6 +46,23 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     return v;
 }
 
+// Sum over the 64 lanes by the same steps.
+__device__ __forceinline__ float wave_sum(float a)
+{
+    auto step = [&](auto ctrl, auto rows) {
+        a += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a),
+                                                                   decltype(ctrl)::value,
+                                                                   decltype(rows)::value, 0xf, false));
+    };
+    step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr:1
+    step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});   // row_shr:2
+    step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});   // row_shr:4
+    step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});   // row_shr:8
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15 -> rows 1, 3
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});   // row_bcast:31 -> rows 2, 3
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, a), 63));
+}
+
 // The flattened schedule, derived identically by every wavefront that needs it.  Two axes run
 // side by side over [sequence][KV head][group]: the REAL one counts groups; the COST one also gives
 // every (sequence, KV head) pair `extra` units in front of its groups, the price (in group times)
@@ -849,12 +866,13 @@ flat_prepare_kernel(const FlatArgs a)
 
 // Merges the partials of each (sequence, query head) row.  The number of partials of the row's
 // (sequence, KV head) pair was left by the split kernel; pairs with no token at all have no writer,
-// so the context length decides whether the count is meaningful.  All loads of the first kSpec
-// partials are issued before the count is known (they lie inside the workspace whatever the count
-// is), so the kernel is one memory round trip deep for rows of up to kSpec partials.
-//   WIDE = false: one wavefront per row, four rows per workgroup.
-//   WIDE = true (long contexts, tens of partials per row): one workgroup per row; wavefront w takes
-//   partials w, w + 4, ... -- 4 * kSpec in the first round trip -- and the four sums meet in LDS.
+// so the context length decides whether the count is meaningful.  A wave-wide load takes 16 bytes per
+// lane, HEAD_DIM/4 lanes per partial row, hence 2 (d = 128) or 4 (d = 64) partials.  The first 8 of a
+// wavefront are asked for before the count is known (they lie inside the workspace whatever the count
+// is), so the kernel is one memory round trip deep for rows of that many.
+//   WIDE = false: one wavefront per row, four rows per workgroup; further partials 32 per round trip.
+//   WIDE = true (long contexts and few rows): one workgroup per row; the wavefronts take the wave-wide
+//   loads in turn -- 32 partials in the first round trip -- and the four sums meet in LDS.
 // Fused step: the merge launch begins with one wavefront per (sequence, KV head) pair (four to a
 // workgroup, ahead of the row workgroups: their stores take the longest, so they start first)
 // that stores the pair's new row into the cache --
@@ -904,12 +922,14 @@ __global__ void __launch_bounds__(256)
 flat_merge_kernel(const FlatArgs a)
 {
     constexpr int E = HEAD_DIM / 64;
-    constexpr int kSpec = 8;
-
-    constexpr int kStep = WIDE ? 4 : 1;                 // distance between a wavefront's partials
+    constexpr int LPR = HEAD_DIM / 4;                   // lanes per partial row
+    constexpr int PPW = 64 / LPR;                       // partials per wave-wide load
+    constexpr int kStep = WIDE ? 4 : 1;                 // wavefronts that share a row
+    constexpr int kSpec = 8 / PPW;                      // loads before the count is known
+    constexpr int kBatch = 32 / (kStep * PPW);          // loads in flight after that
     // Every load whose address does not depend on loaded data is issued before the first branch --
     // the schedule's tag, the pair's count, the length, the first 64 (max, sum) pairs and the first
-    // kSpec partial rows -- so that the kernel is two memory round trips long, not one per check.
+    // kSpec loads of partial rows -- so that the kernel is two memory round trips long, not one per check.
     const int wave = wave_uniform((int)(threadIdx.x >> 6));
     const int rows = a.num_seqs * a.H_q;
     // (fused step: the first append_wgs workgroups store the new rows, see below)
@@ -917,8 +937,11 @@ flat_merge_kernel(const FlatArgs a)
     const int row_id = WIDE ? wg : wg * 4 + wave;                              // seq * H_q + head
     const int row = min(max(row_id, 0), rows - 1);      // (a surplus wavefront reads the last row,
                                                         // an appending one the first)
-    const int first = WIDE ? wave : 0;                  // this wavefront's first partial
+    const int first = WIDE ? wave : 0;                  // this wavefront's first load of the row
     const int lane = threadIdx.x & 63;
+    const int sub = lane / LPR, piece = lane % LPR;
+    auto first_of = [&](int i) { return (i * kStep + first) * PPW; };    // first partial of load i
+    auto partial_of = [&](int i) { return first_of(i) + sub; };          // ... and the lane's
     const int seq = row / a.H_q;
     const int g = (row - seq * a.H_q) / a.G;
     // an appending wavefront's row, slot and length are asked for here, with everything else and
@@ -939,19 +962,19 @@ flat_merge_kernel(const FlatArgs a)
     const size_t base = (size_t)row * a.max_slots;
     const float* ml = a.max_logits + base;
     const float* es = a.exp_sums + base;
-    const float* po = a.tmp_out + base * HEAD_DIM + lane;
+    const float* po = a.tmp_out + base * HEAD_DIM + 4 * piece;
 
     // what the partials were laid out for: the schedule's tag, or the one the split kernel left
     const uint32_t* tag_at = a.sched ? a.sched : a.ws_header;
     const uint32_t tag = *tag_at;
     const int t = a.context_lens[wg < 0 ? app_seq : seq];
     int count = a.counts[seq * a.H_k + g];
-    float o_spec[kSpec][E];
+    floatx4 x_spec[kSpec];
 #pragma unroll
-    for (int j = 0; j < kSpec; ++j) {
-        const int p = first + kStep * j;
-#pragma unroll
-        for (int e = 0; e < E; ++e) o_spec[j][e] = p < a.max_slots ? po[(size_t)p * HEAD_DIM + 64 * e] : 0.0f;
+    for (int i = 0; i < kSpec; ++i) {
+        x_spec[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (partial_of(i) < a.max_slots)
+            x_spec[i] = *reinterpret_cast<const floatx4*>(po + (size_t)partial_of(i) * HEAD_DIM);
     }
     const float ml_l = lane < a.max_slots ? ml[lane] : 0.0f;
     const float es_l = lane < a.max_slots ? es[lane] : 0.0f;
@@ -969,78 +992,74 @@ flat_merge_kernel(const FlatArgs a)
     if (t <= 0) count = 0;
     count = wave_uniform(min(count, a.max_slots));
 
-    float o[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = 0.0f;
+    floatx4 o = {0.f, 0.f, 0.f, 0.f};
     float W = 1.0f;
     if (count > 0) {
         float M = lane < count ? ml_l : -INFINITY;
         for (int p = 64 + lane; p < count; p += 64) M = fmaxf(M, ml[p]);
-#pragma unroll
-        for (int s = 32; s > 0; s >>= 1) M = fmaxf(M, __shfl_xor(M, s));
+        M = wave_max(M);
         const float wv = lane < count ? es_l * __expf(ml_l - M) : 0.0f;   // weights of partials 0..63
         W = wv;
+        // w holds the weights of partials b0 .. b0+63; the load holds partials p0 .. p0+PPW-1 (unused
+        // slots may hold anything: selected away)
+        auto add = [&](floatx4 x, float w, int b0, int p0, int end) {
+            float wj = 0.0f;
 #pragma unroll
-        for (int j = 0; j < kSpec; ++j) {
-            const int p = first + kStep * j;                               // < 64
-            const float wj = __builtin_bit_cast(
-                float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wv), p));
-            if (p < count) {
-#pragma unroll
-                for (int e = 0; e < E; ++e) o[e] += wj * o_spec[j][e];
-            }
-        }
-        // further partials kSpec at a time, all loads of a batch in flight together (long contexts
-        // have tens of partials per row: one dependent load per partial would cost a round trip each).
-        // w holds the weights of partials b0 .. b0+63; the batch is partials p0, p0 + kStep, ...
-        auto add_batch = [&](float w, int b0, int p0, int end) {
-            float x[kSpec][E];
-#pragma unroll
-            for (int jj = 0; jj < kSpec; ++jj) {
-                const int p = min(p0 + kStep * jj, end - 1);
-#pragma unroll
-                for (int e = 0; e < E; ++e) x[jj][e] = po[(size_t)p * HEAD_DIM + 64 * e];
+            for (int k = 0; k < PPW; ++k) {
+                const float wk = __builtin_bit_cast(
+                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), (p0 + k - b0) & 63));
+                wj = sub == k ? wk : wj;
             }
 #pragma unroll
-            for (int jj = 0; jj < kSpec; ++jj) {
-                const int p = p0 + kStep * jj;
-                const float wj = __builtin_bit_cast(
-                    float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), (p - b0) & 63));
-                if (p < end) {
+            for (int c = 0; c < 4; ++c) o[c] += p0 + sub < end ? x[c] * wj : 0.0f;
+        };
+        // loads i0 .. i0+kBatch-1 of the window that begins at b0, all in flight together (long
+        // contexts have tens of partials per row: one dependent load per partial would cost a round
+        // trip each)
+        auto add_batch = [&](float w, int b0, int i0, int end) {
+            floatx4 x[kBatch];
 #pragma unroll
-                    for (int e = 0; e < E; ++e) o[e] += wj * x[jj][e];
-                }
-            }
+            for (int i = 0; i < kBatch; ++i)
+                x[i] = *reinterpret_cast<const floatx4*>(
+                    po + (size_t)min(b0 + partial_of(i0 + i), end - 1) * HEAD_DIM);
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) add(x[i], w, b0, b0 + first_of(i0 + i), end);
         };
         const int end0 = min(count, 64);
-        for (int p0 = first + kStep * kSpec; p0 < end0; p0 += kStep * kSpec) add_batch(wv, 0, p0, end0);
+#pragma unroll
+        for (int i = 0; i < kSpec; ++i) add(x_spec[i], wv, 0, first_of(i), end0);
+        for (int i0 = kSpec; first_of(i0) < end0; i0 += kBatch) add_batch(wv, 0, i0, end0);
         for (int b0 = 64; b0 < count; b0 += 64) {                          // very long contexts
             const int p = b0 + lane;
             const float w2 = p < count ? es[p] * __expf(ml[p] - M) : 0.0f;
             W += w2;
             const int end = min(b0 + 64, count);
-            for (int p0 = b0 + first; p0 < end; p0 += kStep * kSpec) add_batch(w2, b0, p0, end);
+            for (int i0 = 0; b0 + first_of(i0) < end; i0 += kBatch) add_batch(w2, b0, i0, end);
         }
+        W = wave_sum(W);
 #pragma unroll
-        for (int s = 32; s > 0; s >>= 1) W += __shfl_xor(W, s);
+        for (int s = LPR; s < 64; s <<= 1) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[c] += __shfl_xor(o[c], s);
+        }
     }
+    const float inv = count > 0 ? 1.0f / W : 0.0f;
     if constexpr (WIDE) {
-        __shared__ float sm[4][HEAD_DIM];
-#pragma unroll
-        for (int e = 0; e < E; ++e) sm[wave][lane + 64 * e] = o[e];
+        __shared__ __attribute__((aligned(16))) float sm[4][HEAD_DIM];
+        if (sub == 0) *reinterpret_cast<floatx4*>(&sm[wave][4 * piece]) = o;
         __syncthreads();
         if (wave == 0) {
-            const float inv = count > 0 ? 1.0f / W : 0.0f;
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 const int d = lane + 64 * e;
                 a.out[(size_t)row * HEAD_DIM + d] = (half_t)((sm[0][d] + sm[1][d] + sm[2][d] + sm[3][d]) * inv);
             }
         }
-    } else {
-        const float inv = count > 0 ? 1.0f / W : 0.0f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) a.out[(size_t)row * HEAD_DIM + lane + 64 * e] = (half_t)(o[e] * inv);
+    } else if (sub == 0) {
+        // (the caller's rows may begin at any 2-byte boundary)
+        typedef _Float16 row_piece_t __attribute__((ext_vector_type(4), aligned(2)));
+        *reinterpret_cast<row_piece_t*>(a.out + (size_t)row * HEAD_DIM + 4 * piece) = row_piece_t{
+            (half_t)(o[0] * inv), (half_t)(o[1] * inv), (half_t)(o[2] * inv), (half_t)(o[3] * inv)};
     }
 }
 
@@ -1281,7 +1300,11 @@ int launch_flat_merge(const int32_t* context_lens, void* workspace, void* out, c
         a.sched_tag = sched_layout(sh, plan, fused).tag;
     }
     const size_t rows = (size_t)sh->num_seqs * sh->num_q_heads;
-    const bool wide = a.max_slots > 32;      // rows may have tens of partials: a workgroup per row
+    // Rows may have tens of partials: a workgroup per row, unless there are rows enough to give every
+    // SIMD two wavefronts (32 partials a round trip either
+    // way; 96 sequences of 1 to 4001 tokens, d = 64, 3072 rows of up to 34 slots: 7.9 us with a workgroup
+    // per row, a step of two layers 103 us; 91 us with a wavefront per row).
+    const bool wide = a.max_slots > 32 && rows < 2048;
     long long wgs = wide ? (long long)rows : (long long)((rows + 3) / 4);
     if (append) {
         a.new_slots = append->slot_mapping;

@@ -218,3 +218,43 @@ def test_merge_refuses_partials_of_another_plan(oracle_mod):
     planned.paged_gqa_decode_merge(dlen, ws, out, shape)
     torch.cuda.synchronize()
     assert_close(out.cpu().numpy().astype(np.float64), ref, "merge with the split's plan")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("seqs,long_tokens", [(64, 16000), (64, 4500), (64, 600), (2, 16000), (2, 4500)])
+def test_merge_of_few_and_many_partials(d, seqs, long_tokens):
+    """One long sequence among short ones, fp16 cache: rows of 1 to some 90 partials -- within the loads
+    the merge issues before it knows the count, beyond them, and beyond the 64 weights a wavefront holds
+    -- with rows enough for a wavefront per row (64 x 32) and few (2 x 32: a workgroup per row).
+    Reference: float64 over the same fp16 K and V; |out| stays below 4, the plain bar."""
+    from gpu_utils import ABS_TOL
+    hq, hk = 32, 8
+    lens = [long_tokens] + [1 + 5 * i for i in range(1, seqs)]
+    lens[-1] = 0 if seqs > 2 else lens[-1]                    # an empty one: zeros
+    blocks = [(t + 15) // 16 for t in lens]
+    gen = torch.Generator(device="cuda"); gen.manual_seed(seqs + d)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda").half()
+    shape = coopt.Shape(seqs, hq, hk, d, 16, sum(blocks), max(blocks), coopt.COOPT_KV_FP16, d ** -0.5)
+    table = torch.zeros(seqs, max(blocks), dtype=torch.int32)
+    slots, at = [], 0
+    for s, (t, b) in enumerate(zip(lens, blocks)):
+        table[s, :b] = torch.arange(at, at + b, dtype=torch.int32)
+        slots.append(16 * at + torch.arange(t))
+        at += b
+    slots = torch.cat(slots).cuda()
+    k, v, q = rand(len(slots), hk, d), rand(len(slots), hk, d), rand(seqs, hq, d)
+    cache = [torch.zeros(sum(blocks), hk, 32 * d, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    coopt.kv_cache_write_fp16(k, v, slots, *cache, shape)
+    out = torch.full((seqs, hq, d), 7.0, dtype=torch.float16, device="cuda")
+    # partials that nobody wrote hold NaN
+    ws = torch.full((coopt.decode_workspace_bytes(shape),), 0xff, dtype=torch.uint8, device="cuda")
+    coopt.paged_gqa_decode(q, *cache, None, None, table.cuda(), torch.tensor(lens, dtype=torch.int32).cuda(),
+                           out, ws, shape)
+    got, q, k, v, first = out.double().cpu(), q.double().cpu(), k.double().cpu(), v.double().cpu(), 0
+    for s, t in enumerate(lens):
+        ref = torch.zeros(hq, d, dtype=torch.float64)
+        for h in range(hq if t else 0):
+            ks, vs = k[first:first + t, h // 4], v[first:first + t, h // 4]
+            ref[h] = torch.softmax(ks @ q[s, h] * d ** -0.5, 0) @ vs
+        first += t
+        assert (got[s] - ref).abs().max() < ABS_TOL, f"sequence {s} of {t} tokens"
