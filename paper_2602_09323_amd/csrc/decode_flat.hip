@@ -1301,9 +1301,9 @@ int launch_flat_merge(const int32_t* context_lens, void* workspace, void* out, c
     }
     const size_t rows = (size_t)sh->num_seqs * sh->num_q_heads;
     // Rows may have tens of partials: a workgroup per row, unless there are rows enough to give every
-    // SIMD two wavefronts (32 partials a round trip either
-    // way; 96 sequences of 1 to 4001 tokens, d = 64, 3072 rows of up to 34 slots: 7.9 us with a workgroup
-    // per row, a step of two layers 103 us; 91 us with a wavefront per row).
+    // SIMD two wavefronts (32 partials a round trip either way).  96 sequences of 1 to 4001 tokens,
+    // d = 64, 3072 rows of up to 34 slots: a workgroup per row takes 7.9 us a layer and a pass of two
+    // layers 103 us; with a wavefront per row the pass takes 91 us.
     const bool wide = a.max_slots > 32 && rows < 2048;
     long long wgs = wide ? (long long)rows : (long long)((rows + 3) / 4);
     if (append) {
