@@ -736,7 +736,7 @@ prefill_split_merge_kernel(const PrefillArgs a)
     floatx4 x[kPrefillMaxParts];
 #pragma unroll
     for (int p = 0; p < kPrefillMaxParts; ++p) {
-        // (a slot past the last part repeats it, at weight zero: no branch between the loads)
+        // (a slot past the last part loads that part again: no branch between the loads)
         const float* pp = p0 + (size_t)min(p, parts - 1) * kPart;
         m[p] = pp[n];
         l[p] = pp[16 + n];
@@ -757,9 +757,12 @@ prefill_split_merge_kernel(const PrefillArgs a)
     floatx4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < kPrefillMaxParts; ++p) {
-        const float e = p < parts ? __builtin_amdgcn_exp2f(m[p] - M) : 0.0f;
-        den += l[p] * e;
-        o += x[p] * e;
+        // (left out, not weighted by zero: a sum may be infinite, and infinity * 0 is no number)
+        if (p < parts) {
+            const float e = __builtin_amdgcn_exp2f(m[p] - M);
+            den += l[p] * e;
+            o += x[p] * e;
+        }
     }
     const float inv = 1.0f / den;
     half4_t h;

@@ -6,7 +6,7 @@ import torch
 import paper_2602_09323_amd as coopt
 import workloads
 from gpu_utils import alloc_dev_cache, assert_close, cache_to_dev, dev, hip_write, shape_of
-from helpers import oracle_fill
+from helpers import oracle_fill, v_logical, v_store_logical
 
 pytestmark = pytest.mark.gpu
 
@@ -144,6 +144,33 @@ def test_order_of_tiles_and_workgroups(oracle_mod, kv_dtype, max_blocks, with_wo
     torch.cuda.synchronize()
     assert not with_workspace or need == S * H_k * 15 * 5 * 16 * 130 * 4
     assert_close(out.cpu().numpy().astype(np.float64), ref, f"order {kv_dtype} {max_blocks}")
+
+
+@pytest.mark.parametrize("S,H_q,H_k,d,hist,C,parts", [(2, 40, 8, 128, 544, 400, 2), (1, 40, 40, 128, 1056, 333, 3),
+                                                       (8, 40, 8, 64, 512, 16, 4), (1, 40, 8, 128, 1024, 16, 7)])
+def test_infinite_value_rows(oracle_mod, S, H_q, H_k, d, hist, C, parts):
+    """An uncompressed cache may hold an infinity.  Every query row sees the token at the history's
+    end (in the last run of a split stream) with +inf in one dimension of its value row, and token 1
+    (in the first run) with -inf in another: those two outputs are the infinities themselves through
+    both entry points, whatever the number of runs the merge combines, and the other dimensions are
+    what they are without them."""
+    w = workloads.make_custom("inf", seed=58, S=S, H_q=H_q, H_k=H_k, d=d, B=16, NB=S * ((hist + C) // 16 + 2),
+                              context_lens=[hist + C] * S, new_per_seq=C, kv_dtype="fp16")
+    cache = oracle_fill(oracle_mod, w)
+    ref = _oracle_prefill(oracle_mod, w, cache)
+    v = v_logical(w, cache[1])
+    for s in range(S):
+        v[w.block_tables[s, (hist - 1) // 16], :, (hist - 1) % 16, 3] = np.inf
+        v[w.block_tables[s, 0], :, 1, 7] = -np.inf
+    v_store_logical(w, cache[1], v)
+    tiles = H_q // H_k * ((C + 15) // 16)
+    assert coopt.prefill_workspace_bytes(shape_of(w), C) == S * H_k * tiles * parts * 16 * (d + 2) * 4
+    dcache = cache_to_dev(cache)
+    for with_workspace in (False, True):
+        got = _hip_prefill(w, dcache, with_workspace=with_workspace)
+        assert (got[..., 3] == np.inf).all() and (got[..., 7] == -np.inf).all(), f"workspace: {with_workspace}"
+        rest = np.delete(np.arange(d), (3, 7))
+        assert_close(got[..., rest], ref[..., rest], f"infinite values, workspace: {with_workspace}")
 
 
 def test_chunked_prefill_full_size(oracle_mod, record_property):
