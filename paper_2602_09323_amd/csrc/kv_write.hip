@@ -8,6 +8,7 @@
 // this kernel is latency-, not bandwidth-bound and is kept simple; calls with many tokens take the
 // bulk kernel further down.
 #include "kv_quant.hpp"
+#include "launch_grid.hpp"
 
 namespace coopt {
 
@@ -85,25 +86,38 @@ kv_write_fp8_kernel(const half_t* __restrict__ k, const half_t* __restrict__ v,
 // fill reads and writes each byte once and is bound by HBM if its stores are whole lines, so here a
 // workgroup takes a window of consecutive tokens of one KV head:
 //   * one 16-byte K chunk (16 dims of a one-byte cache, 8 of fp16) belongs to a lane, which asks for
-//     all its rows before anything depends on a slot, and stores its K chunks as they are;
+//     its rows before anything depends on a slot, and stores its K chunk as it is;
 //   * the V rows meet in LDS, from where every QUAD -- four consecutive tokens in four consecutive
-//     slots from a multiple of four on -- leaves as whole 16-byte pieces of the V tile, 256 bytes
-//     side by side per 16-dim group set;
+//     slots from a multiple of four on -- leaves as whole 16-byte pieces of the V tile, one per lane,
+//     256 bytes side by side per 16-dim group set;
 //   * quads are found in the slots, not by the tokens' place in the call: in a batch of ragged
 //     sequences most sequences start at a token index that is no multiple of four.  The quads whose
 //     first token lies among a window's first kOwn tokens are the window's own, and the three rows
-//     behind those (the overhang: 5 % more V rows read) are there to complete the last of them.
+//     behind those (the overhang) are there to complete the last of them.
 // A token outside any quad (skipped neighbours, scattered slots, ragged ends) is stored element by
 // element from the registers.  Same arithmetic as the row kernel, hence the same bytes.
 //
-// Measured, 65 504 tokens x 8 heads x 128 dims to E4M3 in 32 ragged sequences (407 MB, 5.5 TB/s; a
-// large copy reaches 5.0): 131 us with quads at multiples of four of the call and a division per
-// element, 92 us with quads from the slots, staged V and the quotients below, 74 us with the cache
-// stores non-temporal (they pass the L2, where the rows' second readers find theirs; with the loads
-// non-temporal too: 108 us).
+// The window is what 256 lanes hold at one chunk each: 16 rows (fp16, d = 128) to 64 (one byte,
+// d = 64).  A window of 64 rows for every type, whose lanes took two to four chunks in turn, read less
+// overhang but left calls of up to a few thousand rows with few wavefronts and a long chain: 64 tokens
+// x 8 heads x 128 dims 4.4 us against 3.4 (fp16: 3.7 against 2.8), and in scattered slots, as a decode
+// step of 64 sequences has them, 7.1 against 4.5 (fp16: 6.3 against 3.1).
+//
+// The stores are non-temporal wherever they come in runs: they pass the L2, where the rows' second
+// readers find theirs.  16 384 tokens x 8 heads x 128 dims in turn to enough buffers to be new to the
+// caches: fp16 23.7 us against 28.9 with plain stores, E4M3 23.4 against 24.1.  (65 504 tokens to E4M3 in
+// 32 ragged sequences, 407 MB, more than the last-level cache holds: 76 against 86 us to the same
+// buffers again and again, but 92 against 86 to six sets of them in turn.)  A token whose neighbours in
+// the call are not its neighbours in the cache would pass the L2 in 16-byte pieces; its K stores are
+// plain (16 384 tokens in random slots, fp16, 8 heads: 102 us non-temporal, 60 us so).
 
-constexpr int kWindow = 64;                     // rows a workgroup holds
-constexpr int kOwn = kWindow - 3;               // ... of which this many are its own
+template <int HEAD_DIM, int KV>
+struct BulkWindow {
+    static constexpr int ES = kIsFp8<KV> ? 1 : 2;           // bytes per cache element
+    static constexpr int CH = HEAD_DIM * ES / 16;           // 16-byte cache chunks, and lanes, per row
+    static constexpr int kRows = 256 / CH;                  // rows a workgroup holds
+    static constexpr int kOwn = kRows - 3;                  // ... of which this many are its own
+};
 
 typedef unsigned int wu32x4 __attribute__((ext_vector_type(4)));
 
@@ -185,39 +199,38 @@ kv_write_bulk_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict_
                      uint8_t* __restrict__ v_cache, float* __restrict__ k_scale,
                      float* __restrict__ v_scale)
 {
+    using W = BulkWindow<HEAD_DIM, KV>;
     constexpr bool FP8 = kIsFp8<KV>;
-    constexpr int ES = FP8 ? 1 : 2;             // bytes per cache element
+    constexpr int ES = W::ES, CH = W::CH;
     constexpr int DPL = 16 / ES;                // dims per lane: one 16-byte cache chunk
     constexpr int NW = FP8 ? 2 : 1;             // 16-byte words of fp16 that those are
-    constexpr int CH = HEAD_DIM / DPL;          // lanes per row
-    constexpr int RPP = 256 / CH;               // rows per pass of the workgroup
-    constexpr int NP = kWindow / RPP;           // passes
+    constexpr int CW = CH < 8 ? CH : 8;         // chunks of a row side by side in a wavefront
     constexpr int RB = HEAD_DIM * ES + 16;      // a staged V row, skewed so that quads differ in bank
-    constexpr int NCQ = HEAD_DIM * ES / 64;     // 16-byte pieces per quad and n
-    __shared__ __attribute__((aligned(16))) unsigned char rows[kWindow * RB];
-    __shared__ int64_t slots[kWindow + 6];      // of rows -3 .. kWindow+2 (-1: no token, or filtered)
+    __shared__ __attribute__((aligned(16))) unsigned char rows[W::kRows * RB];
+    __shared__ int64_t slots[W::kRows + 6];     // of rows -3 .. kRows+2 (-1: no token, or filtered)
 
     const int tid = threadIdx.x;
-    const int window = blockIdx.x / H_k, head = blockIdx.x - window * H_k;
-    const int base = window * kOwn;
-    const int c = tid % CH;
-    if (tid < kWindow + 6) {
+    const int wg = (int)grid_index(blockIdx.x, blockIdx.y);
+    const int window = wg / H_k, head = wg - window * H_k;
+    const int base = window * W::kOwn;
+    if (base >= num_tokens) return;             // a surplus workgroup
+    // a wavefront's lanes cover 8 rows or more: a K chunk of 8 consecutive tokens is a whole line
+    const int wave = tid >> 6;
+    const int c = tid % CW + CW * (wave % (CH / CW));
+    const int r = (tid & 63) / CW + (64 / CW) * (wave / (CH / CW));
+    if (tid < W::kRows + 6) {
         const int tok = base - 3 + tid;
         int64_t s = -1;
-        if (tid < kWindow + 3 && tok >= 0 && tok < num_tokens && !in_skip_set(skip_set, tok))   // Eq. 5
+        if (tid < W::kRows + 3 && tok >= 0 && tok < num_tokens && !in_skip_set(skip_set, tok))   // Eq. 5
             s = slot_mapping[tok];
         slots[tid] = s;
     }
-    wu32x4 kx[NP][NW], vx[NP][NW];
+    wu32x4 kx[NW], vx[NW];
+    const size_t at = ((size_t)min(base + r, num_tokens - 1) * H_k + head) * HEAD_DIM + DPL * c;
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const int tok = min(base + p * RPP + tid / CH, num_tokens - 1);
-        const size_t at = ((size_t)tok * H_k + head) * HEAD_DIM + DPL * c;
-#pragma unroll
-        for (int i = 0; i < NW; ++i) {
-            kx[p][i] = reinterpret_cast<const wu32x4*>(k + at)[i];
-            vx[p][i] = reinterpret_cast<const wu32x4*>(v + at)[i];
-        }
+    for (int i = 0; i < NW; ++i) {
+        kx[i] = reinterpret_cast<const wu32x4*>(k + at)[i];
+        vx[i] = reinterpret_cast<const wu32x4*>(v + at)[i];
     }
     __syncthreads();
 
@@ -229,89 +242,89 @@ kv_write_bulk_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict_
         for (int m = 0; m < 4; ++m) full = full && slots[r + 3 - j + m] == slot - j + m;
         return full;
     };
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const int r = p * RPP + tid / CH;
-        const int64_t slot = slots[r + 3];
-        float ks = 0.0f, vs = 0.0f;
-        wu32x4 kc, vc;
-        if constexpr (FP8) {
-            kc = quantise_chunk<CH, KV>(kx[p][0], kx[p][1], ks);
-            vc = quantise_chunk<CH, KV>(vx[p][0], vx[p][1], vs);
-        } else {
-            kc = kx[p][0];
-            vc = vx[p][0];
+    const int64_t slot = slots[r + 3];
+    const bool mine = slot >= 0 && r < W::kOwn;
+    const bool quad = in_quad(r, slot);
+    const bool alone = slots[r + 2] != slot - 1 && slots[r + 4] != slot + 1;     // (never in a quad)
+    float ks = 0.0f, vs = 0.0f;
+    wu32x4 kc, vc;
+    if constexpr (FP8) {
+        kc = quantise_chunk<CH, KV>(kx[0], kx[1], ks);
+        vc = quantise_chunk<CH, KV>(vx[0], vx[1], vs);
+    } else {
+        kc = kx[0];
+        vc = vx[0];
+    }
+    *reinterpret_cast<wu32x4*>(rows + r * RB + 16 * c) = vc;
+    const int64_t blk = slot / kBlock;
+    const int off = (int)(slot - blk * kBlock);
+    const size_t tile = (size_t)(blk * H_k + head);
+    // K tile [chunks][16 tokens][16 bytes]
+    wu32x4* kdst = reinterpret_cast<wu32x4*>(k_cache + tile * (kBlock * HEAD_DIM * ES) + (c * kBlock + off) * 16);
+    if (mine) {
+        if (FP8 && c == 0) {
+            k_scale[tile * kBlock + off] = ks;
+            v_scale[tile * kBlock + off] = vs;
         }
-        *reinterpret_cast<wu32x4*>(rows + r * RB + 16 * c) = vc;
-        if (slot >= 0 && r < kOwn) {
-            const int64_t blk = slot / kBlock;
-            const int off = (int)(slot - blk * kBlock);
-            const size_t tile = (size_t)(blk * H_k + head);
-            // K tile [chunks][16 tokens][16 bytes]
-            __builtin_nontemporal_store(kc, reinterpret_cast<wu32x4*>(
-                k_cache + tile * (kBlock * HEAD_DIM * ES) + (c * kBlock + off) * 16));
-            if (FP8 && c == 0) {
-                k_scale[tile * kBlock + off] = ks;
-                v_scale[tile * kBlock + off] = vs;
-            }
-            if (!in_quad(r, slot)) {
-                uint8_t* vtile = v_cache + tile * (kBlock * HEAD_DIM * ES);
+        if (!quad) {
+            if (alone) *kdst = kc;
+            uint8_t* vtile = v_cache + tile * (kBlock * HEAD_DIM * ES);
 #pragma unroll
-                for (int n = 0; n < DPL; ++n) {
-                    if constexpr (FP8)
-                        vtile[v_tile_index<1>(off, DPL * c + n)] = (uint8_t)(vc[n >> 2] >> (8 * (n & 3)));
-                    else
-                        reinterpret_cast<uint16_t*>(vtile)[v_tile_index<2>(off, DPL * c + n)] =
-                            (uint16_t)(vc[n >> 1] >> (16 * (n & 1)));
-                }
+            for (int n = 0; n < DPL; ++n) {
+                if constexpr (FP8)
+                    vtile[v_tile_index<1>(off, DPL * c + n)] = (uint8_t)(vc[n >> 2] >> (8 * (n & 3)));
+                else
+                    reinterpret_cast<uint16_t*>(vtile)[v_tile_index<2>(off, DPL * c + n)] =
+                        (uint16_t)(vc[n >> 1] >> (16 * (n & 1)));
             }
         }
     }
     __syncthreads();
+    // (here, behind the barrier: in the other arm of the plain store the compiler makes one plain
+    // store of the two)
+    if (mine && !alone) __builtin_nontemporal_store(kc, kdst);
 
     // ---- V quads.  Their first tokens are at least four rows apart: at most one in rows 4b .. 4b+3.
-    // Sixteen lanes (n) take the quad of one b; four neighbouring quads of a block are 1 KB.
-    const int n = tid & 15, b = tid >> 4;
+    // Sixteen lanes (n) take one 64-byte piece (cq) per token of the quad of one b; four neighbouring
+    // quads of a block are 1 KB.
+    const int n = tid & 15, b = (tid >> 4) % (W::kRows / 4), cq = tid / (4 * W::kRows);
     int lead = -1;
     int64_t slot0 = 0;
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-        const int r = 4 * b + m;
-        const int64_t s = slots[r + 3];
-        if ((s & 3) == 0 && r < kOwn && in_quad(r, s)) {
-            lead = r;
+        const int rr = 4 * b + m;
+        const int64_t s = slots[rr + 3];
+        if ((s & 3) == 0 && rr < W::kOwn && in_quad(rr, s)) {
+            lead = rr;
             slot0 = s;
         }
     }
     if (lead < 0) return;
-    const int64_t blk = slot0 / kBlock;
-    const int tq = (int)(slot0 - blk * kBlock) >> 2;
-    uint8_t* vtile = v_cache + (size_t)(blk * H_k + head) * (kBlock * HEAD_DIM * ES);
+    const int64_t vblk = slot0 / kBlock;
+    const int tq = (int)(slot0 - vblk * kBlock) >> 2;
+    uint8_t* vtile = v_cache + (size_t)(vblk * H_k + head) * (kBlock * HEAD_DIM * ES);
     const unsigned char* src = rows + lead * RB + (n & ~(4 / ES - 1)) * ES;
     // the element's place inside the aligned dword that holds it picks the shuffle's selector
     const uint32_t e = (uint32_t)(n & (4 / ES - 1));
     const uint32_t sel_lo = FP8 ? (0x0c0c0000u | ((4u + e) << 8) | e) : (e ? 0x07060302u : 0x05040100u);
     const uint32_t sel_hi = FP8 ? (0x00000c0cu | ((4u + e) << 24) | (e << 16)) : sel_lo;
+    wu32x4 out;
 #pragma unroll
-    for (int cq = 0; cq < NCQ; ++cq) {
-        wu32x4 out;
+    for (int cc = 0; cc < 4 / ES; ++cc) {
+        const int at = 16 * ES * (cq * (4 / ES) + cc);
+        uint32_t d[4];
 #pragma unroll
-        for (int cc = 0; cc < 4 / ES; ++cc) {
-            const int at = 16 * ES * (cq * (4 / ES) + cc);
-            uint32_t d[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) d[t] = *reinterpret_cast<const uint32_t*>(src + t * RB + at);
-            const uint32_t lo = __builtin_amdgcn_perm(d[1], d[0], sel_lo);
-            const uint32_t hi = __builtin_amdgcn_perm(d[3], d[2], sel_hi);
-            if constexpr (FP8) {
-                out[cc] = lo | hi;
-            } else {
-                out[2 * cc] = lo;
-                out[2 * cc + 1] = hi;
-            }
+        for (int t = 0; t < 4; ++t) d[t] = *reinterpret_cast<const uint32_t*>(src + t * RB + at);
+        const uint32_t lo = __builtin_amdgcn_perm(d[1], d[0], sel_lo);
+        const uint32_t hi = __builtin_amdgcn_perm(d[3], d[2], sel_hi);
+        if constexpr (FP8) {
+            out[cc] = lo | hi;
+        } else {
+            out[2 * cc] = lo;
+            out[2 * cc + 1] = hi;
         }
-        __builtin_nontemporal_store(out, reinterpret_cast<wu32x4*>(vtile + ((cq * 4 + tq) * 16 + n) * 16));
     }
+    __builtin_nontemporal_store(out, reinterpret_cast<wu32x4*>(vtile + ((cq * 4 + tq) * 16 + n) * 16));
 }
 
 template <int HEAD_DIM>
@@ -351,8 +364,9 @@ static void launch_write_bulk(const void* k, const void* v, const int64_t* slot_
                               const uint32_t* skip_set, int32_t num_tokens, int H_k, uint8_t* k_cache,
                               uint8_t* v_cache, float* k_scale, float* v_scale, hipStream_t stream)
 {
-    const long long wgs = (long long)((num_tokens - 1) / kOwn + 1) * H_k;      // one per window and head
-    hipLaunchKernelGGL((kv_write_bulk_kernel<HEAD_DIM, KV>), dim3((unsigned)wgs), dim3(256), 0, stream,
+    // one workgroup per window and head
+    const Grid grid = grid_of((long long)((num_tokens - 1) / BulkWindow<HEAD_DIM, KV>::kOwn + 1) * H_k);
+    hipLaunchKernelGGL((kv_write_bulk_kernel<HEAD_DIM, KV>), dim3(grid.x, grid.y), dim3(256), 0, stream,
                        (const uint16_t*)k, (const uint16_t*)v, slot_mapping, skip_set, num_tokens, H_k,
                        k_cache, v_cache, k_scale, v_scale);
 }

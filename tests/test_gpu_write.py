@@ -190,9 +190,9 @@ def test_bulk_calls_with_every_slot_pattern(oracle_mod, d, H_k, kv_dtype):
 @pytest.mark.parametrize("kv_dtype", ["e4m3", "e5m2", "fp16"])
 @pytest.mark.parametrize("d,H_k", [(128, 3), (64, 2)])
 def test_bulk_windows_equal_rows(d, H_k, kv_dtype):
-    """The bulk kernel takes windows of 61 tokens and completes the last quad of a window from the next
-    one's rows; its quotients come from a reciprocal.  Call lengths around the window's edges, runs
-    from every slot offset in ragged pieces, over every kind of fp16 pattern (zeros of both signs,
+    """The bulk kernel takes windows of 13, 29 or 61 tokens (cache type and head size) and completes the
+    last quad of a window from the next one's rows; its quotients come from a reciprocal.  Call lengths
+    around the windows' edges, runs from every slot offset in ragged pieces with lone tokens between, over every kind of fp16 pattern (zeros of both signs,
     subnormals, infinities, NaN): the bytes of the row kernel, and nothing written beside them."""
     import paper_2602_09323_amd as coopt
     from gpu_utils import dev
@@ -202,7 +202,7 @@ def test_bulk_windows_equal_rows(d, H_k, kv_dtype):
     shape = coopt.Shape(1, H_k, H_k, d, 16, NB, NB, kv, 1.0)
     write = coopt.kv_cache_write_fp8 if fp8 else coopt.kv_cache_write_fp16
     rng = np.random.default_rng(17 * d + H_k)
-    for T in (64, 65, 121, 122, 123, 183, 186, 247):
+    for T in (64, 65, 66, 87, 88, 116, 121, 122, 123, 183, 186, 247):
         for start in (0, 1, 2, 3):
             # ragged pieces, each in fresh blocks from an offset of its own
             slots, block = [], 1
@@ -212,8 +212,9 @@ def test_bulk_windows_equal_rows(d, H_k, kv_dtype):
                 slots += range(first, first + n)
                 block = (first + n + 15) // 16
             slots = np.array(slots, np.int64)
-            assert slots.max() < NB * 16 and len(np.unique(slots)) == T
+            assert slots.max() < NB * 16 - 32 and len(np.unique(slots)) == T
             slots[rng.random(T) < 0.02] = -1
+            slots[9:-9:17] = NB * 16 - 1 - 2 * np.arange(len(slots[9:-9:17]))    # lone tokens
             rows = [rng.integers(0, 1 << 16, (T, H_k, d)).astype(np.uint16) for _ in range(2)]
             for r in rows:
                 r[0::5] &= 0xbfff                   # rows with neither infinity nor NaN
