@@ -366,6 +366,9 @@ int coopt_paged_gqa_reduce(const float* tmp_out, const float* max_logits, const 
  * (chunk included), local row i attends to tokens j < t_s - C_s + i + 1.
  *   q, out [query_start[S]][H_q][d] fp16;  query_start [S+1] int32 (device), increasing from 0
  *   num_query_rows: query_start[S] as known to the host (sizes the launch); C_s <= t_s
+ *   max_chunk_len: the largest C_s as known to the host, which sizes the launch (and the workspace
+ *   below).  Of a sequence with more rows than that some rows of out are left as they were; nothing
+ *   else is affected.
  */
 int coopt_paged_gqa_prefill_chunk(const void* q, const void* k_cache, const void* v_cache,
                                   const float* k_scale, const float* v_scale,

@@ -21,7 +21,7 @@ PROBE_LIB = os.path.join(HERE, "libcoopt_probe.so")      # measurement aid, not 
 SOURCES = ["kv_write.hip", "decode.hip", "decode_flat.hip", "prefill.hip", "gather.hip"]
 PROBE_SOURCES = ["probe.hip"]
 HEADERS = [os.path.join(CSRC, h) for h in ("common.hpp", "attn_tile.hpp", "kv_quant.hpp",
-                                          "decode_internal.hpp", "launch_grid.hpp")] + [
+                                          "decode_internal.hpp", "launch_grid.hpp", "prefill_deal.hpp")] + [
     os.path.join(ROOT, "include", "coopt_attn.h"), os.path.join(ROOT, "include", "coopt_probe.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-I" + os.path.join(ROOT, "include"),

@@ -35,10 +35,11 @@
 // 8 heads, d = 128): 156 us a pass with tiles by head, first rows first and the split streams in a
 // launch behind the whole ones, 100 us so; 8 x 512 rows over 8192 tokens 763 -> 744 us.
 #include "attn_tile.hpp"
+#include "prefill_deal.hpp"
 
 namespace coopt {
 
-struct PrefillArgs {
+struct PrefillArgs : PrefillDeal {
     const half_t* q;
     CacheView cv;
     const int32_t* block_tables;
@@ -48,61 +49,15 @@ struct PrefillArgs {
     int32_t H_q, H_k, G;
     int32_t max_blocks;
     int32_t pool_tiles;
-    int32_t num_pairs;        // num_seqs * H_k
-    int32_t xcd_pairs;        // pairs per XCD: num_pairs rounded up to a multiple of 8, over 8
-    int32_t by_pair;          // order of an XCD's workgroups (see the kernel)
-    int32_t blocks_per_pair;  // workgroups per pair over tiles [tile_base, tile_limit): whole streams
-    int32_t tile_base;
-    int32_t tile_limit;
     float scale_log2e;
-    // split workgroups, behind the whole-stream ones in the grid (the tiles from tile_limit on of
-    // every pair, `split` workgroups per 16 tiles: workgroup p of them streams the p-th of `split`
-    // equal runs of the pair's stages and leaves per tile 16 x (m, l) and the 16 x HEAD_DIM
-    // unnormalised sums in `part`, which a merge launch combines)
-    float* part;
-    int32_t split;            // parts, >= 2 (0: no such workgroups)
-    int32_t split_blocks;     // runs of 16 tiles per pair they cover
-    int32_t tail_cap;         // tiles per pair they cover (sizes `part`)
+    float* part;              // the split workgroups' partial rows, in the workspace
 };
 
-// The tiles [base, end) of a pair -- tile h T + i is rows 16i .. of head h, T tiles a head -- in the
-// order in which workgroups take them: by row, then by head.  A causal stream is as long as its
-// last row needs, so the 16 tiles of a workgroup should lie at neighbouring rows: by head, a
-// workgroup of 256 rows streams up to 240 tokens too far for most of them.
-struct TileOrder {
-    int T, base, end, hb, ib, he, ie;
-    __device__ __forceinline__ TileOrder(int tiles_per_head, int b, int e) : T(tiles_per_head), base(b), end(e)
-    {
-        // (wave_uniform: the quotients are made on the vector ALU; this keeps them out of its registers)
-        hb = wave_uniform(b / T);
-        ib = b - hb * T;
-        he = wave_uniform(e / T);
-        ie = e - he * T;
-    }
-    __device__ __forceinline__ int count() const { return end - base; }
-    // Position p (0 .. count-1) -> first row / 16 and head.  Row i has he - hb tiles of this range,
-    // one more from ib .. or up to ie (whichever of the two partial heads reaches it).
-    __device__ __forceinline__ void at(int p, int& i, int& h) const
-    {
-        const int N = he - hb, b1 = min(ib, ie), b2 = max(ib, ie);
-        const int c2 = ie > ib ? N + 1 : N - 1;                  // tiles per row between b1 and b2
-        const int n1 = b1 * N, n2 = n1 + (b2 - b1) * c2;
-        if (p < n1) i = p / N;
-        else if (p < n2) i = b1 + (p - n1) / c2;
-        else i = b2 + (p - n2) / max(N, 1);
-        i = wave_uniform(i);
-        h = p - (i * N + min(i, ie) - min(i, ib)) + hb + (i < ib ? 1 : 0);
-    }
-};
-
-constexpr int kPrefillWaves = 8;                // two teams of four producer roles
 constexpr int kPrefillGroupsPerStage = 4;      // two-block groups between two barriers
 // Groups of a stage produced by the first team (waves 0-3); the second team takes the rest.
 constexpr int kPrefillFirstTeamGroups = 3;
 constexpr float kNoReference = -1.0e30f;        // a running reference below every score
-constexpr int kPrefillMaxParts = 8;            // runs a split launch cuts a stream into, at most
 constexpr long long kPrefillXcdL2 = 4LL << 20;   // bytes of L2 per XCD
-constexpr int kPrefillCUs = 256;               // MI355X: the launch shape is planned for its CU count
 
 // Byte offsets inside one LDS stage (one group = blocks A and B of one KV head).
 template <int HEAD_DIM>
@@ -233,24 +188,8 @@ prefill_chunk_kernel(const PrefillArgs a)
     const int wave = wave_id & 3;                      // producer role inside its team
     const int team = wave_id >> 2;                     // which groups of a stage it produces: below
     const int n = lane & 15, grp = lane >> 4;
-    // all workgroups of a (sequence, KV head) pair on one XCD (ids go round-robin over 8 XCDs).
-    // `turn` = which of the pair's workgroups this is, longest stream first (below).  By pair: an
-    // XCD's whole-stream workgroups pair after pair, then its split ones; otherwise turn after turn
-    // of all its pairs.
-    const int k8 = blockIdx.x >> 3;
-    const int whole = a.xcd_pairs * a.blocks_per_pair;           // whole-stream workgroups per XCD
-    const int num_split = a.split * a.split_blocks;              // split ones per pair
-    int turn, xcd_pair;
-    if (a.by_pair) {
-        const int k = k8 < whole ? k8 : k8 - whole;
-        const int per = k8 < whole ? a.blocks_per_pair : num_split;
-        xcd_pair = wave_uniform(k / per);
-        turn = k - xcd_pair * per + (k8 < whole ? 0 : a.blocks_per_pair);
-    } else {
-        turn = wave_uniform(k8 / a.xcd_pairs);
-        xcd_pair = k8 - turn * a.xcd_pairs;
-    }
-    const int pair = xcd_pair * 8 + (blockIdx.x & 7);
+    int turn;
+    const int pair = prefill_pair(a, blockIdx.x, turn);
     if (pair >= a.num_pairs) return;
     const int seq = wave_uniform(pair / a.H_k);
     const int g = pair - seq * a.H_k;
@@ -262,25 +201,10 @@ prefill_chunk_kernel(const PrefillArgs a)
     if (C <= 0) return;
     const int tiles_per_head = (C + 15) / 16;
     const int total_tiles = a.G * tiles_per_head;
-    // The pair's workgroups by the length of their streams: whole streams from the last rows down,
-    // and the split ones (about (t_ctx + C) / split tokens each) where that length has its place --
-    // behind all whole ones once the history is longer than that, in front of the first rows of a
-    // fresh prompt.
-    int ahead = a.blocks_per_pair;                     // whole-stream workgroups before the split ones
-    if (num_split > 0 && !a.by_pair) {
-        const int shorter = wave_uniform((int)(((long long)t / a.split - t_ctx) * a.blocks_per_pair / C));
-        ahead -= min(max(shorter, 0), a.blocks_per_pair);
-    }
-    const bool tail_wg = turn >= ahead && turn < ahead + num_split;
-    const int nth = tail_wg ? turn - ahead : (turn < ahead ? turn : turn - num_split);
-    const int parts = tail_wg ? a.split : 1;
-    const int split_block = wave_uniform(nth / parts);
-    const int part = nth - split_block * parts;        // which run of the pair's stages is mine
-    const int block = (tail_wg ? a.split_blocks : a.blocks_per_pair) - 1 - split_block;
-    const int base_tile = tail_wg ? a.tile_limit : a.tile_base;
-    const int end_tile = tail_wg ? total_tiles : min(total_tiles, a.tile_limit);
-    if (base_tile + block * (kPrefillWaves * NR) >= end_tile) return;  // the whole workgroup leaves together
-    const TileOrder order(tiles_per_head, base_tile, end_tile);
+    const PrefillShare share = prefill_share(a, turn, t, C, total_tiles);
+    const int block = share.block, parts = share.parts, part = share.part;
+    if (share.base + block * (kPrefillWaves * NR) >= share.end) return;    // the whole workgroup leaves together
+    const TileOrder order(tiles_per_head, share.base, share.end);
     const int first = block * (kPrefillWaves * NR) + wave_id * NR;     // position of my first tile
     const int count = order.count();
     const bool active = first < count;                 // a wave without tiles still produces
@@ -676,10 +600,10 @@ prefill_chunk_kernel(const PrefillArgs a)
         // column n's sum sits in rows 0 and 1 of lacc: lane (n, 0), registers 0 and 1
         const float L = __shfl(lacc[r][0] + lacc[r][1], n) * 256.0f;
         // (the 2^kPShift common to acc and l cancels; the normaliser of the v_scales is in acc alone)
-        if (tail_wg) {
+        if (share.tail) {
             // this run's share of the tile: reference, row sum and unnormalised sums per column
             if (first + r < count) {
-                const int tile = tile_of[r] - base_tile;
+                const int tile = tile_of[r] - share.base;
                 float* dst = a.part + (((size_t)pair * a.tail_cap + tile) * parts + part) * (16 * (HEAD_DIM + 2));
                 if (grp == 0) {
                     dst[n] = m[r];
@@ -771,78 +695,6 @@ prefill_split_merge_kernel(const PrefillArgs a)
     *reinterpret_cast<half4_t*>(a.out + ((size_t)(qs + row) * a.H_q + g * a.G + hh) * HEAD_DIM + 4 * piece) = h;
 }
 
-// How the tiles of every pair are dealt to launches.  One workgroup (8 waves, 2 tiles each) fills
-// a CU, so a launch runs in rounds of one workgroup per CU, and a last round that is mostly empty
-// costs a full one.  Where that happens the last tiles of every pair go to a second launch: of
-// half-size workgroups (one tile per wave), which takes about 0.65-0.8 of a round -- or, when the
-// caller brings a workspace, of full-size workgroups, `parts` per 16 tiles, that each stream one
-// of `parts` equal runs of the pair's stages, with `parts` (2 to 8) chosen so that the round is as
-// short as it gets (a launch of fewer workgroups than CUs is all "last round": a single
-// sequence's chunk is spread over the chip this way); the parts are combined by
-// prefill_split_merge_kernel.
-struct PrefillLaunchPlan {
-    int tiles, pairs8, a_per_pair, b_per_pair, rest, parts;
-    int nr;          // tiles per wave of the full-size workgroups: 2, or 1 where a pair has at most 8 tiles
-    int wg_tiles;    // = 8 nr
-    PrefillLaunchPlan(const coopt_shape* sh, int max_chunk_len, bool with_workspace)
-    {
-        const int G = sh->num_q_heads / sh->num_kv_heads;
-        tiles = G * ((max_chunk_len + 15) / 16);
-        pairs8 = (sh->num_seqs * sh->num_kv_heads + 7) / 8 * 8;
-        // (a short chunk -- 16 rows of a five-head group, say -- gives every wave one tile at
-        // most: the one-tile kernel then does the same work with fewer registers and 0.78 of the
-        // round time)
-        nr = tiles <= kPrefillWaves ? 1 : 2;
-        wg_tiles = nr * kPrefillWaves;
-        const int full_per_pair = (tiles + wg_tiles - 1) / wg_tiles;
-        a_per_pair = full_per_pair;
-        b_per_pair = 0;
-        rest = 0;
-        parts = 0;
-        auto rounds = [](long long wgs) { return (double)((wgs + kPrefillCUs - 1) / kPrefillCUs); };
-        const long long W = (long long)pairs8 * full_per_pair;
-        const int cand = (int)((W / kPrefillCUs) * kPrefillCUs / pairs8);   // full rounds only
-        if (cand >= full_per_pair) return;                                   // whole rounds
-        const int r = tiles - cand * wg_tiles;                               // tiles of the last round, per pair
-        if (with_workspace) {
-            // p parts make p times the workgroups, each 1/p as long; a part costs about 2 % of a
-            // round on top (its start, its partial rows, its share of the merge)
-            const long long last = (long long)pairs8 * ((r + wg_tiles - 1) / wg_tiles);
-            int best = 1;
-            double best_cost = rounds(last);
-            for (int p = 2; p <= kPrefillMaxParts; ++p) {
-                const double cost = rounds(last * p) / p + 0.02 * (p - 1);
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best = p;
-                }
-            }
-            if (best >= 2) {
-                a_per_pair = cand;
-                rest = r;
-                parts = best;
-                return;
-            }
-        }
-        if (cand >= 1 && nr == 2) {
-            const int small = (r + kPrefillWaves - 1) / kPrefillWaves;
-            const double split = rounds((long long)pairs8 * cand) + 0.65 * rounds((long long)pairs8 * small);
-            if (split < rounds(W)) {
-                a_per_pair = cand;
-                b_per_pair = small;
-                rest = r;
-            }
-        }
-    }
-    // workgroups per pair of the split form of the second launch
-    int split_per_pair() const { return parts * ((rest + wg_tiles - 1) / wg_tiles); }
-    size_t workspace_bytes(const coopt_shape* sh) const
-    {
-        if (parts < 2) return 0;
-        return (size_t)sh->num_seqs * sh->num_kv_heads * rest * parts * 16 * (sh->head_dim + 2) * sizeof(float);
-    }
-};
-
 }  // namespace coopt
 
 using namespace coopt;
@@ -917,13 +769,13 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     a.max_blocks = sh->max_blocks_per_seq;
     a.pool_tiles = sh->num_blocks * sh->num_kv_heads;
     a.scale_log2e = sh->softmax_scale * kLog2e;
-    a.num_pairs = sh->num_seqs * sh->num_kv_heads;
 
     const PrefillLaunchPlan lp(sh, max_chunk_len, workspace != nullptr);
     const int pairs8 = lp.pairs8, a_per_pair = lp.a_per_pair, b_per_pair = lp.b_per_pair;
     const bool split = lp.parts >= 2;
     const int split_per_pair = lp.split_per_pair();
-    a.xcd_pairs = pairs8 / 8;
+    a.set(lp, sh->num_seqs * sh->num_kv_heads);
+    a.part = (float*)workspace;
     // Turn by turn, so that the longest streams of all pairs start first and the launch ends evenly,
     // while the streams of all of an XCD's pairs can share its 4 MB L2; else pair after pair, whose
     // workgroups then read their stream together.  (8 pairs of 2.3 MB an XCD: 760 us a pass by
@@ -942,15 +794,6 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     const bool big = !pool_fits_small(sh);
 #define COOPT_PREFILL_FULL(D, KV, BIG, NR)                                                          \
     do {                                                                                            \
-        a.tile_base = 0;                                                                            \
-        a.tile_limit = (b_per_pair || split) ? a_per_pair * lp.wg_tiles : 0x7fffffff;               \
-        a.blocks_per_pair = a_per_pair;                                                             \
-        if (split) {                                                                                \
-            a.part = (float*)workspace;                                                             \
-            a.split = lp.parts;                                                                     \
-            a.split_blocks = split_per_pair / lp.parts;                                             \
-            a.tail_cap = lp.rest;                                                                   \
-        }                                                                                           \
         hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, NR, BIG>),                                  \
                            dim3((unsigned)((long long)pairs8 * (a_per_pair + split_per_pair))), block, lds, \
                            stream, a);                                                              \
@@ -965,9 +808,7 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
         } else {                                                                                    \
             COOPT_PREFILL_FULL(D, KV, BIG, 2);                                                      \
             if (!split && b_per_pair) {                                                             \
-                a.tile_base = a.tile_limit;                                                         \
-                a.tile_limit = 0x7fffffff;                                                          \
-                a.blocks_per_pair = b_per_pair;                                                     \
+                a.set_rest(lp);                                                                     \
                 hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, 1, BIG>),                           \
                                    dim3((unsigned)((long long)pairs8 * b_per_pair)), block, lds, stream, a); \
             }                                                                                       \

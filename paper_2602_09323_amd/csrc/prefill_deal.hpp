@@ -1,0 +1,211 @@
+// How a prefill launch deals the query tiles of a batch to its workgroups: the host's plan, the order
+// of a pair's tiles, and what the workgroup of a given number takes.  Plain C++ but for wave_uniform (a
+// value that is the same in every lane) and the two function qualifiers, so that a host program which
+// defines those can walk a launch and look at every index that the kernel stores through.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include "coopt_attn.h"
+
+namespace coopt {
+
+constexpr int kPrefillWaves = 8;                // two teams of four producer roles
+constexpr int kPrefillMaxParts = 8;             // runs a split launch cuts a stream into, at most
+constexpr int kPrefillCUs = 256;                // MI355X: the launch shape is planned for its CU count
+
+// How the tiles of every pair are dealt to launches.  One workgroup (8 waves, 2 tiles each) fills
+// a CU, so a launch runs in rounds of one workgroup per CU, and a last round that is mostly empty
+// costs a full one.  Where that happens the last tiles of every pair go to a second launch: of
+// half-size workgroups (one tile per wave), which takes about 0.65-0.8 of a round -- or, when the
+// caller brings a workspace, of full-size workgroups, `parts` per 16 tiles, that each stream one
+// of `parts` equal runs of the pair's stages, with `parts` (2 to 8) chosen so that the round is as
+// short as it gets (a launch of fewer workgroups than CUs is all "last round": a single
+// sequence's chunk is spread over the chip this way); the parts are combined by
+// prefill_split_merge_kernel.
+struct PrefillLaunchPlan {
+    int tiles, pairs8, a_per_pair, b_per_pair, rest, parts;
+    int nr;          // tiles per wave of the full-size workgroups: 2, or 1 where a pair has at most 8 tiles
+    int wg_tiles;    // = 8 nr
+    PrefillLaunchPlan(const coopt_shape* sh, int max_chunk_len, bool with_workspace)
+    {
+        const int G = sh->num_q_heads / sh->num_kv_heads;
+        tiles = G * ((max_chunk_len + 15) / 16);
+        pairs8 = (sh->num_seqs * sh->num_kv_heads + 7) / 8 * 8;
+        // (a short chunk -- 16 rows of a five-head group, say -- gives every wave one tile at
+        // most: the one-tile kernel then does the same work with fewer registers and 0.78 of the
+        // round time)
+        nr = tiles <= kPrefillWaves ? 1 : 2;
+        wg_tiles = nr * kPrefillWaves;
+        const int full_per_pair = (tiles + wg_tiles - 1) / wg_tiles;
+        a_per_pair = full_per_pair;
+        b_per_pair = 0;
+        rest = 0;
+        parts = 0;
+        auto rounds = [](long long wgs) { return (double)((wgs + kPrefillCUs - 1) / kPrefillCUs); };
+        const long long W = (long long)pairs8 * full_per_pair;
+        const int cand = (int)((W / kPrefillCUs) * kPrefillCUs / pairs8);   // full rounds only
+        if (cand >= full_per_pair) return;                                   // whole rounds
+        const int r = tiles - cand * wg_tiles;                               // tiles of the last round, per pair
+        if (with_workspace) {
+            // p parts make p times the workgroups, each 1/p as long; a part costs about 2 % of a
+            // round on top (its start, its partial rows, its share of the merge)
+            const long long last = (long long)pairs8 * ((r + wg_tiles - 1) / wg_tiles);
+            int best = 1;
+            double best_cost = rounds(last);
+            for (int p = 2; p <= kPrefillMaxParts; ++p) {
+                const double cost = rounds(last * p) / p + 0.02 * (p - 1);
+                if (cost < best_cost) {
+                    best_cost = cost;
+                    best = p;
+                }
+            }
+            if (best >= 2) {
+                a_per_pair = cand;
+                rest = r;
+                parts = best;
+                return;
+            }
+        }
+        if (cand >= 1 && nr == 2) {
+            const int small = (r + kPrefillWaves - 1) / kPrefillWaves;
+            const double split = rounds((long long)pairs8 * cand) + 0.65 * rounds((long long)pairs8 * small);
+            if (split < rounds(W)) {
+                a_per_pair = cand;
+                b_per_pair = small;
+                rest = r;
+            }
+        }
+    }
+    // workgroups per pair of the split form of the second launch
+    int split_per_pair() const { return parts * ((rest + wg_tiles - 1) / wg_tiles); }
+    size_t workspace_bytes(const coopt_shape* sh) const
+    {
+        if (parts < 2) return 0;
+        return (size_t)sh->num_seqs * sh->num_kv_heads * rest * parts * 16 * (sh->head_dim + 2) * sizeof(float);
+    }
+};
+
+// What the kernel is told about the deal.
+struct PrefillDeal {
+    int32_t num_pairs;        // num_seqs * H_k
+    int32_t xcd_pairs;        // pairs per XCD: num_pairs rounded up to a multiple of 8, over 8
+    int32_t by_pair;          // order of an XCD's workgroups (prefill_pair)
+    int32_t blocks_per_pair;  // workgroups per pair over tiles [tile_base, tile_limit): whole streams
+    int32_t tile_base;
+    int32_t tile_limit;
+    // split workgroups, behind the whole-stream ones in the grid (the tiles from tile_limit on of
+    // every pair, `split` workgroups per 16 tiles: workgroup p of them streams the p-th of `split`
+    // equal runs of the pair's stages and leaves per tile 16 x (m, l) and the 16 x HEAD_DIM
+    // unnormalised sums in the workspace, which a merge launch combines)
+    int32_t split;            // parts, >= 2 (0: no such workgroups)
+    int32_t split_blocks;     // runs of 16 tiles per pair they cover
+    int32_t tail_cap;         // tiles per pair they cover (sizes the workspace)
+
+    // The first launch of a plan (its only one but for a plan's half-size workgroups).
+    void set(const PrefillLaunchPlan& lp, int pairs)
+    {
+        num_pairs = pairs;
+        xcd_pairs = lp.pairs8 / 8;
+        blocks_per_pair = lp.a_per_pair;
+        tile_base = 0;
+        tile_limit = lp.rest > 0 ? lp.a_per_pair * lp.wg_tiles : 0x7fffffff;
+        split = lp.parts;
+        split_blocks = lp.parts > 0 ? lp.split_per_pair() / lp.parts : 0;
+        tail_cap = lp.parts > 0 ? lp.rest : 0;
+    }
+    // ... and the one of half-size workgroups behind it: the tiles that it left.
+    void set_rest(const PrefillLaunchPlan& lp)
+    {
+        tile_base = tile_limit;
+        tile_limit = 0x7fffffff;
+        blocks_per_pair = lp.b_per_pair;
+    }
+};
+
+// The pair of workgroup `wg`, and `turn`: which of the pair's workgroups it is, longest stream first.
+// All workgroups of a pair sit on one XCD (ids go round-robin over 8 XCDs).  By pair: an XCD's
+// whole-stream workgroups pair after pair, then its split ones; otherwise turn after turn of all its
+// pairs.  A pair >= num_pairs is none.
+__device__ __forceinline__ int prefill_pair(const PrefillDeal& a, unsigned wg, int& turn)
+{
+    const int k8 = wg >> 3;
+    const int whole = a.xcd_pairs * a.blocks_per_pair;           // whole-stream workgroups per XCD
+    const int num_split = a.split * a.split_blocks;              // split ones per pair
+    int xcd_pair;
+    if (a.by_pair) {
+        const int k = k8 < whole ? k8 : k8 - whole;
+        const int per = k8 < whole ? a.blocks_per_pair : num_split;
+        xcd_pair = wave_uniform(k / per);
+        turn = k - xcd_pair * per + (k8 < whole ? 0 : a.blocks_per_pair);
+    } else {
+        turn = wave_uniform(k8 / a.xcd_pairs);
+        xcd_pair = k8 - turn * a.xcd_pairs;
+    }
+    return xcd_pair * 8 + (wg & 7);
+}
+
+// A workgroup's tiles: positions block * WG .. of the range [base, end) in TileOrder, as one of `parts`
+// runs of their stream.
+struct PrefillShare {
+    bool tail;
+    int block, base, end, parts, part;
+};
+
+// The pair's workgroups by the length of their streams: whole streams from the last rows down, and the
+// split ones (about t / split tokens each) where that length has its place -- behind all whole ones once
+// the history is longer than that, in front of the first rows of a fresh prompt.  t: the sequence's
+// tokens, C of them new rows, total_tiles tiles.  C comes from the device and may be more than the
+// host was told: tiles beyond those that the launch and its workspace were sized for are left out.
+__device__ __forceinline__ PrefillShare prefill_share(const PrefillDeal& a, int turn, int t, int C, int total_tiles)
+{
+    const int num_split = a.split * a.split_blocks;
+    int ahead = a.blocks_per_pair;                     // whole-stream workgroups before the split ones
+    if (num_split > 0 && !a.by_pair) {
+        const int shorter = wave_uniform((int)(((long long)t / a.split - (t - C)) * a.blocks_per_pair / C));
+        ahead -= min(max(shorter, 0), a.blocks_per_pair);
+    }
+    PrefillShare s;
+    s.tail = turn >= ahead && turn < ahead + num_split;
+    const int nth = s.tail ? turn - ahead : (turn < ahead ? turn : turn - num_split);
+    s.parts = s.tail ? a.split : 1;
+    const int split_block = wave_uniform(nth / s.parts);
+    s.part = nth - split_block * s.parts;              // which run of the pair's stages is mine
+    s.block = (s.tail ? a.split_blocks : a.blocks_per_pair) - 1 - split_block;
+    s.base = s.tail ? a.tile_limit : a.tile_base;
+    s.end = min(total_tiles, s.tail ? a.tile_limit + a.tail_cap : a.tile_limit);
+    return s;
+}
+
+// The tiles [base, end) of a pair -- tile h T + i is rows 16i .. of head h, T tiles a head -- in the
+// order in which workgroups take them: by row, then by head.  A causal stream is as long as its
+// last row needs, so the 16 tiles of a workgroup should lie at neighbouring rows: by head, a
+// workgroup of 256 rows streams up to 240 tokens too far for most of them.
+struct TileOrder {
+    int T, base, end, hb, ib, he, ie;
+    __device__ __forceinline__ TileOrder(int tiles_per_head, int b, int e) : T(tiles_per_head), base(b), end(e)
+    {
+        // (wave_uniform: the quotients are made on the vector ALU; this keeps them out of its registers)
+        hb = wave_uniform(b / T);
+        ib = b - hb * T;
+        he = wave_uniform(e / T);
+        ie = e - he * T;
+    }
+    __device__ __forceinline__ int count() const { return end - base; }
+    // Position p (0 .. count-1) -> first row / 16 and head.  Row i has he - hb tiles of this range,
+    // one more from ib .. or up to ie (whichever of the two partial heads reaches it).
+    __device__ __forceinline__ void at(int p, int& i, int& h) const
+    {
+        const int N = he - hb, b1 = min(ib, ie), b2 = max(ib, ie);
+        const int c2 = ie > ib ? N + 1 : N - 1;                  // tiles per row between b1 and b2
+        const int n1 = b1 * N, n2 = n1 + (b2 - b1) * c2;
+        if (p < n1) i = p / N;
+        else if (p < n2) i = b1 + (p - n1) / c2;
+        else i = b2 + (p - n2) / max(N, 1);
+        i = wave_uniform(i);
+        h = p - (i * N + min(i, ie) - min(i, ib)) + hb + (i < ib ? 1 : 0);
+    }
+};
+
+}  // namespace coopt

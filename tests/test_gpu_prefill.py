@@ -173,6 +173,31 @@ def test_infinite_value_rows(oracle_mod, S, H_q, H_k, d, hist, C, parts):
         assert_close(got[..., rest], ref[..., rest], f"infinite values, workspace: {with_workspace}")
 
 
+def test_longer_chunk_than_announced(oracle_mod):
+    """A sequence with more rows than `max_chunk_len` says: nothing is written beyond the workspace that
+    was asked for, and the other sequence's rows are what they are without it."""
+    chunks, announced = [64, 400], 64
+    w = workloads.make_custom("over", seed=59, S=2, H_q=40, H_k=8, d=128, B=16, NB=64,
+                              context_lens=[264, 600], kv_dtype="e4m3")
+    query_start = np.array([0, 64, 464], dtype=np.int32)
+    q = np.random.default_rng(60).standard_normal((464, 40, 128), dtype=np.float32).astype(np.float16)
+    cache = oracle_fill(oracle_mod, w)
+    ref = oracle_mod.paged_gqa_prefill_chunk(q, *cache, w.block_tables, w.context_lens, query_start, H_q=40, H_k=8,
+                                             d=128, B=16, softmax_scale=w.softmax_scale)
+    shape, out = shape_of(w), torch.full((464, 40, 128), -7.0, dtype=torch.float16, device="cuda")
+    need = coopt.prefill_workspace_bytes(shape, announced)
+    whole = coopt.prefill_workspace_bytes(shape, max(chunks))
+    buf = torch.full((need + 4 * whole,), 0x5A, dtype=torch.uint8, device="cuda")      # the workspace, and what lies behind
+    coopt.paged_gqa_prefill_chunk_ws(dev(q.view(np.uint16)), *cache_to_dev(cache), dev(w.block_tables),
+                                     dev(w.context_lens), dev(query_start), 464, announced, out, buf[:need], shape)
+    torch.cuda.synchronize()
+    assert need > 0 and bool((buf[need:] == 0x5A).all())
+    got = out.cpu().numpy().astype(np.float64)
+    assert_close(got[:64], ref[:64], "the sequence as announced")
+    written = (got[64:] != -7.0).any(axis=2)
+    assert_close(got[64:][written], ref[64:][written], "what is written of the longer one")
+
+
 def test_chunked_prefill_full_size(oracle_mod, record_property):
     """Full configuration in the launch shape the benchmark times.  The oracle computes every row
     of one whole sequence (512 rows x 40 heads over 8192 + 512 tokens: the stage pipeline 136
