@@ -600,7 +600,7 @@ prefill_chunk_kernel(const PrefillArgs a)
         // column n's sum sits in rows 0 and 1 of lacc: lane (n, 0), registers 0 and 1
         const float L = __shfl(lacc[r][0] + lacc[r][1], n) * 256.0f;
         // (the 2^kPShift common to acc and l cancels; the normaliser of the v_scales is in acc alone)
-        if (share.tail) {
+        if (parts > 1) {
             // this run's share of the tile: reference, row sum and unnormalised sums per column
             if (first + r < count) {
                 const int tile = tile_of[r] - share.base;

@@ -48,25 +48,23 @@ struct PrefillLaunchPlan {
         const int cand = (int)((W / kPrefillCUs) * kPrefillCUs / pairs8);   // full rounds only
         if (cand >= full_per_pair) return;                                   // whole rounds
         const int r = tiles - cand * wg_tiles;                               // tiles of the last round, per pair
-        if (with_workspace) {
-            // p parts make p times the workgroups, each 1/p as long; a part costs about 2 % of a
-            // round on top (its start, its partial rows, its share of the merge)
-            const long long last = (long long)pairs8 * ((r + wg_tiles - 1) / wg_tiles);
-            int best = 1;
-            double best_cost = rounds(last);
-            for (int p = 2; p <= kPrefillMaxParts; ++p) {
-                const double cost = rounds(last * p) / p + 0.02 * (p - 1);
-                if (cost < best_cost) {
-                    best_cost = cost;
-                    best = p;
-                }
+        // p parts make p times the workgroups, each 1/p as long; a part costs about 2 % of a
+        // round on top (its start, its partial rows, its share of the merge)
+        const long long last = (long long)pairs8 * ((r + wg_tiles - 1) / wg_tiles);
+        int best = 1;
+        double best_cost = rounds(last);
+        for (int p = 2; p <= kPrefillMaxParts; ++p) {
+            const double cost = rounds(last * p) / p + 0.02 * (p - 1);
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = p;
             }
-            if (best >= 2) {
-                a_per_pair = cand;
-                rest = r;
-                parts = best;
-                return;
-            }
+        }
+        if (best >= 2 && with_workspace) {
+            a_per_pair = cand;
+            rest = r;
+            parts = best;
+            return;
         }
         if (cand >= 1 && nr == 2) {
             const int small = (r + kPrefillWaves - 1) / kPrefillWaves;
@@ -75,10 +73,19 @@ struct PrefillLaunchPlan {
                 a_per_pair = cand;
                 b_per_pair = small;
                 rest = r;
+                return;
             }
         }
+        // What a workspace would split runs whole, but behind the same cut: which rows share a
+        // workgroup decides the normaliser of their v_scales, and the tiles in front of the cut are
+        // to have the same bits with and without a workspace.
+        if (best >= 2) {
+            a_per_pair = cand;
+            rest = r;
+            parts = 1;
+        }
     }
-    // workgroups per pair of the split form of the second launch
+    // workgroups per pair over the tiles behind the cut
     int split_per_pair() const { return parts * ((rest + wg_tiles - 1) / wg_tiles); }
     size_t workspace_bytes(const coopt_shape* sh) const
     {
@@ -99,7 +106,7 @@ struct PrefillDeal {
     // every pair, `split` workgroups per 16 tiles: workgroup p of them streams the p-th of `split`
     // equal runs of the pair's stages and leaves per tile 16 x (m, l) and the 16 x HEAD_DIM
     // unnormalised sums in the workspace, which a merge launch combines)
-    int32_t split;            // parts, >= 2 (0: no such workgroups)
+    int32_t split;            // parts (0: no such workgroups; 1: whole streams, rows written to out)
     int32_t split_blocks;     // runs of 16 tiles per pair they cover
     int32_t tail_cap;         // tiles per pair they cover (sizes the workspace)
 

@@ -198,6 +198,30 @@ def test_longer_chunk_than_announced(oracle_mod):
     assert_close(got[64:][written], ref[64:][written], "what is written of the longer one")
 
 
+@pytest.mark.parametrize("kv_dtype", ["e4m3", "e5m2"])
+@pytest.mark.parametrize("S,C,limit,rest,parts", [(8, 352, 64, 46, 4), (3, 777, 160, 85, 5)])
+def test_tiles_that_are_not_split_are_the_same_bits(S, C, limit, rest, parts, kv_dtype):
+    """Fresh prompts for which the entry point without a workspace makes one launch of full workgroups
+    and the one with a workspace splits the tiles from `limit` on.  The value rows grow along the prompt,
+    so the normaliser of the v_scales -- taken over the rows of a workgroup -- tells which rows a tile
+    was grouped with: tiles below `limit` have the same bits from both."""
+    H_q, H_k, d = 40, 8, 128
+    w = workloads.make_custom("bits", seed=61, S=S, H_q=H_q, H_k=H_k, d=d, B=16, NB=S * (C // 16 + 2),
+                              context_lens=[C] * S, new_per_seq=C, kv_dtype=kv_dtype)
+    grow = np.exp2((np.arange(len(w.slots)) % C) / 64.0).astype(np.float16)
+    w.v_ctx = (w.v_ctx * grow[:, None, None]).astype(np.float16)
+    dcache = alloc_dev_cache(w)
+    hip_write(w, dcache)
+    assert coopt.prefill_workspace_bytes(shape_of(w), C) == S * H_k * rest * parts * 16 * 130 * 4
+    plain, split = (_hip_prefill(w, dcache, with_workspace=ws) for ws in (False, True))
+    tiles_per_head = (C + 15) // 16
+    tile = np.arange(H_q)[None, :] % (H_q // H_k) * tiles_per_head + (np.arange(S * C)[:, None] % C) // 16
+    same = (plain == split).all(axis=2)                         # [row, head]
+    assert same[tile < limit].all(), f"{int((~same[tile < limit]).sum())} rows differ"
+    # (the others: two roundings to fp16, 2^-11 of the value each, and 2^-10 of the arithmetic's)
+    assert np.abs(plain - split).max() <= 2e-3 * np.abs(plain).max()
+
+
 def test_chunked_prefill_full_size(oracle_mod, record_property):
     """Full configuration in the launch shape the benchmark times.  The oracle computes every row
     of one whole sequence (512 rows x 40 heads over 8192 + 512 tokens: the stage pipeline 136

@@ -1,6 +1,7 @@
 """The deal of a prefill launch (csrc/prefill_deal.hpp, compiled here for the CPU): every workgroup of
 every launch is walked with the kernel's own mapping.  Every tile of every pair is taken exactly once, or
-once per part; where a sequence is longer than the `max_chunk_len` the host was told, nothing is stored
+once per part; a tile that the entry point with a workspace does not split is taken whole by a
+workgroup of the same rows with and without one, so that its bits are the same; where a sequence is longer than the `max_chunk_len` the host was told, nothing is stored
 beyond the workspace that the host asked for, nor into another pair's share of it."""
 import subprocess
 from pathlib import Path
@@ -30,7 +31,7 @@ typedef std::vector<std::vector<int>> Tiles;      // [pair][tile]
 
 struct Walk {
     Tiles taken, of_part;          // times a tile was taken whole; times its parts were
-    Tiles group;                   // the last row of the workgroup that took it whole, -1 else
+    Tiles group;                   // last row / 16 of the workgroup that took it whole, -1 else
     int parts, limit, cap;
     std::vector<int> slots;        // times a part's slot of the workspace was written
 };
@@ -128,11 +129,14 @@ int main(int argc, char** argv)
                             C.push_back(c);
                             t.push_back(c + history * (s % 2 + 1));
                         }
+                        // mode 0 comes first: what the entry point without a workspace does
+                        Walk plain;
                         for (int mode = 0; mode < 4; ++mode) {
                             const bool ws = mode & 1, by_pair = mode & 2;
                             sprintf(what, "%d/%d heads, %d x %d rows, ragged %d, history %d, workspace %d, by pair %d",
                                     hh[0], hh[1], S, announced, ragged, history, ws, by_pair);
                             const Walk w = walk(hh[0], hh[1], announced, ws, by_pair, C, t);
+                            if (mode == 0) plain = w;
                             ++calls;
                             split += w.parts > 1;
                             for (int n : w.slots) CHECK(n <= 1);
@@ -144,6 +148,8 @@ int main(int argc, char** argv)
                                     if (tail) CHECK(whole == 0 && parts == ((int)i < w.limit + w.cap ? w.parts : 0));
                                     else if (C[p / hh[1]] <= announced) CHECK(whole == 1 && parts == 0);
                                     else CHECK(whole <= 1 && parts == 0);
+                                    // vnorm, and with it the rounding of a tile, is its workgroup's
+                                    if (!tail && whole) CHECK(w.group[p][i] == plain.group[p][i]);
                                 }
                         }
                     }
