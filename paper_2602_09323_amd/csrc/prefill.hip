@@ -681,12 +681,12 @@ prefill_split_merge_kernel(const PrefillArgs a)
     floatx4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < kPrefillMaxParts; ++p) {
-        // (left out, not weighted by zero: a sum may be infinite, and infinity * 0 is no number)
-        if (p < parts) {
-            const float e = __builtin_amdgcn_exp2f(m[p] - M);
-            den += l[p] * e;
-            o += x[p] * e;
-        }
+        // (left out, not weighted by zero: a sum may be infinite, and infinity * 0 is no number.  By
+        // selects: the compiler moves loads into a branch, behind the others' arrival)
+        const float e = __builtin_amdgcn_exp2f(m[p] - M);
+        den += p < parts ? l[p] * e : 0.0f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[c] += p < parts ? x[p][c] * e : 0.0f;
     }
     const float inv = 1.0f / den;
     half4_t h;
