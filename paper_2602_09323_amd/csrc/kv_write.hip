@@ -210,10 +210,8 @@ kv_write_bulk_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict_
     __shared__ int64_t slots[W::kRows + 6];     // of rows -3 .. kRows+2 (-1: no token, or filtered)
 
     const int tid = threadIdx.x;
-    const int wg = (int)grid_index(blockIdx.x, blockIdx.y);
-    const int window = wg / H_k, head = wg - window * H_k;
+    const int window = blockIdx.x / H_k, head = blockIdx.x - window * H_k;
     const int base = window * W::kOwn;
-    if (base >= num_tokens) return;             // a surplus workgroup
     // a wavefront's lanes cover 8 rows or more: a K chunk of 8 consecutive tokens is a whole line
     const int wave = tid >> 6;
     const int c = tid % CW + CW * (wave % (CH / CW));
@@ -364,11 +362,17 @@ static void launch_write_bulk(const void* k, const void* v, const int64_t* slot_
                               const uint32_t* skip_set, int32_t num_tokens, int H_k, uint8_t* k_cache,
                               uint8_t* v_cache, float* k_scale, float* v_scale, hipStream_t stream)
 {
-    // one workgroup per window and head
-    const Grid grid = grid_of((long long)((num_tokens - 1) / BulkWindow<HEAD_DIM, KV>::kOwn + 1) * H_k);
-    hipLaunchKernelGGL((kv_write_bulk_kernel<HEAD_DIM, KV>), dim3(grid.x, grid.y), dim3(256), 0, stream,
-                       (const uint16_t*)k, (const uint16_t*)v, slot_mapping, skip_set, num_tokens, H_k,
-                       k_cache, v_cache, k_scale, v_scale);
+    constexpr int kOwn = BulkWindow<HEAD_DIM, KV>::kOwn;
+    const long long step = tokens_per_launch(num_tokens, kOwn, H_k);
+    for (long long first = 0; first < num_tokens; first += step) {
+        const int n = (int)(step < num_tokens - first ? step : num_tokens - first);
+        const size_t at = (size_t)first * H_k * HEAD_DIM;
+        // one workgroup per window and head
+        hipLaunchKernelGGL((kv_write_bulk_kernel<HEAD_DIM, KV>), dim3((unsigned)((n - 1) / kOwn + 1) * H_k),
+                           dim3(256), 0, stream, (const uint16_t*)k + at, (const uint16_t*)v + at,
+                           slot_mapping + first, skip_set ? skip_set + first / 32 : nullptr, n, H_k, k_cache,
+                           v_cache, k_scale, v_scale);
+    }
 }
 
 template <int HEAD_DIM, int KV>

@@ -1,23 +1,23 @@
-// The grid of a kernel that numbers its workgroups of 256 in one run.  A grid dimension holds fewer
-// than 2^32 work-items, 2^24 such workgroups; a call of more takes several rows of 2^23, and the
-// surplus workgroups of the last row leave at once.  (Plain C++: a host program can include it.)
+// Launches of more workgroups than a grid holds.  A grid dimension holds fewer than 2^32 work-items,
+// 2^24 workgroups of 256: a call that needs more is launched in slices (of its tokens, of its
+// sequences), which costs the kernels nothing.  (Plain C++: a host program can include it.)
 #pragma once
 
 namespace coopt {
 
-constexpr unsigned kGridRow = 1u << 23;
+constexpr long long kMaxWorkgroups = 1LL << 23;
 
-struct Grid {
-    unsigned x, y;
-};
-
-constexpr Grid grid_of(long long workgroups)
+// Tokens per launch where every `own` of them take `heads` workgroups: a multiple of 32 (a skip set's
+// word), the whole call where it fits.
+constexpr long long tokens_per_launch(long long tokens, int own, int heads)
 {
-    return workgroups <= kGridRow ? Grid{(unsigned)workgroups, 1u}
-                                  : Grid{kGridRow, (unsigned)((workgroups + kGridRow - 1) / kGridRow)};
+    return ((tokens - 1) / own + 1) * heads <= kMaxWorkgroups ? tokens : kMaxWorkgroups / heads * own / 32 * 32;
 }
 
-// A workgroup's number from its place in that grid.
-constexpr long long grid_index(unsigned x, unsigned y) { return x + (long long)kGridRow * y; }
+// Sequences per launch where each takes `workgroups`.
+constexpr long long seqs_per_launch(long long seqs, long long workgroups)
+{
+    return seqs * workgroups <= kMaxWorkgroups ? seqs : (workgroups < kMaxWorkgroups ? kMaxWorkgroups / workgroups : 1);
+}
 
 }  // namespace coopt
