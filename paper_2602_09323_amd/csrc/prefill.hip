@@ -35,6 +35,7 @@
 // 8 heads, d = 128): 156 us a pass with tiles by head, first rows first and the split streams in a
 // launch behind the whole ones, 100 us so; 8 x 512 rows over 8192 tokens 763 -> 744 us.
 #include "attn_tile.hpp"
+#include "launch_grid.hpp"
 #include "prefill_deal.hpp"
 
 namespace coopt {
@@ -743,6 +744,22 @@ extern "C" int coopt_paged_gqa_prefill_chunk_ws(const void* q, const void* k_cac
                          num_query_rows, max_chunk_len, out, workspace, sh, hip_stream);
 }
 
+// The merge of the tiles behind the cut, of all sequences in one launch where a grid holds them.
+template <int HEAD_DIM>
+static void launch_split_merge(PrefillArgs a, int num_seqs, hipStream_t stream)
+{
+    // 256 / (d/4) rows per workgroup: two workgroups per tile at d = 128, one at 64
+    const long long seq_wgs = (long long)a.H_k * a.tail_cap * (HEAD_DIM / 64);
+    const long long step = seqs_per_launch(num_seqs, seq_wgs);
+    for (long long left = num_seqs; left > 0; left -= step) {
+        const long long n = step < left ? step : left;
+        hipLaunchKernelGGL((prefill_split_merge_kernel<HEAD_DIM>), dim3((unsigned)(n * seq_wgs)), dim3(256), 0,
+                           stream, a);
+        a.query_start += n;
+        a.part += (size_t)n * a.H_k * a.tail_cap * a.split * (16 * (HEAD_DIM + 2));
+    }
+}
+
 static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache, const float* k_scale,
                          const float* v_scale, const int32_t* block_tables, const int32_t* context_lens,
                          const int32_t* query_start, int32_t num_query_rows, int32_t max_chunk_len,
@@ -784,9 +801,6 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
                                   (sh->kv_dtype == COOPT_KV_FP16 ? 0 : 8);
     a.by_pair = a.xcd_pairs * (long long)sh->max_blocks_per_seq * kBlock * token_bytes > kPrefillXcdL2;
     if ((long long)pairs8 * (a_per_pair + b_per_pair + split_per_pair) > 0x7fffffffLL) return COOPT_ERR_SHAPE;
-    // 256 / (d/4) rows per workgroup of the merge: two workgroups per tile at d = 128, one at 64
-    const long long merge_wgs = (long long)a.num_pairs * lp.rest * (sh->head_dim == 128 ? 2 : 1);
-    if (split && merge_wgs > 0x7fffffffLL) return COOPT_ERR_SHAPE;
     const dim3 block(64 * kPrefillWaves);
     const size_t lds = 2 * kPrefillGroupsPerStage *
                        (size_t)(sh->head_dim == 128 ? PrefillStage<128>::kBytes : PrefillStage<64>::kBytes);
@@ -798,8 +812,7 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
                            dim3((unsigned)((long long)pairs8 * (a_per_pair + split_per_pair))), block, lds, \
                            stream, a);                                                              \
         if (split)                                                                                  \
-            hipLaunchKernelGGL((prefill_split_merge_kernel<D>), dim3((unsigned)merge_wgs), dim3(256), \
-                               0, stream, a);                                                       \
+            launch_split_merge<D>(a, sh->num_seqs, stream);                                         \
     } while (0)
 #define COOPT_PREFILL(D, KV, BIG)                                                                   \
     do {                                                                                            \
