@@ -870,7 +870,10 @@ flat_prepare_kernel(const FlatArgs a)
 // lane, HEAD_DIM/4 lanes per partial row, hence 2 (d = 128) or 4 (d = 64) partials.  The first 8 of a
 // wavefront are asked for before the count is known (they lie inside the workspace whatever the count
 // is), so the kernel is one memory round trip deep for rows of that many.
-//   WIDE = false: one wavefront per row, four rows per workgroup; further partials 32 per round trip.
+//   WIDE = false: one wavefront per row, four rows per workgroup; 8 further partials in a second round
+//   trip, or 32 in each where there are more (a second of 32 for the one or two that batches of 1000 to
+//   3000 tokens a sequence have beyond the first 8 costs 0.3-0.7 us of loads: 16 sequences of up to 1500
+//   tokens, 40 over 8 heads, E4M3: 14.8 us, 14.1 so).
 //   WIDE = true (long contexts and few rows): one workgroup per row; the wavefronts take the wave-wide
 //   loads in turn -- 32 partials in the first round trip -- and the four sums meet in LDS.
 // Fused step: the merge launch begins with one wavefront per (sequence, KV head) pair (four to a
@@ -1013,28 +1016,34 @@ flat_merge_kernel(const FlatArgs a)
 #pragma unroll
             for (int c = 0; c < 4; ++c) o[c] += p0 + sub < end ? x[c] * wj : 0.0f;
         };
-        // loads i0 .. i0+kBatch-1 of the window that begins at b0, all in flight together (long
-        // contexts have tens of partials per row: one dependent load per partial would cost a round
-        // trip each)
-        auto add_batch = [&](float w, int b0, int i0, int end) {
-            floatx4 x[kBatch];
+        // loads i0 .. i0+N-1 of the window that begins at b0, all in flight together (long contexts
+        // have tens of partials per row: one dependent load per partial would cost a round trip each)
+        auto add_batch = [&](auto loads, float w, int b0, int i0, int end) {
+            constexpr int N = decltype(loads)::value;
+            floatx4 x[N];
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i)
+            for (int i = 0; i < N; ++i)
                 x[i] = *reinterpret_cast<const floatx4*>(
                     po + (size_t)min(b0 + partial_of(i0 + i), end - 1) * HEAD_DIM);
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) add(x[i], w, b0, b0 + first_of(i0 + i), end);
+            for (int i = 0; i < N; ++i) add(x[i], w, b0, b0 + first_of(i0 + i), end);
         };
+        constexpr std::integral_constant<int, kSpec> few{};
+        constexpr std::integral_constant<int, kBatch> many{};
         const int end0 = min(count, 64);
 #pragma unroll
         for (int i = 0; i < kSpec; ++i) add(x_spec[i], wv, 0, first_of(i), end0);
-        for (int i0 = kSpec; first_of(i0) < end0; i0 += kBatch) add_batch(wv, 0, i0, end0);
+        if (!WIDE && end0 <= first_of(2 * kSpec)) {
+            if (first_of(kSpec) < end0) add_batch(few, wv, 0, kSpec, end0);
+        } else {
+            for (int i0 = kSpec; first_of(i0) < end0; i0 += kBatch) add_batch(many, wv, 0, i0, end0);
+        }
         for (int b0 = 64; b0 < count; b0 += 64) {                          // very long contexts
             const int p = b0 + lane;
             const float w2 = p < count ? es[p] * __expf(ml[p] - M) : 0.0f;
             W += w2;
             const int end = min(b0 + 64, count);
-            for (int i0 = 0; b0 + first_of(i0) < end; i0 += kBatch) add_batch(w2, b0, i0, end);
+            for (int i0 = 0; b0 + first_of(i0) < end; i0 += kBatch) add_batch(many, w2, b0, i0, end);
         }
         W = wave_sum(W);
 #pragma unroll
