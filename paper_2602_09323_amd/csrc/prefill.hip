@@ -499,8 +499,9 @@ prefill_chunk_kernel(const PrefillArgs a)
     // numerator alone and is taken out, exactly, in the final division.  One pass over the pair's
     // scales (64 bytes per block) before the first stage is stored; its two dependent round trips
     // (block numbers, scales) run beside the first stage's own two (block numbers, tiles), and a
-    // later batch's block numbers beside the scales of the one before.
-    constexpr bool kIssueEarly = FP8 && !BIG && KV != COOPT_KV_E5M2;
+    // later batch's block numbers beside the scales of the one before.  (One kernel, d = 128 with two
+    // tiles per wave over an E5M2 pool of 64-bit addresses, has no registers for both: 12 spills.)
+    constexpr bool kIssueEarly = FP8 && !(HEAD_DIM == 128 && NR == 2 && BIG && KV == COOPT_KV_E5M2);
     if constexpr (kIssueEarly) ids = load_ids(s_lo);
     if constexpr (FP8) {
         __shared__ float vmax_of_wave[kPrefillWaves];
