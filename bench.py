@@ -36,10 +36,10 @@ MFMA_F16_PEAK_TFLOPS = 2500.0
 PMC_TRAFFIC = {
     # (workload, launch mode) -> counters of the kernel that `roofline` times, and the hash of the
     # kernel sources they were measured on (kernel_sources_sha16): quoted only while that matches
-    ("llama13b_gqa_fp8_decode", "fused"): {"fetch_kib": 36678.9, "fetch_scale": 2.0, "write_kib": 3152.1,
-                                           "write_scale": 1.0, "sources_sha16": "f67412d6569893ab"},
-    ("llama13b_gqa_fp8_decode", "plain"): {"fetch_kib": 36582.8, "fetch_scale": 2.0, "write_kib": 3152.1,
-                                           "write_scale": 1.0, "sources_sha16": "f67412d6569893ab"},
+    ("llama13b_gqa_fp8_decode", "fused"): {"fetch_kib": 36678.6, "fetch_scale": 2.0, "write_kib": 3152.1,
+                                           "write_scale": 1.0, "sources_sha16": "b10ef7119b3961ab"},
+    ("llama13b_gqa_fp8_decode", "plain"): {"fetch_kib": 36536.5, "fetch_scale": 2.0, "write_kib": 3152.1,
+                                           "write_scale": 1.0, "sources_sha16": "b10ef7119b3961ab"},
 }
 
 
@@ -703,8 +703,8 @@ def bench_prefill(args, w, coopt, torch, dev, steps, warmup, cpu):
                    "launch": "eager"},
         "wall_ms_timed_region": round(wall_ms, 2),
         "roofline": {"bound": "mfma",
-                     "kernel": ("prefill_chunk_kernel (coopt_paged_gqa_prefill_chunk_ws: full workgroups, then the "
-                                "last tiles as half-streams in full workgroups, and the merge of the halves)")
+                     "kernel": ("prefill_chunk_kernel (coopt_paged_gqa_prefill_chunk_ws: whole streams and the last "
+                                "tiles' half-streams in one launch, and the merge of the halves)")
                      if with_ws else
                      "prefill_chunk_kernel (coopt_paged_gqa_prefill_chunk: its two launches, full and half-size workgroups)",
                      "achieved": round(flops / kern_ms / 1e9, 1), "peak": MFMA_F16_PEAK_TFLOPS,

@@ -394,7 +394,8 @@ int coopt_paged_gqa_prefill_chunk(const void* q, const void* k_cache, const void
  *                    is coopt_paged_gqa_prefill_chunk); contents on entry are ignored, on return
  *                    they are scratch.  The caller owns it; calls that share it must not overlap.
  *   workspace_bytes  its size; COOPT_ERR_WORKSPACE if too small, COOPT_ERR_NULL if needed and NULL
- * Allocates nothing, synchronises nothing; three launches at most.
+ * Allocates nothing, synchronises nothing; two launches at most (a batch whose merge a grid does
+ * not hold, 67 million rows of all heads, takes several merge launches).
  */
 size_t coopt_prefill_workspace_bytes(const coopt_shape* shape, int32_t max_chunk_len);
 int coopt_paged_gqa_prefill_chunk_ws(const void* q, const void* k_cache, const void* v_cache,

@@ -21,17 +21,17 @@
 //     pair on ONE XCD: the pair's 2 MB of cache are fetched from HBM once and re-read from that
 //     XCD's L2 by the pair's other workgroups.
 //   * A launch runs in rounds of one workgroup per CU.  The tiles of a last round that would be
-//     mostly empty go to a second launch: of half-size workgroups, or -- when the caller brings a
-//     workspace -- of full-size workgroups, 2 to 8 per 16 tiles, that each stream one of as many
-//     equal runs of the pair's stages and leave (m, l, unnormalised sums) per tile, which a merge
-//     launch combines (Opt-Pa Eq. 10 over the parts).
+//     mostly empty go to a launch of half-size workgroups behind it, or -- when the caller brings a
+//     workspace -- to full-size workgroups of the same launch, 2 to 8 per 16 tiles, that each stream
+//     one of as many equal runs of the pair's stages and leave (m, l, unnormalised sums) per tile,
+//     which a merge launch combines (Opt-Pa Eq. 10 over the parts).
 // The only difference from decode in the arithmetic is that the visible-token limit is per column
 // (causal).
 //
 // The launch's order.  A causal stream is as long as its last row needs and one workgroup holds a
 // CU, so how long a launch takes is decided by which rows a workgroup takes and in which order the
 // workgroups start: tiles by row, the longest streams first, whole and split streams in one launch
-// (TileOrder and the start of the kernel).  Three fresh prompts of 301, 1039 and 1777 rows (40 over
+// (prefill_deal.hpp).  Three fresh prompts of 301, 1039 and 1777 rows (40 over
 // 8 heads, d = 128): 156 us a pass with tiles by head, first rows first and the split streams in a
 // launch behind the whole ones, 100 us so; 8 x 512 rows over 8192 tokens 763 -> 744 us.
 #include "attn_tile.hpp"
@@ -797,7 +797,9 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     // Turn by turn, so that the longest streams of all pairs start first and the launch ends evenly,
     // while the streams of all of an XCD's pairs can share its 4 MB L2; else pair after pair, whose
     // workgroups then read their stream together.  (8 pairs of 2.3 MB an XCD: 760 us a pass by
-    // pair, 770 turn by turn.  The table's width bounds what the host does not see, the lengths.)
+    // pair, 770 turn by turn.)  The host does not see the lengths, only what bounds them, the table's
+    // width: three fresh prompts of up to 1777 rows take 94 us with a table as wide as the longest
+    // and 102 with one of 2048 columns, 3 x 3.5 MB an XCD (159 by head, first rows first).
     const long long token_bytes = (sh->kv_dtype == COOPT_KV_FP16 ? 4LL : 2LL) * sh->head_dim +
                                   (sh->kv_dtype == COOPT_KV_FP16 ? 0 : 8);
     a.by_pair = a.xcd_pairs * (long long)sh->max_blocks_per_seq * kBlock * token_bytes > kPrefillXcdL2;

@@ -17,13 +17,14 @@ constexpr int kPrefillCUs = 256;                // MI355X: the launch shape is p
 
 // How the tiles of every pair are dealt to launches.  One workgroup (8 waves, 2 tiles each) fills
 // a CU, so a launch runs in rounds of one workgroup per CU, and a last round that is mostly empty
-// costs a full one.  Where that happens the last tiles of every pair go to a second launch: of
-// half-size workgroups (one tile per wave), which takes about 0.65-0.8 of a round -- or, when the
-// caller brings a workspace, of full-size workgroups, `parts` per 16 tiles, that each stream one
-// of `parts` equal runs of the pair's stages, with `parts` (2 to 8) chosen so that the round is as
-// short as it gets (a launch of fewer workgroups than CUs is all "last round": a single
-// sequence's chunk is spread over the chip this way); the parts are combined by
-// prefill_split_merge_kernel.
+// costs a full one.  Where that happens the last tiles of every pair go to a launch of half-size
+// workgroups behind it (one tile per wave), which takes about 0.65-0.8 of a round -- or, when the
+// caller brings a workspace, to full-size workgroups of the same launch, `parts` per 16 tiles, that
+// each stream one of `parts` equal runs of the pair's stages, with `parts` (2 to 8) chosen so that
+// the round is as short as it gets (a launch of fewer workgroups than CUs is all "last round": a
+// single sequence's chunk is spread over the chip this way); the parts are combined by
+// prefill_split_merge_kernel.  (The rounds are counted as if all streams were equally long, which
+// short prompts' are not: 8 fresh prompts of 352 rows take 79 us split and 41 whole.)
 struct PrefillLaunchPlan {
     int tiles, pairs8, a_per_pair, b_per_pair, rest, parts;
     int nr;          // tiles per wave of the full-size workgroups: 2, or 1 where a pair has at most 8 tiles

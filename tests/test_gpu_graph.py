@@ -3,7 +3,7 @@ step once and replay it; a replay has to give what the same calls give eagerly, 
 with eager work of the same library and synchronisations in between.  Captured here: the fused
 step from a prepared schedule (attention launch + merge launch, which also stores the step's new
 rows into the cache), the decode that keeps its partials in the library's built-in array, and a
-prefill chunk (two launches; three with a workspace).  None of them allocates, sets memory or
+prefill chunk (two launches, with and without a workspace).  None of them allocates, sets memory or
 synchronises, so capture needs no special path -- this test is what holds them to that."""
 import numpy as np
 import pytest

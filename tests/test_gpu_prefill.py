@@ -94,10 +94,10 @@ def test_chunk_written_on_device_then_attended(oracle_mod):
 def test_two_launch_split_every_row(oracle_mod, kv_dtype, chunks, with_workspace):
     """As many workgroups as the full configuration (64 pairs, up to 160 tiles each), so the entry
     point splits the work into its two launches, over a short history so that the oracle can check
-    every row; the other cases have a different chunk length per sequence.  With a workspace the
-    second launch streams half of every pair's stages per workgroup and a third one merges the
-    halves (histories of 0 to 250 tokens: halves of one to five stages, and sequences whose last
-    tiles do not exist)."""
+    every row; the other cases have a different chunk length per sequence.  With a workspace one
+    launch holds the whole streams and workgroups that stream half of a pair's stages each, and the
+    other merges the halves (histories of 0 to 250 tokens: halves of one to five stages, and
+    sequences whose last tiles do not exist)."""
     S, H_q, H_k, d = len(chunks), 40, 8, 128
     history = [48, 0, 100, 16, 33, 64, 7, 250]
     lens = [h + c for h, c in zip(history, chunks)]
@@ -225,7 +225,7 @@ def test_tiles_that_are_not_split_are_the_same_bits(S, C, limit, rest, parts, kv
 def test_chunked_prefill_full_size(oracle_mod, record_property):
     """Full configuration in the launch shape the benchmark times.  The oracle computes every row
     of one whole sequence (512 rows x 40 heads over 8192 + 512 tokens: the stage pipeline 136
-    stages deep, every tile of both launches) and, of the other sequences, a sample of rows
+    stages deep, every tile, whole and split) and, of the other sequences, a sample of rows
     (first, last, tile edges, random).  About a minute and a half of oracle time on 16 cores."""
     w = workloads.make(4)
     print(f"full cfg4: tokens={w.total_tokens}", flush=True)
@@ -252,7 +252,7 @@ def test_chunked_prefill_full_size(oracle_mod, record_property):
     same = (got_ws == got).all(axis=2)                         # [row, head]
     tiles_per_head = C // 16
     tile = np.arange(w.H_q)[None, :] % (w.H_q // w.H_k) * tiles_per_head + (np.arange(w.S * C)[:, None] % C) // 16
-    assert same[tile < 128].all(), "rows of the first launch differ between the two entry points"
+    assert same[tile < 128].all(), "rows of whole streams differ between the two entry points"
 
 
 def test_gather_cached_kv(oracle_mod):

@@ -192,8 +192,9 @@ def test_bulk_calls_with_every_slot_pattern(oracle_mod, d, H_k, kv_dtype):
 def test_bulk_windows_equal_rows(d, H_k, kv_dtype):
     """The bulk kernel takes windows of 13, 29 or 61 tokens (cache type and head size) and completes the
     last quad of a window from the next one's rows; its quotients come from a reciprocal.  Call lengths
-    around the windows' edges, runs from every slot offset in ragged pieces with lone tokens between, over every kind of fp16 pattern (zeros of both signs,
-    subnormals, infinities, NaN): the bytes of the row kernel, and nothing written beside them."""
+    around the windows' edges, runs from every slot offset in ragged pieces with lone tokens between,
+    over every kind of fp16 pattern (zeros of both signs, subnormals, infinities, NaN): the bytes of the
+    row kernel, and nothing written beside them."""
     import paper_2602_09323_amd as coopt
     from gpu_utils import dev
     kv = {"e4m3": coopt.COOPT_KV_E4M3, "e5m2": coopt.COOPT_KV_E5M2, "fp16": coopt.COOPT_KV_FP16}[kv_dtype]
