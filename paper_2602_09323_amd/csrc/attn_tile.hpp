@@ -131,6 +131,19 @@ struct TileLoader {
         }
     }
 
+    // One token's scale per lane.
+    __device__ __forceinline__ float load_scale(const float* pool, int tile, int token, bool valid) const
+    {
+        if constexpr (BIG) {
+            const __amdgpu_buffer_rsrc_t r =
+                rsrc(pool + (size_t)(uint32_t)tile * kBlock, valid ? kBlock * 4 : 0);
+            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, 4 * token, 0, 0));
+        } else {
+            const __amdgpu_buffer_rsrc_t r = rsrc(pool, valid ? scale_pool_bytes : 0);
+            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, 4 * token, tile * (kBlock * 4), 0));
+        }
+    }
+
     // `tile` (= physical block * H_k + KV head) must be wave-uniform.
     __device__ __forceinline__ void issue(BlockRegs<HEAD_DIM, KV>& r, int tile, bool valid) const
     {

@@ -14,6 +14,7 @@ typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBlock = 16;          // tokens per cache block (the only supported block_size)
 constexpr float kLog2e = 1.4426950408889634f;

@@ -6,17 +6,22 @@
 // every cache byte is fetched and converted once per WORKGROUP:
 //   * A score tile has 16 query rows of ONE query head as its columns (column n = chunk row
 //     i0+n).  A wavefront carries NR such tiles, a workgroup of 8 wavefronts 8*NR of them (256 rows
-//     at NR = 2), all of the same (sequence, KV head) pair.
-//   * The pair's K/V stream, two 16-token blocks (a group) at a time, through a double-buffered
-//     LDS stage in matrix-core operand order, already converted to fp16.  The waves form two
-//     producer teams that share a stage's groups three to one (the first team's waves are the
+//     at NR = 2), all of the same (sequence, KV head) pair.  Two tiles are one operand of 32 columns.
+//   * The pair's K/V stream, two 16-token blocks (a group) at a time, through a ring of LDS slots
+//     in matrix-core operand order, already converted to fp16.  The waves form two
+//     producer teams that share a stage's four groups three to one (the first team's waves are the
 //     older ones on their SIMDs and get through a stage sooner); in a team wave 0 brings block
 //     A's K, wave 1 block B's K, waves 2 and 3 the V pieces of both blocks (and zero the V entries
 //     and scales of tokens that are not in the cache, so stale bytes cannot reach an accumulator).
-//     All eight then read their operands back with 16-byte LDS loads, conflict-free, and run the
-//     online-softmax update of attn_tile.hpp's arithmetic on each of their tiles.  One barrier
-//     per stage of four groups; the global loads of the stage after next are in flight while a
-//     stage is consumed.
+//     All eight then read their operands back with 16-byte LDS loads and run the online-softmax
+//     update of attn_tile.hpp's arithmetic on their columns.  One barrier per stage of four groups;
+//     the global loads of the stage after next are in flight while a stage is consumed.
+//   * What bounds it: energy.  At d = 128 over E4M3 a stage takes 7 500 cycles against 4 350 of matrix
+//     instructions and the chip lowers its clock to 1.9 GHz; the form with 16x16x32 products and without
+//     the pipeline below took 9 600 cycles at 2.35 GHz, 4.10 us a stage against 3.99.  (On zeros, which
+//     hardly toggle a wire, the clock stays at 2.4 GHz: 731 -> 598 us for 8 x 512 rows over 8192
+//     tokens.)  Without the K/V operand reads from LDS a stage is 11 % shorter, without production
+//     10 %, without exponentials 6 %.
 //   * Workgroup ids are dealt to the 8 XCDs round-robin, so the mapping puts all workgroups of a
 //     pair on ONE XCD: the pair's 2 MB of cache are fetched from HBM once and re-read from that
 //     XCD's L2 by the pair's other workgroups.
@@ -34,7 +39,15 @@
 // (prefill_deal.hpp).  Three fresh prompts of 301, 1039 and 1777 rows (40 over
 // 8 heads, d = 128): 156 us a pass with tiles by head, first rows first and the split streams in a
 // launch behind the whole ones, 100 us so; 8 x 512 rows over 8192 tokens 763 -> 744 us.
+//
+// A workgroup's two ends, where its CU's matrix cores idle, are latency: the rows leave through LDS in
+// whole lines (straight from the registers, 16 bytes of 32 rows an instruction, the CU got its next
+// workgroup 6-8 us after the stream's end, so 3), and the block numbers of three stages are asked for
+// before anything else.  Both together: the three prompts 102 -> 92 us.
+#include <type_traits>
+
 #include "attn_tile.hpp"
+#include "kv_quant.hpp"
 #include "launch_grid.hpp"
 #include "prefill_deal.hpp"
 
@@ -48,6 +61,7 @@ struct PrefillArgs : PrefillDeal {
     const int32_t* query_start;
     half_t* out;
     int32_t H_q, H_k, G;
+    Divisor kv_heads;         // H_k
     int32_t max_blocks;
     int32_t pool_tiles;
     float scale_log2e;
@@ -55,44 +69,25 @@ struct PrefillArgs : PrefillDeal {
 };
 
 constexpr int kPrefillGroupsPerStage = 4;      // two-block groups between two barriers
+constexpr int kPrefillSlots = 2 * kPrefillGroupsPerStage + 1;      // groups in LDS: two stages and one more (below)
 // Groups of a stage produced by the first team (waves 0-3); the second team takes the rest.
 constexpr int kPrefillFirstTeamGroups = 3;
 constexpr float kNoReference = -1.0e30f;        // a running reference below every score
 constexpr long long kPrefillXcdL2 = 4LL << 20;   // bytes of L2 per XCD
 
-// Byte offsets inside one LDS stage (one group = blocks A and B of one KV head).
+// Byte offsets inside one LDS stage (one group = blocks A and B of one KV head, 32 tokens).  Operands
+// are in the order in which a 32x32x16 product takes them, lane 32h + r 16 bytes at 16 (32h + r); the
+// 16x16x32 products of the one-tile kernel find theirs in the same bytes.
 template <int HEAD_DIM>
 struct PrefillStage {
-    static constexpr int kKOps = HEAD_DIM / 32;        // S^T MFMAs per block
-    static constexpr int kVOps = HEAD_DIM / 16;        // O^T MFMAs per group
-    static constexpr int kK = 0;                        // [2 blocks][kKOps][64 lanes] 8 halves
-    static constexpr int kV = 2 * kKOps * 1024;         // [kVOps][64 lanes] 4 halves of A, 4 of B
-    static constexpr int kS = kV + kVOps * 1024;        // 16 floats each: k_scale*c A, B; log2 v_scale A, B
-    static constexpr int kR = kS + 256;                 // [64 lanes] 8 halves: 1/v_scale rows (below)
-    static constexpr int kBytes = kR + 1024;
+    static constexpr int kOps = HEAD_DIM / 16;          // operands of K, and of V
+    static constexpr int kK = 0;                        // [dim / 16][h][token of the group]: dims 8h .. 8h+7
+    static constexpr int kV = kOps * 1024;              // [dim / 32][u][h][dim % 32]: tokens 8u + 4h .. +3 of A, of B
+    static constexpr int kS = 2 * kOps * 1024;          // 16 floats each: k_scale*c A, B; log2 v_scale A, B
+    static constexpr int kR = kS + 256;                 // [u][16 entries, a zero] of 8 halves: 1/v_scale (below)
+    static constexpr int kRStride = 272;
+    static constexpr int kBytes = kR + 2 * kRStride;
 };
-
-// One online-softmax step of a 16-column tile against a group whose operands are ready, in two
-// parts so that the caller can issue the score products of all its tiles before the first
-// softmax (the matrix pipe then works on the next tile's scores and on this tile's P.V while the
-// vector ALU does the exponentials).
-//   kA/kB = K operands of blocks A/B, vop = V operands of the group, ksc = k_scale * softmax_scale
-//   * log2(e) and lv = log2(v_scale) of this lane's 4 tokens per block.  tail / visA / visB as in
-//   group_update (attn_tile.hpp); absent tokens are already zero in vop and have lv = -inf.
-template <int HEAD_DIM>
-__device__ __forceinline__ void tile_scores(const half8_t (&kA)[HEAD_DIM / 32],
-                                            const half8_t (&kB)[HEAD_DIM / 32],
-                                            const half8_t (&qop)[HEAD_DIM / 32], floatx4& sA,
-                                            floatx4& sB)
-{
-    sA = floatx4{0.f, 0.f, 0.f, 0.f};
-    sB = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int jj = 0; jj < HEAD_DIM / 32; ++jj) {
-        sA = mfma_16x16x32(kA[jj], qop[jj], sA);
-        sB = mfma_16x16x32(kB[jj], qop[jj], sB);
-    }
-}
 
 // The weights enter the second product rounded to fp16, w~ = fp16(P * v_scale): one token's weight
 // is then off by up to 2^-10 relative, which shows in the output when that token carries the row
@@ -112,10 +107,10 @@ __device__ __forceinline__ void tile_scores(const half8_t (&kA)[HEAD_DIM / 32],
 // exp2(z' - m) = P * v_scale * 2^(...) then needs no multiplication of its own and is at most
 // 2^(kPShift + kRescaleSlack) whatever the scales are.  A token that is not in the cache has
 // lv = -inf and so the weight 0.
-// The step in four parts, so that the caller can run the parts of its tiles side by side: the
-// scores of a token (one fused multiply-add each) and their maximum; the rare raise of the running
-// reference; the weights; the two matrix products.  TAIL: some of the group's tokens are not
-// visible to every column.
+//
+// One tile (16 columns, lane 16 grp + n: column n, tokens 4 grp .. of blocks A and B): its scores in log2
+// units and their maximum.  TAIL: some of the group's tokens are not visible to every column; visA /
+// visB as in group_update (attn_tile.hpp).  Absent tokens are already zero in V and have lv = -inf.
 template <bool TAIL>
 __device__ __forceinline__ float tile_logits(floatx4 sA, floatx4 sB, floatx4 kscA, floatx4 kscB,
                                              floatx4 lvA, floatx4 lvB, int visA, int visB,
@@ -136,19 +131,6 @@ __device__ __forceinline__ float tile_logits(floatx4 sA, floatx4 sB, floatx4 ksc
     return fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
 }
 
-template <int HEAD_DIM>
-__device__ __forceinline__ void tile_raise(float bm, float& m, floatx4& lacc, floatx4 (&acc)[HEAD_DIM / 16])
-{
-    float nm = fmaxf(bm, __shfl_xor(bm, 16));
-    nm = fmaxf(nm, __shfl_xor(nm, 32));
-    nm = fmaxf(nm, m);
-    const float alpha = __builtin_amdgcn_exp2f(m - nm);   // m = kNoReference at the start gives 0
-    lacc *= alpha;
-#pragma unroll
-    for (int c = 0; c < HEAD_DIM / 16; ++c) acc[c] *= alpha;
-    m = nm;
-}
-
 __device__ __forceinline__ half8_t tile_weights(const float (&z)[8], float m)
 {
     const float mm = m - kPShift;
@@ -164,13 +146,38 @@ __device__ __forceinline__ half8_t tile_weights(const float (&z)[8], float m)
     return pop;
 }
 
-template <int HEAD_DIM>
-__device__ __forceinline__ void tile_pv(const half8_t (&vop)[HEAD_DIM / 16], half8_t rop, half8_t pop,
-                                        floatx4& lacc, floatx4 (&acc)[HEAD_DIM / 16])
+// ---- The two tiles of a wave as ONE tile of 32 columns (lane 32h + c: column c, tile c / 16), for
+// 32x32x16 products.  S^T[token][col]: row = token of the group, so lane (c, h) has the scores of
+// tokens 8j + 4h + 0..3 (j = 0, 1 of block A, 2, 3 of B) in registers 4j ..; as k-slots of
+// O^T[dim][col] += V^T P^T product u takes registers 4u .. and 8 + 4u ..: tokens 8u + 4h of A and of B.
+__device__ __forceinline__ floatx16 mfma_32x32x16(half8_t a, half8_t b, floatx16 c)
 {
-    lacc = mfma_16x16x32(rop, pop, lacc);
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// z = s * ksc + lv of four tokens (registers 4j ..), and their maximum.
+template <bool TAIL>
+__device__ __forceinline__ float wide_logits(floatx16& z, int j, floatx4 ksc, floatx4 lv, int vis)
+{
 #pragma unroll
-    for (int c = 0; c < HEAD_DIM / 16; ++c) acc[c] = mfma_16x16x32(vop[c], pop, acc[c]);
+    for (int i = 0; i < 4; ++i) {
+        const float x = __builtin_fmaf(z[4 * j + i], ksc[i], lv[i]);
+        z[4 * j + i] = TAIL ? (i < vis ? x : -INFINITY) : x;       // (a select also drops a NaN score)
+    }
+    return fmaxf(fmaxf(z[4 * j], z[4 * j + 1]), fmaxf(z[4 * j + 2], z[4 * j + 3]));
+}
+
+// Two weights, registers k and k + 1 of z, as fp16 (cut: a common bias cancels, see above).
+__device__ __forceinline__ half2_t wide_weights(const floatx16& z, int k, float mm)
+{
+    return __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(__builtin_amdgcn_exp2f(z[k] - mm),
+                                                                  __builtin_amdgcn_exp2f(z[k + 1] - mm)));
+}
+// The same from scores that are not scaled yet (an fp16 cache: one factor for all tokens).
+__device__ __forceinline__ half2_t wide_weights(const floatx16& s, int k, float scale, float mm)
+{
+    return __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(__builtin_amdgcn_exp2f(__builtin_fmaf(s[k], scale, -mm)),
+                                                                  __builtin_amdgcn_exp2f(__builtin_fmaf(s[k + 1], scale, -mm))));
 }
 
 template <int HEAD_DIM, int KV, int NR, bool BIG>
@@ -182,7 +189,7 @@ prefill_chunk_kernel(const PrefillArgs a)
     constexpr int NL = BlockRegs<HEAD_DIM, KV>::NL;   // 16-byte pieces per lane of a K (or V) tile
     constexpr int NLH = (NL + 1) / 2;                 // V pieces per V wave
     constexpr int NP = NL > 2 * NLH ? NL : 2 * NLH;   // producer registers per wave
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];     // two stages of GPS groups
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];     // kPrefillSlots groups
 
     const int lane = threadIdx.x & 63;
     const int wave_id = wave_uniform((int)(threadIdx.x >> 6));
@@ -192,7 +199,7 @@ prefill_chunk_kernel(const PrefillArgs a)
     int turn;
     const int pair = prefill_pair(a, blockIdx.x, turn);
     if (pair >= a.num_pairs) return;
-    const int seq = wave_uniform(pair / a.H_k);
+    const int seq = a.kv_heads.quotient(pair);
     const int g = pair - seq * a.H_k;
 
     const int qs = a.query_start[seq];
@@ -210,52 +217,45 @@ prefill_chunk_kernel(const PrefillArgs a)
     const int count = order.count();
     const bool active = first < count;                 // a wave without tiles still produces
 
-    half8_t qop[NR][HEAD_DIM / 32];
-    int limit[NR];          // tokens visible to column n of tile r
-    int tile_of[NR];        // head of the group * tiles_per_head + row / 16
-    int my_max = 0, min_row = 0x7fffffff;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        int hh, i0;
-        order.at(min(first + r, count - 1), i0, hh);             // surplus tiles repeat the last
-        i0 *= 16;
-        const int row = min(i0 + n, C - 1);                      // surplus rows repeat row C-1
-        tile_of[r] = hh * tiles_per_head + i0 / 16;
-        limit[r] = t_ctx + row + 1;
-        my_max = max(my_max, t_ctx + min(i0 + 15, C - 1) + 1);
-        min_row = min(min_row, i0);
-        load_q_operand<HEAD_DIM, KV>(qop[r], a.q + ((size_t)(qs + row) * a.H_q + g * a.G + hh) * HEAD_DIM,
-                                     true, grp);
-    }
-    if (!active) my_max = 0;
-    // the workgroup streams as far as its longest column needs
-    int wg_row, wg_head;
-    order.at(min((block + 1) * (kPrefillWaves * NR), count) - 1, wg_row, wg_head);
-    const int wg_max = t_ctx + min(16 * wg_row + 15, C - 1) + 1;
+    constexpr bool WIDE = NR == 2;                     // two tiles: one product of 32 columns
+    constexpr int NCOL = WIDE ? 32 : 16;
+    constexpr int NQ = HEAD_DIM * NCOL / 512;          // q operands per column tile
+    // Lane r works out tile r of the wave, lane NR the workgroup's last, which sees furthest.
+    int tile_row, tile_head;
+    order.at(lane < NR ? min(first + lane, count - 1)             // surplus tiles repeat the last
+                       : min((block + 1) * (kPrefillWaves * NR), count) - 1, tile_row, tile_head);
+    const int wg_max = t_ctx + min(16 * __builtin_amdgcn_readlane(tile_row, NR) + 15, C - 1) + 1;
     const int nblk = (wg_max + kBlock - 1) / kBlock;
     const int num_groups = (nblk + 1) >> 1;
     const int32_t* bt = a.block_tables + (size_t)seq * a.max_blocks;
+    // A stage holds GPS consecutive groups; one barrier per stage.  The workgroup streams stages
+    // s_lo .. s_hi-1: all of them, or one of `parts` equal runs in a split launch (an empty run
+    // leaves the neutral partial m = kNoReference, l = 0).
+    constexpr int GPS = kPrefillGroupsPerStage;
+    const int num_stages = (num_groups + GPS - 1) / GPS;
+    const int s_lo = parts == 1 ? 0 : wave_uniform(quotient(num_stages * part, parts));
+    const int s_hi = parts == 1 ? num_stages : wave_uniform(quotient(num_stages * (part + 1), parts));
+    const int g_end = min(num_groups, s_hi * GPS);            // groups below this one are mine
 
     float vnorm = 1.0f, vdenorm = 1.0f;                       // set by the pass over the v_scales below
 
-    float m[NR];
-    floatx4 lacc[NR];       // rows 0 and 1 (lanes of group 0, registers 0 and 1): the row sums / 2^8
-    floatx4 acc[NR][HEAD_DIM / 16];
+    // (finite, not -inf: a workgroup that streams a later run of a pair's stages meets columns that
+    // see none of a group's tokens before any they do see, and the weights exp2(z - m) of such a
+    // column must come out as exp2(-inf) = 0, not exp2(-inf + inf))
+    float m = kNoReference;
+    // the row sums / 2^8, in lanes 0..15: rows 0 and 1 (registers 0 and 1) of column n and, wide, rows 2
+    // and 3 of column 16 + n
+    floatx4 lacc = {0.f, 0.f, 0.f, 0.f};
+    typedef std::conditional_t<WIDE, floatx16, floatx4> AccT;
+    AccT acc[HEAD_DIM / NCOL];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        // (finite, not -inf: a workgroup that streams a later run of a pair's stages meets
-        // columns that see none of a group's tokens before any they do see, and the weights
-        // exp2(z - m) of such a column must come out as exp2(-inf) = 0, not exp2(-inf + inf))
-        m[r] = kNoReference;
-        lacc[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < HEAD_DIM / NCOL; ++c)
 #pragma unroll
-        for (int c = 0; c < HEAD_DIM / 16; ++c) acc[r][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int i = 0; i < NCOL * NCOL / 64; ++i) acc[c][i] = 0.f;
 
     // ---- which team produces which group of a stage.  The two waves of a SIMD do not get equal
     // shares of it: the older one (a wave of the first team) is through with a stage's groups well
     // before the younger one, so the first team produces more of the next stage.
-    constexpr int GPS = kPrefillGroupsPerStage;
     constexpr int kFirst = kPrefillFirstTeamGroups;           // sub-groups 0 .. kFirst-1: team 0
     constexpr int kOwn = kFirst > GPS - kFirst ? kFirst : GPS - kFirst;   // most groups a wave holds
     static_assert(kFirst >= 1 && kFirst <= GPS, "the first team produces at least one group");
@@ -274,19 +274,54 @@ prefill_chunk_kernel(const PrefillArgs a)
         return __builtin_amdgcn_raw_buffer_load_b32(bt_rsrc, lane < 2 * kOwn ? 4 * b : 0, 0, 0);
     };
     auto id_of = [&](uint32_t ids, int i, int b) { return __builtin_amdgcn_readlane((int)ids, 2 * i + b); };
+    // (the first three stages' at once, ahead of everything that a wave asks for: the first tiles wait
+    // for nothing else)
+    uint32_t ids = load_ids(s_lo), ids_second = load_ids(s_lo + 1), ids_next = load_ids(s_lo + 2);
+
+    // ---- the queries
+    half8_t qop[NQ];
+    int limit = 0;          // tokens visible to this lane's column
+    int row0_of[NR], head_of[NR];      // of my tiles: first row, head of the group
+    int my_max = 0, min_row = 0x7fffffff;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int hh = __builtin_amdgcn_readlane(tile_head, r), i0 = 16 * __builtin_amdgcn_readlane(tile_row, r);
+        const int row = min(i0 + n, C - 1);                      // surplus rows repeat row C-1
+        row0_of[r] = i0;
+        head_of[r] = hh;
+        my_max = max(my_max, t_ctx + min(i0 + 15, C - 1) + 1);
+        min_row = min(min_row, i0);
+        const half_t* qrow = a.q + ((size_t)(qs + row) * a.H_q + g * a.G + hh) * HEAD_DIM;
+        if (!WIDE || (grp & 1) == r) {                           // (wide: columns 16r .. are tile r's)
+            limit = t_ctx + row + 1;
+#pragma unroll
+            for (int m = 0; m < NQ; ++m)
+                qop[m] = *reinterpret_cast<const half8_t*>(qrow + (WIDE ? 16 * m + 8 * (grp >> 1) : 32 * m + 8 * grp));
+        }
+    }
+    if (!active) my_max = 0;
+    // (a negative softmax scale is the queries' sign: the scores' factor is not negative then)
+    const float scale = fabsf(a.scale_log2e);
+    if (a.scale_log2e < 0.0f) {
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) qop[m] = -qop[m];
+    }
 
     // ---- producer side: this wave's pieces of group p
     const TileLoader<HEAD_DIM, KV, BIG> loader(a.cv, lane, a.pool_tiles);
     u32x4 prs[kOwn][NP];
-    floatx4 pscs[kOwn];
+    float pscs[kOwn];
     // The four producer roles of a team -- 0: K of block A, 1: K of block B, 2 and 3: the two halves
     // of the V pieces of both blocks (and the v_scale work of block A, B).  A V role costs twice a
     // K role (890 against 440 cycles per group).  The two teams take the roles crosswise: waves w
     // and w + 4 share a SIMD, so with the second team's roles shifted by two every SIMD carries
     // one K role and one V role (1 % faster than the same roles in both teams; shifts of one or
     // three, and rotating the roles from group to group inside a team, were slower).
+    const int my_token = 4 * grp + (n & 3);            // of a block: whose scales this lane takes
+    // where its 1 / v_scale goes: u = grp / 2, entry 4 (2h + n / 8) + n / 4, half n % 4
+    const int r_entry = (grp >> 1) * St::kRStride + 16 * (4 * (2 * (grp & 1) + (n >> 3)) + (n >> 2)) + 2 * (n & 3);
     auto role_of = [&](int) { return (wave + 2 * team) & 3; };
-    auto produce_issue = [&](int p, int blockA, int blockB, u32x4 (&pr)[NP], floatx4& psc) {
+    auto produce_issue = [&](int p, int blockA, int blockB, u32x4 (&pr)[NP], float& psc) {
         const int role = role_of(p);
         const int vj0 = role == 2 ? 0 : NLH;               // first V piece of a V role
         const int vcnt = role == 2 ? NLH : NL - NLH;       // and how many it brings
@@ -302,7 +337,7 @@ prefill_chunk_kernel(const PrefillArgs a)
         if (role < 2) {
 #pragma unroll
             for (int j = 0; j < NL; ++j) pr[j] = loader.load_piece(a.cv.k_cache, t_mine, j, ok_mine);
-            if constexpr (FP8) psc = loader.load_scales(a.cv.k_scale, t_mine, ok_mine);
+            if constexpr (FP8) psc = loader.load_scale(a.cv.k_scale, t_mine, my_token, ok_mine);
         } else {
 #pragma unroll
             for (int jj = 0; jj < NLH; ++jj) {
@@ -311,29 +346,32 @@ prefill_chunk_kernel(const PrefillArgs a)
                     pr[2 * jj + 1] = loader.load_piece(a.cv.v_cache, tB, vj0 + jj, okB);
                 }
             }
-            if constexpr (FP8) psc = loader.load_scales(a.cv.v_scale, t_mine, ok_mine);
+            if constexpr (FP8) psc = loader.load_scale(a.cv.v_scale, t_mine, my_token, ok_mine);
         }
     };
-    auto produce_store = [&](int p, unsigned char* st, const u32x4 (&pr)[NP], const floatx4& psc) {
+    auto produce_store = [&](int p, unsigned char* st, const u32x4 (&pr)[NP], float psc) {
         const int role = role_of(p);
         const int vj0 = role == 2 ? 0 : NLH;
         const int vcnt = role == 2 ? NLH : NL - NLH;
         if (role < 2) {
-            unsigned char* kdst = st + St::kK + role * (St::kKOps * 1024) + 16 * lane;
+            // (a one-byte piece: dims 16 (4j + grp) .. +15 of token n, both h; an fp16 one: 8 dims)
+            unsigned char* kdst = st + St::kK + 16 * (16 * role + n) +
+                                  (FP8 ? 1024 * grp : 1024 * (grp >> 1) + 512 * (grp & 1));
 #pragma unroll
             for (int j = 0; j < NL; ++j) {
                 if constexpr (FP8) {
-                    *reinterpret_cast<half8_t*>(kdst + (2 * j) * 1024) = fp8x8_to_half8<KV>(pr[j].x, pr[j].y);
-                    *reinterpret_cast<half8_t*>(kdst + (2 * j + 1) * 1024) = fp8x8_to_half8<KV>(pr[j].z, pr[j].w);
+                    *reinterpret_cast<half8_t*>(kdst + j * 4096) = fp8x8_to_half8<KV>(pr[j].x, pr[j].y);
+                    *reinterpret_cast<half8_t*>(kdst + j * 4096 + 512) = fp8x8_to_half8<KV>(pr[j].z, pr[j].w);
                 } else {
-                    *reinterpret_cast<u32x4*>(kdst + j * 1024) = pr[j];
+                    *reinterpret_cast<u32x4*>(kdst + j * 2048) = pr[j];
                 }
             }
             if constexpr (FP8) {
-                if (n == 0)
-                    *reinterpret_cast<floatx4*>(st + St::kS + 64 * role + 16 * grp) = psc * a.scale_log2e;
+                if (n < 4)
+                    *reinterpret_cast<float*>(st + St::kS + 64 * role + 4 * my_token) = psc * scale;
             }
         } else {
+            unsigned char* vdst = st + St::kV + 512 * grp + 16 * n;       // dim n of the first 32, tokens 4 grp ..
             // this lane's 4 tokens of block A start at 32p + 4grp, of block B 16 later
             const int cacheA = t - (32 * p + 4 * grp), cacheB = cacheA - kBlock;
             uint32_t a0 = 0xffffffffu, a1 = 0xffffffffu, b0 = 0xffffffffu, b1 = 0xffffffffu;
@@ -349,140 +387,128 @@ prefill_chunk_kernel(const PrefillArgs a)
 #pragma unroll
                         for (int cc = 0; cc < 4; ++cc) {
                             const half4_t va = fp8x4_to_half4<KV>(wa[cc]), vb = fp8x4_to_half4<KV>(wb[cc]);
-                            *reinterpret_cast<half8_t*>(st + St::kV + (4 * (vj0 + jj) + cc) * 1024 + 16 * lane) =
+                            *reinterpret_cast<half8_t*>(vdst + (2 * (vj0 + jj) + (cc >> 1)) * 2048 + (cc & 1) * 256) =
                                 half8_t{va[0], va[1], va[2], va[3], vb[0], vb[1], vb[2], vb[3]};
                         }
                     } else {
                         const u32x4 wa = pr[2 * jj] & u32x4{a0, a1, a0, a1};
                         const u32x4 wb = pr[2 * jj + 1] & u32x4{b0, b1, b0, b1};
-                        *reinterpret_cast<u32x4*>(st + St::kV + (2 * (vj0 + jj)) * 1024 + 16 * lane) =
+                        *reinterpret_cast<u32x4*>(vdst + (vj0 + jj) * 2048) =
                             u32x4{wa.x, wa.y, wb.x, wb.y};
-                        *reinterpret_cast<u32x4*>(st + St::kV + (2 * (vj0 + jj) + 1) * 1024 + 16 * lane) =
+                        *reinterpret_cast<u32x4*>(vdst + (vj0 + jj) * 2048 + 256) =
                             u32x4{wa.z, wa.w, wb.z, wb.w};
                     }
                 }
             }
             // v_scale of this role's block (role 2: A, role 3: B) times the pair's normaliser (an
             // exact power of two, the same for every token), zero for tokens not in the cache
-            // (a stale scale), and the operand of the row-sum product: row 0 = 2^-8 / v_scale cut
-            // to fp16, row 1 = the remainder, rows 2..15 zero; block A's tokens are the lane's
-            // first four halves, block B's the other four
-            const int cache = role == 2 ? cacheA : cacheB;
-            floatx4 lv;
-            half4_t rr;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float vs = FP8 ? ((i < cache) ? psc[i] * vnorm : 0.0f) : 1.0f;
-                lv[i] = __builtin_amdgcn_logf(vs);                   // log2; -inf for an absent token
-                // (the hardware reciprocal, 1 ulp: far inside what the fp16 pair keeps)
-                const float r = fminf(vs > 0.0f ? 0.00390625f * __builtin_amdgcn_rcpf(vs) : 0.0f, 65504.0f);
-                const float hi = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, r) & 0xffffe000u);
-                rr[i] = n == 0 ? (half_t)hi : (n == 1 ? (half_t)(r - hi) : (half_t)0.0f);
+            // (a stale scale), one token a lane; and its entries of the row-sum operands: 2^-8 / v_scale
+            // cut to fp16 in row 0 and the remainder in row 1 for columns 0..15, the same in rows 2
+            // and 3 for columns 16..31 (lane n / 4 writes row n / 4; block A's tokens are an
+            // entry's first four halves, block B's the other four)
+            const float vs = FP8 ? ((my_token < (role == 2 ? t - 32 * p : t - 32 * p - kBlock)) ? psc * vnorm : 0.0f) : 1.0f;
+            // (the hardware reciprocal, 1 ulp: far inside what the fp16 pair keeps)
+            const float r = fminf(vs > 0.0f ? 0.00390625f * __builtin_amdgcn_rcpf(vs) : 0.0f, 65504.0f);
+            const float hi = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, r) & 0xffffe000u);
+            *reinterpret_cast<half_t*>(st + St::kR + r_entry + 8 * (role - 2)) = (half_t)((n & 4) ? r - hi : hi);
+            if constexpr (FP8) {                                       // log2; -inf for an absent token
+                if (n < 4) *reinterpret_cast<float*>(st + St::kS + 64 * role + 4 * my_token) = __builtin_amdgcn_logf(vs);
             }
-            if constexpr (FP8) {
-                if (n == 0) *reinterpret_cast<floatx4*>(st + St::kS + 64 * role + 16 * grp) = lv;
-            }
-            *reinterpret_cast<half4_t*>(st + St::kR + 16 * lane + 8 * (role - 2)) = rr;
         }
     };
 
     // ---- consumer side
     const int full_limit = min(t, t_ctx + min_row + 1);   // tokens visible to every column of mine
+    auto op = [&](const unsigned char* st, int at) { return *reinterpret_cast<const half8_t*>(st + at + 16 * lane); };
+    auto scales = [&](const unsigned char* st, int at) { return *reinterpret_cast<const floatx4*>(st + St::kS + at); };
+    const int r_of = (n < 4 ? 16 * (4 * grp + n) : 256);      // my row-sum operand; rows beyond 3 are zero
+    // raises the reference of this lane's column where a score of the group exceeds it
+    auto raise = [&](float bm) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bm > m + kRescaleSlack) == 0, 1)) return;   // wave-uniform
+        float nm = fmaxf(bm, __shfl_xor(bm, 32));
+        if constexpr (!WIDE) nm = fmaxf(nm, __shfl_xor(nm, 16));
+        nm = fmaxf(nm, m);
+        const float alpha = __builtin_amdgcn_exp2f(m - nm);   // m = kNoReference at the start gives 0
+        const float other = __shfl(alpha, 16 + n);             // (wide: column 16 + n's)
+        lacc *= floatx4{alpha, alpha, other, other};
+#pragma unroll
+        for (int c = 0; c < HEAD_DIM / NCOL; ++c) acc[c] *= alpha;
+        m = nm;
+    };
     auto consume = [&](const unsigned char* st, int gi) {
-        half8_t kA[St::kKOps], kB[St::kKOps], vop[St::kVOps];
-#pragma unroll
-        for (int jj = 0; jj < St::kKOps; ++jj) {
-            kA[jj] = *reinterpret_cast<const half8_t*>(st + St::kK + jj * 1024 + 16 * lane);
-            kB[jj] = *reinterpret_cast<const half8_t*>(st + St::kK + (St::kKOps + jj) * 1024 + 16 * lane);
-        }
-#pragma unroll
-        for (int c = 0; c < St::kVOps; ++c)
-            vop[c] = *reinterpret_cast<const half8_t*>(st + St::kV + c * 1024 + 16 * lane);
-        const half8_t rop = *reinterpret_cast<const half8_t*>(st + St::kR + 16 * lane);
-        floatx4 kscA, kscB, lvA, lvB;
-        if constexpr (FP8) {
-            kscA = *reinterpret_cast<const floatx4*>(st + St::kS + 16 * grp);
-            kscB = *reinterpret_cast<const floatx4*>(st + St::kS + 64 + 16 * grp);
-            lvA = *reinterpret_cast<const floatx4*>(st + St::kS + 128 + 16 * grp);
-            lvB = *reinterpret_cast<const floatx4*>(st + St::kS + 192 + 16 * grp);
-        } else {
-            kscA = kscB = floatx4{a.scale_log2e, a.scale_log2e, a.scale_log2e, a.scale_log2e};
-            lvA = lvB = floatx4{0.f, 0.f, 0.f, 0.f};              // log2 of a unit scale
-        }
         const int baseA = 2 * gi * kBlock;
-        const int tokA = baseA + 4 * grp;
-        const bool hasB = 2 * gi + 1 < nblk;
-        const bool tail = !(hasB && baseA + 2 * kBlock <= full_limit);
-        floatx4 sA[NR], sB[NR];
+        const bool tail = baseA + 2 * kBlock > full_limit;        // (a missing block B is beyond every limit)
+        if constexpr (WIDE) {
+            floatx16 z = {};
 #pragma unroll
-        for (int r = 0; r < NR; ++r) tile_scores<HEAD_DIM>(kA, kB, qop[r], sA[r], sB[r]);
-        // every tile's scores and maxima first, ONE (rare) branch for all of them, and then a
-        // single stretch of straight-line code in which the weights of one tile (vector ALU,
-        // exponentials) and the matrix products of the tile before it can run side by side
-        float z[NR][8], bm[NR];
-        if (tail) {
+            for (int k = 0; k < NQ; ++k) z = mfma_32x32x16(op(st, St::kK + 1024 * k), qop[k], z);
+            float bm = -INFINITY;
+            const int h = grp >> 1;
 #pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const int visA = limit[r] - tokA;
-                bm[r] = tile_logits<true>(sA[r], sB[r], kscA, kscB, lvA, lvB, visA, hasB ? visA - kBlock : 0, z[r]);
+            for (int j = 0; j < 4; ++j) {
+                floatx4 ksc = {scale, scale, scale, scale}, lv = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (FP8) {
+                    ksc = scales(st, 32 * j + 16 * h);
+                    lv = scales(st, 128 + 32 * j + 16 * h);
+                }
+                bm = fmaxf(bm, tail ? wide_logits<true>(z, j, ksc, lv, limit - baseA - 8 * j - 4 * h)
+                                    : wide_logits<false>(z, j, ksc, lv, 0));
+            }
+            raise(bm);
+            const float mm = m - kPShift;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                half8_t pop;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const half2_t w = wide_weights(z, 4 * u + 2 * (i & 1) + 8 * (i >> 1), mm);
+                    pop[2 * i] = w.x;
+                    pop[2 * i + 1] = w.y;
+                }
+                lacc = mfma_16x16x32(*reinterpret_cast<const half8_t*>(st + St::kR + u * St::kRStride + r_of), pop, lacc);
+#pragma unroll
+                for (int c = 0; c < HEAD_DIM / 32; ++c)
+                    acc[c] = mfma_32x32x16(op(st, St::kV + 2048 * c + 1024 * u), pop, acc[c]);
             }
         } else {
+            const half8_t rop = *reinterpret_cast<const half8_t*>(
+                st + St::kR + (n < 2 ? (grp >> 1) * St::kRStride + 128 * (grp & 1) + 16 * n : 256));
+            floatx4 sA = {0.f, 0.f, 0.f, 0.f}, sB = {0.f, 0.f, 0.f, 0.f};
+            // (dims 32k + 8 grp .. of token n)
+            const unsigned char* kop = st + St::kK + 1024 * (grp >> 1) + 512 * (grp & 1) + 16 * n;
 #pragma unroll
-            for (int r = 0; r < NR; ++r)
-                bm[r] = tile_logits<false>(sA[r], sB[r], kscA, kscB, lvA, lvB, 0, 0, z[r]);
-        }
-        bool raise = false;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) raise = raise || bm[r] > m[r] + kRescaleSlack;
-        if (__builtin_amdgcn_ballot_w64(raise) != 0) {            // wave-uniform, rare
-#pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (__builtin_amdgcn_ballot_w64(bm[r] > m[r] + kRescaleSlack) != 0)
-                    tile_raise<HEAD_DIM>(bm[r], m[r], lacc[r], acc[r]);
-        }
-        if constexpr (NR == 2) {
-            // tile 0's weights; then tile 0's products with tile 1's weights between them, a pair
-            // of exponentials to every two products (the matrix pipe and the vector ALU then work
-            // side by side: each order is pinned by a scheduling fence); then tile 1's products
-            const half8_t pop0 = tile_weights(z[0], m[0]);
-            __builtin_amdgcn_sched_barrier(0);
-            const float mm1 = m[1] - kPShift;
-            half8_t pop1;
-            lacc[0] = mfma_16x16x32(rop, pop0, lacc[0]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int c = 2 * i; c < 2 * i + 2; ++c)
-                    if (c < HEAD_DIM / 16) acc[0][c] = mfma_16x16x32(vop[c], pop0, acc[0][c]);
-                const half2_t h = __builtin_bit_cast(
-                    half2_t, __builtin_amdgcn_cvt_pkrtz(__builtin_amdgcn_exp2f(z[1][2 * i] - mm1),
-                                                        __builtin_amdgcn_exp2f(z[1][2 * i + 1] - mm1)));
-                pop1[2 * i] = h.x;
-                pop1[2 * i + 1] = h.y;
-                __builtin_amdgcn_sched_barrier(0);
+            for (int k = 0; k < NQ; ++k) {
+                sA = mfma_16x16x32(*reinterpret_cast<const half8_t*>(kop + 2048 * k), qop[k], sA);
+                sB = mfma_16x16x32(*reinterpret_cast<const half8_t*>(kop + 2048 * k + 256), qop[k], sB);
             }
+            floatx4 kscA = {scale, scale, scale, scale}, kscB = kscA;
+            floatx4 lvA = {0.f, 0.f, 0.f, 0.f}, lvB = lvA;              // log2 of a unit scale
+            if constexpr (FP8) {
+                kscA = scales(st, 16 * grp);
+                kscB = scales(st, 64 + 16 * grp);
+                lvA = scales(st, 128 + 16 * grp);
+                lvB = scales(st, 192 + 16 * grp);
+            }
+            float z[8];
+            const int vis = limit - baseA - 4 * grp;
+            raise(tail ? tile_logits<true>(sA, sB, kscA, kscB, lvA, lvB, vis, vis - kBlock, z)
+                       : tile_logits<false>(sA, sB, kscA, kscB, lvA, lvB, 0, 0, z));
+            const half8_t pop = tile_weights(z, m);
+            lacc = mfma_16x16x32(rop, pop, lacc);
 #pragma unroll
-            for (int c = 8; c < HEAD_DIM / 16; ++c) acc[0][c] = mfma_16x16x32(vop[c], pop0, acc[0][c]);
-            tile_pv<HEAD_DIM>(vop, rop, pop1, lacc[1], acc[1]);
-        } else {
-            half8_t pop[NR];
-#pragma unroll
-            for (int r = 0; r < NR; ++r) pop[r] = tile_weights(z[r], m[r]);
-#pragma unroll
-            for (int r = 0; r < NR; ++r) tile_pv<HEAD_DIM>(vop, rop, pop[r], lacc[r], acc[r]);
+            for (int c = 0; c < HEAD_DIM / 16; ++c)
+                acc[c] = mfma_16x16x32(*reinterpret_cast<const half8_t*>(
+                                           st + St::kV + 2048 * (c >> 1) + 256 * (c & 1) + 512 * grp + 16 * n), pop, acc[c]);
         }
     };
-
-    // A stage holds GPS consecutive groups; one barrier per stage.  The workgroup streams stages
-    // s_lo .. s_hi-1: all of them, or one of `parts` equal runs in a split launch (an empty run
-    // leaves the neutral partial m = kNoReference, l = 0).
-    const int num_stages = (num_groups + GPS - 1) / GPS;
-    const int s_lo = wave_uniform((int)((long long)num_stages * part / parts));
-    const int s_hi = wave_uniform((int)((long long)num_stages * (part + 1) / parts));
-    const int g_end = min(num_groups, s_hi * GPS);            // groups below this one are mine
-    auto slot = [&](int si, int sub) { return lds + ((si & 1) * GPS + sub) * St::kBytes; };
+    // Groups live in a ring of slots; `ring` is that of stage si's first group.
+    int ring = 0;
+    auto slot = [&](int sub) {                                // of group `sub` counted from there, 0 .. 2 GPS - 1
+        const int x = ring + sub;
+        return lds + (x >= kPrefillSlots ? x - kPrefillSlots : x) * St::kBytes;
+    };
+    auto next_stage = [&]() { ring = ring + GPS >= kPrefillSlots ? ring + GPS - kPrefillSlots : ring + GPS; };
     // (a wave keeps registers for the sub-groups of its own team)
-    uint32_t ids;
     auto issue_first_stage = [&]() {
 #pragma unroll
         for (int sub = 0; sub < GPS; ++sub)
@@ -490,6 +516,12 @@ prefill_chunk_kernel(const PrefillArgs a)
                 produce_issue(s_lo * GPS + sub, id_of(ids, own_index(sub), 0), id_of(ids, own_index(sub), 1),
                               prs[own_index(sub)], pscs[own_index(sub)]);
     };
+    // the row-sum operands' rows without a token (a row of zeros for all of them), and the unused entries
+    for (int i = threadIdx.x; i < kPrefillSlots * (2 * St::kRStride / 16); i += 64 * kPrefillWaves) {
+        const int of = i / (2 * St::kRStride / 16);
+        *reinterpret_cast<u32x4*>(lds + of * St::kBytes + St::kR + 16 * (i - of * (2 * St::kRStride / 16))) = u32x4{0, 0, 0, 0};
+    }
+    if constexpr (!FP8) __syncthreads();               // (else the barrier of the pass over the v_scales)
     // ---- the pair's largest v_scale as a power of two.  The weights P * v_scale enter the second
     // product as fp16 (5 exponent bits); value rows can be of any magnitude (an E5M2 cache's scales
     // are 2^-7 of an E4M3 cache's, small value rows' smaller still), so every v_scale is divided by
@@ -501,40 +533,39 @@ prefill_chunk_kernel(const PrefillArgs a)
     // (block numbers, scales) run beside the first stage's own two (block numbers, tiles), and a
     // later batch's block numbers beside the scales of the one before.  (One kernel, d = 128 with two
     // tiles per wave over an E5M2 pool of 64-bit addresses, has no registers for both: 12 spills.)
-    constexpr bool kIssueEarly = FP8 && !(HEAD_DIM == 128 && NR == 2 && BIG && KV == COOPT_KV_E5M2);
-    if constexpr (kIssueEarly) ids = load_ids(s_lo);
     if constexpr (FP8) {
         __shared__ float vmax_of_wave[kPrefillWaves];
         float mx = 0.0f;
-        constexpr int kBatch = 8;                          // loads in flight per lane
-        constexpr int kPass = 4 * kPrefillWaves * kBatch;  // blocks per pass of the workgroup
+        constexpr int kBatch = 4;                          // loads in flight per lane
+        constexpr int kPass = 16 * kPrefillWaves * kBatch; // blocks per pass of the workgroup
         int id[kBatch];
         auto batch_ids = [&](int b0) {
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) {             // lane group grp takes block b, all 16 tokens
-                const int b = b0 + (u * kPrefillWaves + wave_id) * 4 + grp;
+            for (int u = 0; u < kBatch; ++u) {             // four lanes take a block, 4 tokens each
+                const int b = b0 + (u * kPrefillWaves + wave_id) * 16 + (lane >> 2);
                 id[u] = b < nblk ? bt[b] : -1;
             }
         };
         const int in_cache = min(wg_max, t);
         batch_ids(0);
         for (int b0 = 0; b0 < nblk; b0 += kPass) {
-            float sc[kBatch];
+            floatx4 sc[kBatch];
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                const int b = b0 + (u * kPrefillWaves + wave_id) * 4 + grp;
-                const bool in = id[u] >= 0 && b * kBlock + n < in_cache;
-                sc[u] = in ? a.cv.v_scale[((size_t)id[u] * a.H_k + g) * kBlock + n] : 0.0f;
+                sc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if (id[u] >= 0)
+                    sc[u] = *reinterpret_cast<const floatx4*>(a.cv.v_scale + ((size_t)id[u] * a.H_k + g) * kBlock + 4 * (lane & 3));
             }
             if (b0 + kPass < nblk) batch_ids(b0 + kPass);
-            if constexpr (kIssueEarly) {
-                if (b0 == 0) issue_first_stage();
+            if (b0 == 0) issue_first_stage();
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int left = in_cache - ((b0 + (u * kPrefillWaves + wave_id) * 16 + (lane >> 2)) * kBlock + 4 * (lane & 3));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mx = fmaxf(mx, i < left ? sc[u][i] : 0.0f);      // (fmaxf drops a NaN)
             }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) mx = fmaxf(mx, sc[u]);      // (fmaxf drops a NaN)
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        mx = wave_max(mx);
         if (lane == 0) vmax_of_wave[wave_id] = mx;
         __syncthreads();
 #pragma unroll
@@ -546,89 +577,241 @@ prefill_chunk_kernel(const PrefillArgs a)
             vdenorm = __builtin_bit_cast(float, (ebits + 1u) << 23);
         }
     }
-    if constexpr (!kIssueEarly) {
-        ids = load_ids(s_lo);
-        issue_first_stage();
-    }
-    ids = load_ids(s_lo + 1);
-    uint32_t ids_next = load_ids(s_lo + 2);
+    if constexpr (!FP8) issue_first_stage();
 #pragma unroll
     for (int sub = 0; sub < GPS; ++sub)
         if (owner(sub) == team && s_lo * GPS + sub < g_end)
-            produce_store(s_lo * GPS + sub, slot(s_lo, sub), prs[own_index(sub)], pscs[own_index(sub)]);
+            produce_store(s_lo * GPS + sub, slot(sub), prs[own_index(sub)], pscs[own_index(sub)]);
 #pragma unroll
     for (int sub = 0; sub < GPS; ++sub)
         if (owner(sub) == team && (s_lo + 1) * GPS + sub < g_end)
-            produce_issue((s_lo + 1) * GPS + sub, id_of(ids, own_index(sub), 0), id_of(ids, own_index(sub), 1),
+            produce_issue((s_lo + 1) * GPS + sub, id_of(ids_second, own_index(sub), 0), id_of(ids_second, own_index(sub), 1),
                           prs[own_index(sub)], pscs[own_index(sub)]);
     __syncthreads();
-    for (int si = s_lo; si < s_hi; ++si) {
+    // The producers' part of stage si's turn, one of the team's groups at a time: the next stage's to LDS,
+    // the one after that asked for.
+    uint32_t ids_use = 0;
+    auto produce = [&](int si, int i) {
+        const int sub = team == 0 ? i : kFirst + i;
+        if (sub >= GPS || (team == 0 && i >= kFirst)) return;
+        const int gn = (si + 1) * GPS + sub;
+        if (gn < g_end) produce_store(gn, slot(GPS + sub), prs[i], pscs[i]);
+        if (i == 0) {
+            // (ahead of the tile loads: by the time those are waited for, the numbers are back)
+            ids_use = ids_next;
+            ids_next = load_ids(si + 3);
+        }
+        if (gn + GPS < g_end) {
+            const int bA = id_of(ids_use, i, 0), bB = id_of(ids_use, i, 1);
+            produce_issue(gn + GPS, bA, bB, prs[i], pscs[i]);
+        }
+    };
+    // Stages of tokens that every column of mine sees run as a pipeline over their groups, so that the
+    // vector ALU has work under every product: the score products of a group run beside the
+    // exponentials of half the tokens of the group before it, that group's value products over those
+    // tokens beside the other half's exponentials, and over the other half beside the new group's
+    // multiply-adds and maxima; the order is pinned by scheduling fences.  Operands are asked for half a
+    // group's products ahead, in the registers that the ones just used leave.  The pipeline does not
+    // drain at a stage's end: the barrier behind which the next stage may be read stands in front of the
+    // stage's last group, and that group's slot is the ring's spare one -- until the next barrier nobody
+    // writes to it.
+    constexpr int W = NQ / 2;                                  // operands in flight
+    constexpr int PER = 8 / NQ;                                // d = 64 has half as many products for the same vector work
+    const int h16 = 16 * (grp >> 1);
+    half8_t ops[W];
+    floatx16 z;
+    auto k_op = [&](const unsigned char* st, int k) { return op(st, St::kK + 1024 * k); };
+    auto v_op = [&](const unsigned char* st, int u, int c) { return op(st, St::kV + 2048 * c + 1024 * u); };
+    auto r_op = [&](const unsigned char* st, int u) {
+        return *reinterpret_cast<const half8_t*>(st + St::kR + u * St::kRStride + r_of);
+    };
+    // The scores of four tokens scaled, and their maximum.  An fp16 cache's are left as they are (the
+    // exponentials' multiply-adds scale them), its maximum scaled behind: the factor is not negative.
+    auto ksc_of = [&](const unsigned char* st, int j) { return FP8 ? scales(st, 32 * j + h16) : floatx4{}; };
+    auto lv_of = [&](const unsigned char* st, int j) { return FP8 ? scales(st, 128 + 32 * j + h16) : floatx4{}; };
+    auto logits = [&](floatx16& x, int j, floatx4 ksc, floatx4 lv) {
+        if constexpr (FP8) return wide_logits<false>(x, j, ksc, lv, 0);
+        else return fmaxf(fmaxf(x[4 * j], x[4 * j + 1]), fmaxf(x[4 * j + 2], x[4 * j + 3]));
+    };
+    auto top = [&](float bm) { return FP8 ? bm : bm * scale; };
+    auto pipeline_start = [&]() {                              // scores of the first group; K operands of the second
+        const unsigned char* st = slot(0);
+        floatx4 ksc[4], lv[4];
+        z = floatx16{};
 #pragma unroll
-        for (int sub = 0; sub < GPS; ++sub) {
-            const int gi = si * GPS + sub;
-            if (gi < g_end && 2 * gi * kBlock < my_max) consume(slot(si, sub), gi);
+        for (int k = 0; k < W; ++k) ops[k] = k_op(st, k);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            ksc[j] = ksc_of(st, j);
+            lv[j] = lv_of(st, j);
         }
 #pragma unroll
-        for (int sub = 0; sub < GPS; ++sub) {
-            const int gn = (si + 1) * GPS + sub;
-            if (owner(sub) == team && gn < g_end)
-                produce_store(gn, slot(si + 1, sub), prs[own_index(sub)], pscs[own_index(sub)]);
+        for (int k = 0; k < NQ; ++k) {
+            z = mfma_32x32x16(ops[k % W], qop[k], z);
+            ops[k % W] = k < W ? k_op(st, k + W) : k_op(slot(1), k - W);
         }
-        // the numbers fetched a stage ago go to scalar registers before anything new is issued,
-        // so that taking them waits for nothing younger than the tiles just stored
-        int blk[kOwn][2];
+        float bm = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < kOwn; ++i) {
-            blk[i][0] = id_of(ids_next, i, 0);
-            blk[i][1] = id_of(ids_next, i, 1);
-            // (pinned here: moved down to their uses, each would wait for the loads issued before it)
-            asm volatile("" : "+s"(blk[i][0]), "+s"(blk[i][1]));
-        }
-        ids_next = load_ids(si + 3);
+        for (int j = 0; j < 4; ++j) bm = fmaxf(bm, logits(z, j, ksc[j], lv[j]));
+        raise(top(bm));
+    };
+    auto pipeline_stage = [&](int si, bool more) {            // more: the stage behind this one is such a stage, too
+        static_assert(kOwn < GPS, "a stage is in LDS before the last group of the one in front of it");
 #pragma unroll
-        for (int sub = 0; sub < GPS; ++sub) {
-            const int g2 = (si + 2) * GPS + sub;
-            if (owner(sub) == team && g2 < g_end)
-                produce_issue(g2, blk[own_index(sub)][0], blk[own_index(sub)][1], prs[own_index(sub)],
-                              pscs[own_index(sub)]);
+        for (int sub = 0; WIDE && sub < GPS; ++sub) {
+            const unsigned char* st = slot(sub);
+            const unsigned char* sn = slot(sub + 1);
+            const float mm = m - kPShift;
+            half8_t pop[2];
+            floatx16 zn = {};
+            floatx4 ksc, lv;
+            half8_t rop;
+            auto weights = [&](int u, int i) {                 // tokens 8u + 4h .. of block A, then of B
+                const int x = 4 * u + 2 * (i & 1) + 8 * (i >> 1);
+                const half2_t w = FP8 ? wide_weights(z, x, mm) : wide_weights(z, x, scale, mm);
+                pop[u][2 * i] = w.x;
+                pop[u][2 * i + 1] = w.y;
+            };
+            if (sub == GPS - 1) {
+                __syncthreads();                               // stage si+1 is complete, and nobody reads stage si but for this group
+#pragma unroll
+                for (int k = 0; k < W; ++k) ops[k] = k_op(sn, k);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) {
+                zn = mfma_32x32x16(ops[k % W], qop[k], zn);
+                ops[k % W] = k < W ? k_op(sn, k + W) : v_op(st, 0, k - W);
+                if (k == NQ - 1) rop = r_op(st, 0);
+#pragma unroll
+                for (int e = 0; e < PER; ++e)
+                    if ((PER * k + e) & 1) weights(0, (PER * k + e) >> 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                if (c == 0) {
+                    lacc = mfma_16x16x32(rop, pop[0], lacc);
+                    rop = r_op(st, 1);
+                }
+                if constexpr (WIDE) acc[c] = mfma_32x32x16(ops[c], pop[0], acc[c]);
+                ops[c] = v_op(st, 1, c);
+                if (c == W - 1) {
+                    ksc = ksc_of(sn, 0);
+                    lv = lv_of(sn, 0);
+                }
+#pragma unroll
+                for (int e = 0; e < PER; ++e) weights(1, PER * c + e);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            float bm = -INFINITY;
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                if (c == 0) lacc = mfma_16x16x32(rop, pop[1], lacc);
+                if constexpr (WIDE) acc[c] = mfma_32x32x16(ops[c], pop[1], acc[c]);
+                if (sub != GPS - 2) ops[c] = k_op(slot(sub + 2), c);
+#pragma unroll
+                for (int e = 0; e < PER; ++e) {
+                    const int j = PER * c + e;
+                    bm = fmaxf(bm, logits(zn, j, ksc, lv));
+                    if (j < 3) {
+                        ksc = ksc_of(sn, j + 1);
+                        lv = lv_of(sn, j + 1);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (sub < kOwn) produce(si, sub);
+            if (sub < GPS - 1 || more) raise(top(bm));
+            z = zn;
         }
-        // stage si+1 is complete, and nobody still reads stage si
-        __syncthreads();
+    };
+
+    // Whole stages that all my columns see, then the others group by group.  (Two loops, not a branch
+    // in one: the pipeline leaves no registers for what the two forms would share.  Waves may change
+    // over at different stages; each passes one barrier per stage.)
+    int si = s_lo;
+    if constexpr (WIDE) {
+        const int whole = min(active ? min(g_end, full_limit / (2 * kBlock)) / GPS : 0, s_hi);
+        if (si < whole) {
+            pipeline_start();
+            for (; si < whole; ++si) {
+                pipeline_stage(si, si + 1 < whole);
+                next_stage();
+            }
+        }
+    }
+    for (; si < s_hi; ++si) {
+#pragma unroll 1
+        for (int gi = si * GPS; gi < min((si + 1) * GPS, g_end) && 2 * gi * kBlock < my_max; ++gi)
+            consume(slot(gi - si * GPS), gi);
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) produce(si, i);
+        __syncthreads();                                       // stage si+1 is complete, and nobody reads stage si
+        next_stage();
     }
 
     if (!active) return;
+    // the sums of the lane's column: rows 0 and 1 of lacc (wide: rows 2 and 3 for columns 16..31)
+    const float sum_a = __shfl(lacc[0] + lacc[1], n), sum_b = __shfl(lacc[2] + lacc[3], n);
+    const float L = (WIDE && (grp & 1) ? sum_b : sum_a) * 256.0f;
+    // The rows leave through LDS, so that a store instruction writes whole rows: a lane's registers are
+    // 4 dims of 8 each (register 4j + i of acc[c]: dim NCOL c + 8j + 4h + i; one column tile: 16c + 4 grp + i),
+    // 16 bytes of 32 rows an instruction.  Every wave has a slot of its own: of the last stage only its
+    // last group can still be read by others, and that is the ring's ninth.
+    constexpr int NJ = WIDE ? 4 : 1;
+    const int dim0 = 4 * (WIDE ? grp >> 1 : grp);
+    const int col = WIDE ? lane & 31 : n;
+    unsigned char* mine = slot(wave_id);
+    static_assert(2 * GPS >= kPrefillWaves && 32 * (4 * HEAD_DIM + 16) <= St::kBytes, "a wave's rows fit its slot");
+    // (the 2^kPShift common to acc and l cancels; the normaliser of the v_scales is in acc alone)
+    if (parts > 1) {
+        // this run's share of the tiles: reference, row sum and unnormalised sums per column
+        constexpr int kRow = 4 * HEAD_DIM + 16;
+#pragma unroll
+        for (int c = 0; c < HEAD_DIM / NCOL; ++c)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                *reinterpret_cast<floatx4*>(mine + col * kRow + 4 * (NCOL * c + 8 * j + dim0)) =
+                    floatx4{acc[c][4 * j], acc[c][4 * j + 1], acc[c][4 * j + 2], acc[c][4 * j + 3]} * vdenorm;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            if (first + r >= count) break;
+            float* dst = a.part + (((size_t)pair * a.tail_cap + head_of[r] * tiles_per_head + row0_of[r] / 16 - share.base) * parts + part) * (16 * (HEAD_DIM + 2));
+            if (dim0 == 0 && col >> 4 == r) {
+                dst[n] = m;
+                dst[16 + n] = L;
+            }
+#pragma unroll
+            for (int at = 4 * lane; at < 16 * HEAD_DIM; at += 256)
+                *reinterpret_cast<floatx4*>(dst + 32 + at) = *reinterpret_cast<const floatx4*>(
+                    mine + (16 * r + at / HEAD_DIM) * kRow + 4 * (at % HEAD_DIM));
+        }
+        return;
+    }
+    constexpr int kRow = 2 * HEAD_DIM + 16;
+    const float inv = (1.0f / L) * vdenorm;
+#pragma unroll
+    for (int c = 0; c < HEAD_DIM / NCOL; ++c)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            half4_t o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = (half_t)(acc[c][4 * j + i] * inv);
+            *reinterpret_cast<half4_t*>(mine + col * kRow + 2 * (NCOL * c + 8 * j + dim0)) = o;
+        }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        // column n's sum sits in rows 0 and 1 of lacc: lane (n, 0), registers 0 and 1
-        const float L = __shfl(lacc[r][0] + lacc[r][1], n) * 256.0f;
-        // (the 2^kPShift common to acc and l cancels; the normaliser of the v_scales is in acc alone)
-        if (parts > 1) {
-            // this run's share of the tile: reference, row sum and unnormalised sums per column
-            if (first + r < count) {
-                const int tile = tile_of[r] - share.base;
-                float* dst = a.part + (((size_t)pair * a.tail_cap + tile) * parts + part) * (16 * (HEAD_DIM + 2));
-                if (grp == 0) {
-                    dst[n] = m[r];
-                    dst[16 + n] = L;
-                }
+        if (first + r >= count) break;
+        half_t* dst = a.out + ((size_t)(qs + row0_of[r]) * a.H_q + g * a.G + head_of[r]) * HEAD_DIM;
 #pragma unroll
-                for (int c = 0; c < HEAD_DIM / 16; ++c)
-                    *reinterpret_cast<floatx4*>(dst + 32 + n * HEAD_DIM + 16 * c + 4 * grp) = acc[r][c] * vdenorm;
-            }
-            continue;
-        }
-        const float inv = (1.0f / L) * vdenorm;
-        const int hh = wave_uniform(tile_of[r] / tiles_per_head);
-        const int row = (tile_of[r] - hh * tiles_per_head) * 16 + n;
-        if (first + r < count && row < C) {
-            half_t* dst = a.out + ((size_t)(qs + row) * a.H_q + g * a.G + hh) * HEAD_DIM + 4 * grp;
-#pragma unroll
-            for (int c = 0; c < HEAD_DIM / 16; ++c) {
-                half4_t h;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) h[i] = (half_t)(acc[r][c][i] * inv);
-                *reinterpret_cast<half4_t*>(dst + 16 * c) = h;
-            }
+        for (int at = 8 * lane; at < 16 * HEAD_DIM; at += 512) {
+            const int rr = at / HEAD_DIM;
+            if (row0_of[r] + rr < C)
+                *reinterpret_cast<u32x4*>(dst + (size_t)rr * a.H_q * HEAD_DIM + at % HEAD_DIM) =
+                    *reinterpret_cast<const u32x4*>(mine + (16 * r + rr) * kRow + 2 * (at % HEAD_DIM));
         }
     }
 }
@@ -783,6 +966,7 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     a.out = (half_t*)out;
     a.H_q = sh->num_q_heads;
     a.H_k = sh->num_kv_heads;
+    a.kv_heads = Divisor(sh->num_kv_heads);
     a.G = sh->num_q_heads / sh->num_kv_heads;
     a.max_blocks = sh->max_blocks_per_seq;
     a.pool_tiles = sh->num_blocks * sh->num_kv_heads;
@@ -805,7 +989,7 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     a.by_pair = a.xcd_pairs * (long long)sh->max_blocks_per_seq * kBlock * token_bytes > kPrefillXcdL2;
     if ((long long)pairs8 * (a_per_pair + b_per_pair + split_per_pair) > 0x7fffffffLL) return COOPT_ERR_SHAPE;
     const dim3 block(64 * kPrefillWaves);
-    const size_t lds = 2 * kPrefillGroupsPerStage *
+    const size_t lds = kPrefillSlots *
                        (size_t)(sh->head_dim == 128 ? PrefillStage<128>::kBytes : PrefillStage<64>::kBytes);
     hipStream_t stream = (hipStream_t)hip_stream;
     const bool big = !pool_fits_small(sh);

@@ -15,6 +15,34 @@ constexpr int kPrefillWaves = 8;                // two teams of four producer ro
 constexpr int kPrefillMaxParts = 8;             // runs a split launch cuts a stream into, at most
 constexpr int kPrefillCUs = 256;                // MI355X: the launch shape is planned for its CU count
 
+// A divisor that the host knows: a quotient of wave-uniform values is then a product on the scalar unit
+// (a division goes through the vector ALU, 0.1 us of a workgroup's start each).  0 <= x < 2^31.
+struct Divisor {
+    uint32_t d, m;             // m = floor((2^32 - 1) / d): the high half of x m is the quotient or one less
+    Divisor() = default;
+    explicit Divisor(int by) : d((uint32_t)by), m(0xffffffffu / (uint32_t)by) {}
+    __device__ __forceinline__ int quotient(int x) const
+    {
+        const uint32_t q = (uint32_t)(((uint64_t)(uint32_t)x * m) >> 32);
+        return (int)(q + ((uint32_t)x - q * d >= d ? 1u : 0u));
+    }
+};
+
+// x / y for a divisor that only the device knows, 0 <= x, 1 <= y.  Below 2^22 by way of binary32: x and y
+// are exact there, the reciprocal is off by an ulp and the product by half of one, so the truncated
+// product is the quotient or one off it.
+__device__ __forceinline__ int quotient(int x, int y)
+{
+    if (x >= (1 << 22)) return (int)((uint32_t)x / (uint32_t)y);
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float r = __builtin_amdgcn_rcpf((float)y);
+#else
+    const float r = 1.0f / (float)y;
+#endif
+    const int q = (int)((float)x * r), left = x - q * y;
+    return q + (left >= y ? 1 : 0) - (left < 0 ? 1 : 0);
+}
+
 // How the tiles of every pair are dealt to launches.  One workgroup (8 waves, 2 tiles each) fills
 // a CU, so a launch runs in rounds of one workgroup per CU, and a last round that is mostly empty
 // costs a full one.  Where that happens the last tiles of every pair go to a launch of half-size
@@ -110,6 +138,7 @@ struct PrefillDeal {
     int32_t split;            // parts (0: no such workgroups; 1: whole streams, rows written to out)
     int32_t split_blocks;     // runs of 16 tiles per pair they cover
     int32_t tail_cap;         // tiles per pair they cover (sizes the workspace)
+    Divisor pairs_of_xcd, whole_of_pair, split_of_pair, split_parts;     // (at least 1 each)
 
     // The first launch of a plan (its only one but for a plan's half-size workgroups).
     void set(const PrefillLaunchPlan& lp, int pairs)
@@ -122,6 +151,7 @@ struct PrefillDeal {
         split = lp.parts;
         split_blocks = lp.parts > 0 ? lp.split_per_pair() / lp.parts : 0;
         tail_cap = lp.parts > 0 ? lp.rest : 0;
+        set_divisors();
     }
     // ... and the one of half-size workgroups behind it: the tiles that it left.
     void set_rest(const PrefillLaunchPlan& lp)
@@ -129,6 +159,15 @@ struct PrefillDeal {
         tile_base = tile_limit;
         tile_limit = 0x7fffffff;
         blocks_per_pair = lp.b_per_pair;
+        set_divisors();
+    }
+    void set_divisors()
+    {
+        const int num_split = split * split_blocks;
+        pairs_of_xcd = Divisor(xcd_pairs > 0 ? xcd_pairs : 1);
+        whole_of_pair = Divisor(blocks_per_pair > 0 ? blocks_per_pair : 1);
+        split_of_pair = Divisor(num_split > 0 ? num_split : 1);
+        split_parts = Divisor(split > 0 ? split : 1);
     }
 };
 
@@ -145,10 +184,10 @@ __device__ __forceinline__ int prefill_pair(const PrefillDeal& a, unsigned wg, i
     if (a.by_pair) {
         const int k = k8 < whole ? k8 : k8 - whole;
         const int per = k8 < whole ? a.blocks_per_pair : num_split;
-        xcd_pair = wave_uniform(k / per);
+        xcd_pair = k8 < whole ? a.whole_of_pair.quotient(k) : a.split_of_pair.quotient(k);
         turn = k - xcd_pair * per + (k8 < whole ? 0 : a.blocks_per_pair);
     } else {
-        turn = wave_uniform(k8 / a.xcd_pairs);
+        turn = a.pairs_of_xcd.quotient(k8);
         xcd_pair = k8 - turn * a.xcd_pairs;
     }
     return xcd_pair * 8 + (wg & 7);
@@ -171,14 +210,15 @@ __device__ __forceinline__ PrefillShare prefill_share(const PrefillDeal& a, int 
     const int num_split = a.split * a.split_blocks;
     int ahead = a.blocks_per_pair;                     // whole-stream workgroups before the split ones
     if (num_split > 0 && !a.by_pair) {
-        const int shorter = wave_uniform((int)(((long long)t / a.split - (t - C)) * a.blocks_per_pair / C));
+        // (in binary32, the same for every workgroup of the pair: it only places them)
+        const int shorter = wave_uniform((int)((float)(a.split_parts.quotient(t) - (t - C)) * (float)a.blocks_per_pair / (float)C));
         ahead -= min(max(shorter, 0), a.blocks_per_pair);
     }
     PrefillShare s;
     s.tail = turn >= ahead && turn < ahead + num_split;
     const int nth = s.tail ? turn - ahead : (turn < ahead ? turn : turn - num_split);
     s.parts = s.tail ? a.split : 1;
-    const int split_block = wave_uniform(nth / s.parts);
+    const int split_block = s.tail ? a.split_parts.quotient(nth) : nth;
     s.part = nth - split_block * s.parts;              // which run of the pair's stages is mine
     s.block = (s.tail ? a.split_blocks : a.blocks_per_pair) - 1 - split_block;
     s.base = s.tail ? a.tile_limit : a.tile_base;
@@ -195,9 +235,9 @@ struct TileOrder {
     __device__ __forceinline__ TileOrder(int tiles_per_head, int b, int e) : T(tiles_per_head), base(b), end(e)
     {
         // (wave_uniform: the quotients are made on the vector ALU; this keeps them out of its registers)
-        hb = wave_uniform(b / T);
+        hb = wave_uniform(quotient(b, T));
         ib = b - hb * T;
-        he = wave_uniform(e / T);
+        he = wave_uniform(quotient(e, T));
         ie = e - he * T;
     }
     __device__ __forceinline__ int count() const { return end - base; }
@@ -208,10 +248,9 @@ struct TileOrder {
         const int N = he - hb, b1 = min(ib, ie), b2 = max(ib, ie);
         const int c2 = ie > ib ? N + 1 : N - 1;                  // tiles per row between b1 and b2
         const int n1 = b1 * N, n2 = n1 + (b2 - b1) * c2;
-        if (p < n1) i = p / N;
-        else if (p < n2) i = b1 + (p - n1) / c2;
-        else i = b2 + (p - n2) / max(N, 1);
-        i = wave_uniform(i);
+        // (one division whatever the lane's third of the rows; max: a divisor even where nothing divides)
+        const bool mid = p >= n1 && p < n2;
+        i = (p < n1 ? 0 : mid ? b1 : b2) + quotient(p - (p < n1 ? 0 : mid ? n1 : n2), max(mid ? c2 : N, 1));
         h = p - (i * N + min(i, ie) - min(i, ib)) + hb + (i < ib ? 1 : 0);
     }
 };
