@@ -53,7 +53,7 @@ struct CacheView {
 // An E5M2 cache's scales are 2^-7 of an E4M3 cache's (largest code 57344 against 448), so its
 // weights are carried 2^7 higher: P * 2^13 * v_scale then lies where the E4M3 weights lie, well
 // inside fp16's normal range for value rows of ordinary magnitude, and at most 2^15 * 65504/57344.
-constexpr float kPShift = 6.0f;                     // (chunked prefill: it normalises the scales itself)
+constexpr float kPShift = 6.0f;                     // (chunked prefill: v_scale is in the exponent there)
 constexpr float kRescaleSlack = 2.0f;
 template <int KV> constexpr float kPShiftOf = KV == COOPT_KV_E5M2 ? 13.0f : 6.0f;
 template <int KV> constexpr float kPUnshiftOf = KV == COOPT_KV_E5M2 ? 1.0f / 8192.0f : 1.0f / 64.0f;
@@ -131,16 +131,16 @@ struct TileLoader {
         }
     }
 
-    // One token's scale per lane.
-    __device__ __forceinline__ float load_scale(const float* pool, int tile, int token, bool valid) const
+    // One token's scale per lane, of a tile that differs between lanes (0 where the tile is none).
+    __device__ __forceinline__ float load_scale_of(const float* pool, int tile, int token) const
     {
         if constexpr (BIG) {
-            const __amdgpu_buffer_rsrc_t r =
-                rsrc(pool + (size_t)(uint32_t)tile * kBlock, valid ? kBlock * 4 : 0);
-            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, 4 * token, 0, 0));
+            float x = 0.0f;
+            if (tile >= 0) x = pool[(size_t)(uint32_t)tile * kBlock + token];
+            return x;
         } else {
-            const __amdgpu_buffer_rsrc_t r = rsrc(pool, valid ? scale_pool_bytes : 0);
-            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, 4 * token, tile * (kBlock * 4), 0));
+            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                 rsrc(pool, scale_pool_bytes), tile * (kBlock * 4) + 4 * token, 0, 0));
         }
     }
 

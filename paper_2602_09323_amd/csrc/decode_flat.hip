@@ -33,19 +33,6 @@ __device__ __forceinline__ int groups_of(int context_len)
     return (nb + 1) >> 1;
 }
 
-// Inclusive prefix sum over the 64 lanes on the vector ALU (DPP row shifts, then the two row
-// broadcasts that carry a row's total into the following rows); no LDS round trips.
-__device__ __forceinline__ int wave_inclusive_scan(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 -> rows 1, 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 -> rows 2, 3
-    return v;
-}
-
 // Sum over the 64 lanes by the same steps.
 __device__ __forceinline__ float wave_sum(float a)
 {

@@ -5,14 +5,16 @@
 // Query length > 1 makes this a dense contraction, so the matrix cores are used at full width and
 // every cache byte is fetched and converted once per WORKGROUP:
 //   * A score tile has 16 query rows of ONE query head as its columns (column n = chunk row
-//     i0+n).  A wavefront carries NR such tiles, a workgroup of 8 wavefronts 8*NR of them (256 rows
-//     at NR = 2), all of the same (sequence, KV head) pair.  Two tiles are one operand of 32 columns.
+//     i0+n).  A wavefront carries two such tiles as one operand of 32 columns, a workgroup of 8
+//     wavefronts 16 of them (256 rows), all of the same (sequence, KV head) pair; or 8 tiles, four
+//     waves' worth, where a pair has no more (the other waves then bring three quarters of the stream:
+//     8 sequences x 16 rows over 8192 tokens 72 -> 61 us, one 16-column tile a wave before).
 //   * The pair's K/V stream, two 16-token blocks (a group) at a time, through a ring of LDS slots
 //     in matrix-core operand order, already converted to fp16.  The waves form two
 //     producer teams that share a stage's four groups three to one (the first team's waves are the
 //     older ones on their SIMDs and get through a stage sooner); in a team wave 0 brings block
-//     A's K, wave 1 block B's K, waves 2 and 3 the V pieces of both blocks (and zero the V entries
-//     and scales of tokens that are not in the cache, so stale bytes cannot reach an accumulator).
+//     A's K and all K scales, wave 1 block B's K and the V scales, waves 2 and 3 the V pieces of both
+//     blocks (tokens that are not in the cache are zeroed, so stale bytes cannot reach an accumulator).
 //     All eight then read their operands back with 16-byte LDS loads and run the online-softmax
 //     update of attn_tile.hpp's arithmetic on their columns.  One barrier per stage of four groups;
 //     the global loads of the stage after next are in flight while a stage is consumed.
@@ -42,10 +44,9 @@
 //
 // A workgroup's two ends, where its CU's matrix cores idle, are latency: the rows leave through LDS in
 // whole lines (straight from the registers, 16 bytes of 32 rows an instruction, the CU got its next
-// workgroup 6-8 us after the stream's end, so 3), and the block numbers of three stages are asked for
-// before anything else.  Both together: the three prompts 102 -> 92 us.
-#include <type_traits>
-
+// workgroup 6-8 us after the stream's end, so 3), the block numbers of three stages are asked for
+// before anything else, and nothing is read ahead of the stream (a pass over all v_scales for their
+// largest took 3-6 us a workgroup).  Together: the three prompts 102 -> 90 us, 8 x 352 rows 92 -> 80.
 #include "attn_tile.hpp"
 #include "kv_quant.hpp"
 #include "launch_grid.hpp"
@@ -66,11 +67,14 @@ struct PrefillArgs : PrefillDeal {
     int32_t pool_tiles;
     float scale_log2e;
     float* part;              // the split workgroups' partial rows, in the workspace
+    int32_t rank_bits;        // > 0: workgroups in the order of their streams' lengths, which have so many bits (in stages)
 };
 
-constexpr int kPrefillGroupsPerStage = 4;      // two-block groups between two barriers
+constexpr int kPrefillGroupsPerStage = kPrefillStageTokens / (2 * kBlock);      // two-block groups between two barriers
 constexpr int kPrefillSlots = 2 * kPrefillGroupsPerStage + 1;      // groups in LDS: two stages and one more (below)
 // Groups of a stage produced by the first team (waves 0-3); the second team takes the rest.
+// ... of a workgroup of 8 tiles, whose first team alone consumes.
+constexpr int kPrefillFirstTeamGroupsOf8 = 1;
 constexpr int kPrefillFirstTeamGroups = 3;
 constexpr float kNoReference = -1.0e30f;        // a running reference below every score
 constexpr long long kPrefillXcdL2 = 4LL << 20;   // bytes of L2 per XCD
@@ -84,9 +88,11 @@ struct PrefillStage {
     static constexpr int kK = 0;                        // [dim / 16][h][token of the group]: dims 8h .. 8h+7
     static constexpr int kV = kOps * 1024;              // [dim / 32][u][h][dim % 32]: tokens 8u + 4h .. +3 of A, of B
     static constexpr int kS = 2 * kOps * 1024;          // 16 floats each: k_scale*c A, B; log2 v_scale A, B
-    static constexpr int kR = kS + 256;                 // [u][16 entries, a zero] of 8 halves: 1/v_scale (below)
-    static constexpr int kRStride = 272;
-    static constexpr int kBytes = kR + 2 * kRStride;
+    static constexpr int kF = kS + 256;                 // the factor that the 1/v_scale entries carry, undone (below)
+    static constexpr int kR = kF + 16;                  // [u][h][cut, remainder] of 8 halves: 1/v_scale (below)
+    static constexpr int kZero = 128;                   // of kR: 16 bytes of zeros, and again kRStride behind them
+    static constexpr int kRStride = 64;
+    static constexpr int kBytes = kS + 512;
 };
 
 // The weights enter the second product rounded to fp16, w~ = fp16(P * v_scale): one token's weight
@@ -97,55 +103,16 @@ struct PrefillStage {
 // that times the weighted mean deviation of the value rows from the result -- nothing for one
 // token or a dominant one.  (For the same reason the convert may truncate: a common bias of the
 // weights cancels.)  The sum runs on the matrix cores: `rop` is a 16-row operand whose row 0
-// holds 2^-8 / v_scale of the group's 32 tokens cut to fp16 and row 1 the remainder (the producers
-// write it), so one more 16x16x32 product per tile accumulates it in rows 0 and 1 of `lacc`,
+// holds 2^-8 / v_scale of the group's 32 tokens, times a power of two that the sum is freed of again, cut
+// to fp16 and row 1 the remainder (the producers write it), so one more 16x16x32 product per tile accumulates it in rows 0 and 1 of `lacc`,
 // which replaces eight vector additions.
 //
 // v_scale reaches the weight through the exponent: the producers leave lv = log2(v_scale) beside
-// k_scale (both already normalised, see the kernel), the score of a token is z' = s * ksc + lv in
+// k_scale, the score of a token is z' = s * ksc + lv in
 // one fused multiply-add, and the running reference m follows the maximum of z'.  The weight
 // exp2(z' - m) = P * v_scale * 2^(...) then needs no multiplication of its own and is at most
 // 2^(kPShift + kRescaleSlack) whatever the scales are.  A token that is not in the cache has
 // lv = -inf and so the weight 0.
-//
-// One tile (16 columns, lane 16 grp + n: column n, tokens 4 grp .. of blocks A and B): its scores in log2
-// units and their maximum.  TAIL: some of the group's tokens are not visible to every column; visA /
-// visB as in group_update (attn_tile.hpp).  Absent tokens are already zero in V and have lv = -inf.
-template <bool TAIL>
-__device__ __forceinline__ float tile_logits(floatx4 sA, floatx4 sB, floatx4 kscA, floatx4 kscB,
-                                             floatx4 lvA, floatx4 lvB, int visA, int visB,
-                                             float (&z)[8])
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        z[i] = __builtin_fmaf(sA[i], kscA[i], lvA[i]);
-        z[4 + i] = __builtin_fmaf(sB[i], kscB[i], lvB[i]);
-    }
-    if constexpr (TAIL) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {                   // (a select also drops a NaN score)
-            z[i] = (i < visA) ? z[i] : -INFINITY;
-            z[4 + i] = (i < visB) ? z[4 + i] : -INFINITY;
-        }
-    }
-    return fmaxf(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), fmaxf(fmaxf(z[4], z[5]), fmaxf(z[6], z[7])));
-}
-
-__device__ __forceinline__ half8_t tile_weights(const float (&z)[8], float m)
-{
-    const float mm = m - kPShift;
-    half8_t pop;
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-        const half2_t h = __builtin_bit_cast(
-            half2_t, __builtin_amdgcn_cvt_pkrtz(__builtin_amdgcn_exp2f(z[i] - mm),      // invisible: exp2(-inf) = 0
-                                                __builtin_amdgcn_exp2f(z[i + 1] - mm)));
-        pop[i] = h.x;
-        pop[i + 1] = h.y;
-    }
-    return pop;
-}
-
 // ---- The two tiles of a wave as ONE tile of 32 columns (lane 32h + c: column c, tile c / 16), for
 // 32x32x16 products.  S^T[token][col]: row = token of the group, so lane (c, h) has the scores of
 // tokens 8j + 4h + 0..3 (j = 0, 1 of block A, 2, 3 of B) in registers 4j ..; as k-slots of
@@ -180,7 +147,8 @@ __device__ __forceinline__ half2_t wide_weights(const floatx16& s, int k, float 
                                                                   __builtin_amdgcn_exp2f(__builtin_fmaf(s[k + 1], scale, -mm))));
 }
 
-template <int HEAD_DIM, int KV, int NR, bool BIG>
+// TILES: of a workgroup, 16 or, where a pair has no more, 8 (whose first four waves alone consume).
+template <int HEAD_DIM, int KV, int TILES, bool BIG>
 __global__ void __launch_bounds__(64 * kPrefillWaves, 2)
 prefill_chunk_kernel(const PrefillArgs a)
 {
@@ -196,34 +164,61 @@ prefill_chunk_kernel(const PrefillArgs a)
     const int wave = wave_id & 3;                      // producer role inside its team
     const int team = wave_id >> 2;                     // which groups of a stage it produces: below
     const int n = lane & 15, grp = lane >> 4;
-    int turn;
-    const int pair = prefill_pair(a, blockIdx.x, turn);
-    if (pair >= a.num_pairs) return;
+    int pair, turn, qs, C, t;
+    if (a.rank_bits > 0) {
+        // Lane p: the XCD's p-th pair.  The stream length (in stages) of the workgroup that I am in the
+        // order of all pairs' items by length, bit by bit; then which of the items of that length.
+        const int my_pair = 8 * lane + (int)(blockIdx.x & 7), rank = blockIdx.x >> 3;
+        const bool there = lane < a.xcd_pairs && my_pair < a.num_pairs;
+        const int my_seq = there ? a.kv_heads.quotient(my_pair) : 0;
+        const int my_qs = a.query_start[my_seq], my_C = there ? a.query_start[my_seq + 1] - my_qs : 0;
+        const int my_t = a.context_lens[my_seq];
+        const PairItems items(a, my_t, my_C, a.G, TILES);
+        const int stages = stages_of_rank(rank, a.rank_bits, [&](int l) { return wave_total(items.at_least(l)); });
+        if (stages == 0) return;                                   // fewer items than workgroups
+        const int longer = items.at_least(stages + 1), here = items.at_least(stages) - longer;
+        const int behind = rank - wave_total(longer);              // among the items of this length
+        const int before = wave_inclusive_scan(here) - here;
+        const unsigned long long mine = __builtin_amdgcn_ballot_w64(behind >= before && behind < before + here);
+        if (mine == 0) return;                                     // (a length beyond what the block table holds)
+        const int it = __builtin_ctzll(mine);
+        const int my_turn = items.turn(stages, behind - before);
+        pair = 8 * it + (int)(blockIdx.x & 7);
+        turn = __builtin_amdgcn_readlane(my_turn, it);
+        qs = __builtin_amdgcn_readlane(my_qs, it);
+        C = __builtin_amdgcn_readlane(my_C, it);
+        t = __builtin_amdgcn_readlane(my_t, it);
+    } else {
+        pair = prefill_pair(a, blockIdx.x, turn);
+        if (pair >= a.num_pairs) return;
+        const int seq = a.kv_heads.quotient(pair);
+        qs = a.query_start[seq];
+        C = a.query_start[seq + 1] - qs;
+        t = a.context_lens[seq];
+        if (C <= 0) return;
+    }
     const int seq = a.kv_heads.quotient(pair);
     const int g = pair - seq * a.H_k;
-
-    const int qs = a.query_start[seq];
-    const int C = a.query_start[seq + 1] - qs;
-    const int t = a.context_lens[seq];
     const int t_ctx = t - C;
-    if (C <= 0) return;
     const int tiles_per_head = (C + 15) / 16;
     const int total_tiles = a.G * tiles_per_head;
     const PrefillShare share = prefill_share(a, turn, t, C, total_tiles);
-    const int block = share.block, parts = share.parts, part = share.part;
-    if (share.base + block * (kPrefillWaves * NR) >= share.end) return;    // the whole workgroup leaves together
-    const TileOrder order(tiles_per_head, share.base, share.end);
-    const int first = block * (kPrefillWaves * NR) + wave_id * NR;     // position of my first tile
+    const bool whole = share.parts == 1 || prefill_runs_whole(a, t);
+    if (whole && share.part > 0) return;
+    const int block = share.block, parts = whole ? 1 : share.parts, part = share.part;
+    if (share.base + block * TILES >= share.end) return;    // the whole workgroup leaves together
+    TileOrder order(tiles_per_head, share.base, share.end);
+    order.to_scalar();
+    constexpr int NR = 2;                              // tiles of a wave: its 32 columns
+    const int first = block * TILES + wave_id * NR;    // position of my first tile
     const int count = order.count();
-    const bool active = first < count;                 // a wave without tiles still produces
+    const bool active = wave_id * NR < TILES && first < count;     // a wave without tiles still produces
 
-    constexpr bool WIDE = NR == 2;                     // two tiles: one product of 32 columns
-    constexpr int NCOL = WIDE ? 32 : 16;
-    constexpr int NQ = HEAD_DIM * NCOL / 512;          // q operands per column tile
+    constexpr int NQ = HEAD_DIM / 16;                  // q operands
     // Lane r works out tile r of the wave, lane NR the workgroup's last, which sees furthest.
     int tile_row, tile_head;
     order.at(lane < NR ? min(first + lane, count - 1)             // surplus tiles repeat the last
-                       : min((block + 1) * (kPrefillWaves * NR), count) - 1, tile_row, tile_head);
+                       : min((block + 1) * TILES, count) - 1, tile_row, tile_head);
     const int wg_max = t_ctx + min(16 * __builtin_amdgcn_readlane(tile_row, NR) + 15, C - 1) + 1;
     const int nblk = (wg_max + kBlock - 1) / kBlock;
     const int num_groups = (nblk + 1) >> 1;
@@ -237,26 +232,20 @@ prefill_chunk_kernel(const PrefillArgs a)
     const int s_hi = parts == 1 ? num_stages : wave_uniform(quotient(num_stages * (part + 1), parts));
     const int g_end = min(num_groups, s_hi * GPS);            // groups below this one are mine
 
-    float vnorm = 1.0f, vdenorm = 1.0f;                       // set by the pass over the v_scales below
-
     // (finite, not -inf: a workgroup that streams a later run of a pair's stages meets columns that
     // see none of a group's tokens before any they do see, and the weights exp2(z - m) of such a
     // column must come out as exp2(-inf) = 0, not exp2(-inf + inf))
     float m = kNoReference;
-    // the row sums / 2^8, in lanes 0..15: rows 0 and 1 (registers 0 and 1) of column n and, wide, rows 2
-    // and 3 of column 16 + n
+    // the row sums / 2^8, in lanes 0..15: rows 0 and 1 (registers 0 and 1) of column n, 2 and 3 of 16 + n
     floatx4 lacc = {0.f, 0.f, 0.f, 0.f};
-    typedef std::conditional_t<WIDE, floatx16, floatx4> AccT;
-    AccT acc[HEAD_DIM / NCOL];
+    floatx16 acc[HEAD_DIM / 32];
 #pragma unroll
-    for (int c = 0; c < HEAD_DIM / NCOL; ++c)
-#pragma unroll
-        for (int i = 0; i < NCOL * NCOL / 64; ++i) acc[c][i] = 0.f;
+    for (int c = 0; c < HEAD_DIM / 32; ++c) acc[c] = floatx16{};
 
     // ---- which team produces which group of a stage.  The two waves of a SIMD do not get equal
     // shares of it: the older one (a wave of the first team) is through with a stage's groups well
     // before the younger one, so the first team produces more of the next stage.
-    constexpr int kFirst = kPrefillFirstTeamGroups;           // sub-groups 0 .. kFirst-1: team 0
+    constexpr int kFirst = TILES == 8 ? kPrefillFirstTeamGroupsOf8 : kPrefillFirstTeamGroups;           // sub-groups 0 .. kFirst-1: team 0
     constexpr int kOwn = kFirst > GPS - kFirst ? kFirst : GPS - kFirst;   // most groups a wave holds
     static_assert(kFirst >= 1 && kFirst <= GPS, "the first team produces at least one group");
     auto owner = [](int sub) { return sub < kFirst ? 0 : 1; };
@@ -280,25 +269,24 @@ prefill_chunk_kernel(const PrefillArgs a)
 
     // ---- the queries
     half8_t qop[NQ];
-    int limit = 0;          // tokens visible to this lane's column
     int row0_of[NR], head_of[NR];      // of my tiles: first row, head of the group
     int my_max = 0, min_row = 0x7fffffff;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const int hh = __builtin_amdgcn_readlane(tile_head, r), i0 = 16 * __builtin_amdgcn_readlane(tile_row, r);
-        const int row = min(i0 + n, C - 1);                      // surplus rows repeat row C-1
-        row0_of[r] = i0;
-        head_of[r] = hh;
-        my_max = max(my_max, t_ctx + min(i0 + 15, C - 1) + 1);
-        min_row = min(min_row, i0);
-        const half_t* qrow = a.q + ((size_t)(qs + row) * a.H_q + g * a.G + hh) * HEAD_DIM;
-        if (!WIDE || (grp & 1) == r) {                           // (wide: columns 16r .. are tile r's)
-            limit = t_ctx + row + 1;
-#pragma unroll
-            for (int m = 0; m < NQ; ++m)
-                qop[m] = *reinterpret_cast<const half8_t*>(qrow + (WIDE ? 16 * m + 8 * (grp >> 1) : 32 * m + 8 * grp));
-        }
+        head_of[r] = __builtin_amdgcn_readlane(tile_head, r);
+        row0_of[r] = 16 * __builtin_amdgcn_readlane(tile_row, r);
+        my_max = max(my_max, t_ctx + min(row0_of[r] + 15, C - 1) + 1);
+        min_row = min(min_row, row0_of[r]);
     }
+    // (columns 16r .. are tile r's; surplus rows repeat row C-1)
+    const bool second = grp & 1;
+    const int h = grp >> 1;                    // lane 32h + c: column c
+    const int my_row = min((second ? row0_of[NR - 1] : row0_of[0]) + n, C - 1);
+    const int limit = t_ctx + my_row + 1;      // tokens visible to this lane's column
+    const half_t* qrow = a.q + ((size_t)(qs + my_row) * a.H_q + g * a.G + (second ? head_of[NR - 1] : head_of[0])) * HEAD_DIM +
+                         8 * h;
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) qop[m] = *reinterpret_cast<const half8_t*>(qrow + 16 * m);
     if (!active) my_max = 0;
     // (a negative softmax scale is the queries' sign: the scores' factor is not negative then)
     const float scale = fabsf(a.scale_log2e);
@@ -317,9 +305,10 @@ prefill_chunk_kernel(const PrefillArgs a)
     // and w + 4 share a SIMD, so with the second team's roles shifted by two every SIMD carries
     // one K role and one V role (1 % faster than the same roles in both teams; shifts of one or
     // three, and rotating the roles from group to group inside a team, were slower).
+    float norm = 0x1p126f;                             // of the v_scales (below): the first one lowers it
     const int my_token = 4 * grp + (n & 3);            // of a block: whose scales this lane takes
-    // where its 1 / v_scale goes: u = grp / 2, entry 4 (2h + n / 8) + n / 4, half n % 4
-    const int r_entry = (grp >> 1) * St::kRStride + 16 * (4 * (2 * (grp & 1) + (n >> 3)) + (n >> 2)) + 2 * (n & 3);
+    // (v_scale: of block A where n < 8, of B otherwise; 1 / v_scale cut to fp16, or with n & 4 the rest)
+    const int r_entry = (grp >> 1) * St::kRStride + 32 * (grp & 1) + 16 * ((n >> 2) & 1) + 8 * (n >> 3) + 2 * (n & 3);
     auto role_of = [&](int) { return (wave + 2 * team) & 3; };
     auto produce_issue = [&](int p, int blockA, int blockB, u32x4 (&pr)[NP], float& psc) {
         const int role = role_of(p);
@@ -335,9 +324,12 @@ prefill_chunk_kernel(const PrefillArgs a)
         const bool ok_mine = 2 * p + mine < nblk;
         const int t_mine = mine ? tB : tA;
         if (role < 2) {
+            // (ahead of the pieces: its address is made in vector registers, and one that a load will fill is
+            // waited for; an absent B's scales are A's, which nobody looks at)
+            if constexpr (FP8)
+                psc = loader.load_scale_of(role == 0 ? a.cv.k_scale : a.cv.v_scale, n >= 8 && okB ? tB : tA, my_token);
 #pragma unroll
             for (int j = 0; j < NL; ++j) pr[j] = loader.load_piece(a.cv.k_cache, t_mine, j, ok_mine);
-            if constexpr (FP8) psc = loader.load_scale(a.cv.k_scale, t_mine, my_token, ok_mine);
         } else {
 #pragma unroll
             for (int jj = 0; jj < NLH; ++jj) {
@@ -346,7 +338,6 @@ prefill_chunk_kernel(const PrefillArgs a)
                     pr[2 * jj + 1] = loader.load_piece(a.cv.v_cache, tB, vj0 + jj, okB);
                 }
             }
-            if constexpr (FP8) psc = loader.load_scale(a.cv.v_scale, t_mine, my_token, ok_mine);
         }
     };
     auto produce_store = [&](int p, unsigned char* st, const u32x4 (&pr)[NP], float psc) {
@@ -367,8 +358,32 @@ prefill_chunk_kernel(const PrefillArgs a)
                 }
             }
             if constexpr (FP8) {
-                if (n < 4)
-                    *reinterpret_cast<float*>(st + St::kS + 64 * role + 4 * my_token) = psc * scale;
+                float* dst = reinterpret_cast<float*>(st + St::kS + 128 * role + 64 * (n >> 3) + 4 * my_token);
+                if (role == 0) {
+                    if ((n & 4) == 0) *dst = psc * scale;
+                } else {
+                    // The group's v_scales, one token a lane: the logarithms, and the entries of the row-sum
+                    // operands, 2^-8 / v_scale cut to fp16 and the remainder (an entry: four tokens of block A,
+                    // the same of B).  Scales may be of any magnitude (an E5M2 cache's are 2^-7 of an E4M3
+                    // cache's, small value rows' smaller still) and fp16 holds five bits of exponent, so the
+                    // entries are taken times a power of two, 1 over the one just above the largest scale so
+                    // far, which the group's row sums are multiplied by again: both are exact.
+                    const bool there = my_token + (n >= 8 ? kBlock : 0) < t - 32 * p;      // (else a stale scale)
+                    const float vs = there ? psc : 0.0f;
+                    if ((n & 4) == 0) *dst = __builtin_amdgcn_logf(vs);                    // log2; -inf: absent
+                    // (kept from group to group: one vote in the place of a reduction, but where a scale is
+                    // larger than all before it)
+                    if (__builtin_amdgcn_ballot_w64(vs * norm > 1.0f) != 0) {
+                        // largest = f * 2^e, f in [1, 2): norm = 2^-(e+1)
+                        const uint32_t ebits = (__builtin_bit_cast(uint32_t, wave_max(fmaxf(vs, 0.0f))) >> 23) & 0xffu;
+                        if (ebits > 0u && ebits < 253u) norm = __builtin_bit_cast(float, (253u - ebits) << 23);
+                    }
+                    if (lane == 0) *reinterpret_cast<float*>(st + St::kF) = norm;
+                    // (the hardware reciprocal, 1 ulp: far inside what the fp16 pair keeps)
+                    const float r = fminf(vs > 0.0f ? 0.00390625f * __builtin_amdgcn_rcpf(vs * norm) : 0.0f, 65504.0f);
+                    const float hi = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, r) & 0xffffe000u);
+                    *reinterpret_cast<half_t*>(st + St::kR + r_entry) = (half_t)((n & 4) ? r - hi : hi);
+                }
             }
         } else {
             unsigned char* vdst = st + St::kV + 512 * grp + 16 * n;       // dim n of the first 32, tokens 4 grp ..
@@ -400,20 +415,6 @@ prefill_chunk_kernel(const PrefillArgs a)
                     }
                 }
             }
-            // v_scale of this role's block (role 2: A, role 3: B) times the pair's normaliser (an
-            // exact power of two, the same for every token), zero for tokens not in the cache
-            // (a stale scale), one token a lane; and its entries of the row-sum operands: 2^-8 / v_scale
-            // cut to fp16 in row 0 and the remainder in row 1 for columns 0..15, the same in rows 2
-            // and 3 for columns 16..31 (lane n / 4 writes row n / 4; block A's tokens are an
-            // entry's first four halves, block B's the other four)
-            const float vs = FP8 ? ((my_token < (role == 2 ? t - 32 * p : t - 32 * p - kBlock)) ? psc * vnorm : 0.0f) : 1.0f;
-            // (the hardware reciprocal, 1 ulp: far inside what the fp16 pair keeps)
-            const float r = fminf(vs > 0.0f ? 0.00390625f * __builtin_amdgcn_rcpf(vs) : 0.0f, 65504.0f);
-            const float hi = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, r) & 0xffffe000u);
-            *reinterpret_cast<half_t*>(st + St::kR + r_entry + 8 * (role - 2)) = (half_t)((n & 4) ? r - hi : hi);
-            if constexpr (FP8) {                                       // log2; -inf for an absent token
-                if (n < 4) *reinterpret_cast<float*>(st + St::kS + 64 * role + 4 * my_token) = __builtin_amdgcn_logf(vs);
-            }
         }
     };
 
@@ -421,85 +422,60 @@ prefill_chunk_kernel(const PrefillArgs a)
     const int full_limit = min(t, t_ctx + min_row + 1);   // tokens visible to every column of mine
     auto op = [&](const unsigned char* st, int at) { return *reinterpret_cast<const half8_t*>(st + at + 16 * lane); };
     auto scales = [&](const unsigned char* st, int at) { return *reinterpret_cast<const floatx4*>(st + St::kS + at); };
-    const int r_of = (n < 4 ? 16 * (4 * grp + n) : 256);      // my row-sum operand; rows beyond 3 are zero
+    // My row-sum operand: the cut reciprocals and the rest of tokens 8u + 4h .. are rows 0 and 1 in the lanes
+    // of columns 0..15 (grp even), rows 2 and 3 in those of columns 16..31; zeros elsewhere.
+    const int r_of = (n >> 1) == (grp & 1) ? 32 * h + 16 * (n & 1) : St::kZero;
+    auto r_op = [&](const unsigned char* st, int u) {
+        return *reinterpret_cast<const half8_t*>(st + St::kR + u * St::kRStride + r_of);
+    };
+    auto norm_of = [&](const unsigned char* st) { return FP8 ? *reinterpret_cast<const float*>(st + St::kF) : 1.0f; };
     // raises the reference of this lane's column where a score of the group exceeds it
     auto raise = [&](float bm) {
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(bm > m + kRescaleSlack) == 0, 1)) return;   // wave-uniform
         float nm = fmaxf(bm, __shfl_xor(bm, 32));
-        if constexpr (!WIDE) nm = fmaxf(nm, __shfl_xor(nm, 16));
         nm = fmaxf(nm, m);
         const float alpha = __builtin_amdgcn_exp2f(m - nm);   // m = kNoReference at the start gives 0
-        const float other = __shfl(alpha, 16 + n);             // (wide: column 16 + n's)
+        const float other = __shfl(alpha, 16 + n);             // (column 16 + n's)
         lacc *= floatx4{alpha, alpha, other, other};
 #pragma unroll
-        for (int c = 0; c < HEAD_DIM / NCOL; ++c) acc[c] *= alpha;
+        for (int c = 0; c < HEAD_DIM / 32; ++c) acc[c] *= alpha;
         m = nm;
     };
     auto consume = [&](const unsigned char* st, int gi) {
         const int baseA = 2 * gi * kBlock;
         const bool tail = baseA + 2 * kBlock > full_limit;        // (a missing block B is beyond every limit)
-        if constexpr (WIDE) {
-            floatx16 z = {};
+        floatx16 z = {};
 #pragma unroll
-            for (int k = 0; k < NQ; ++k) z = mfma_32x32x16(op(st, St::kK + 1024 * k), qop[k], z);
-            float bm = -INFINITY;
-            const int h = grp >> 1;
+        for (int k = 0; k < NQ; ++k) z = mfma_32x32x16(op(st, St::kK + 1024 * k), qop[k], z);
+        float bm = -INFINITY;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                floatx4 ksc = {scale, scale, scale, scale}, lv = {0.f, 0.f, 0.f, 0.f};
-                if constexpr (FP8) {
-                    ksc = scales(st, 32 * j + 16 * h);
-                    lv = scales(st, 128 + 32 * j + 16 * h);
-                }
-                bm = fmaxf(bm, tail ? wide_logits<true>(z, j, ksc, lv, limit - baseA - 8 * j - 4 * h)
-                                    : wide_logits<false>(z, j, ksc, lv, 0));
-            }
-            raise(bm);
-            const float mm = m - kPShift;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                half8_t pop;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const half2_t w = wide_weights(z, 4 * u + 2 * (i & 1) + 8 * (i >> 1), mm);
-                    pop[2 * i] = w.x;
-                    pop[2 * i + 1] = w.y;
-                }
-                lacc = mfma_16x16x32(*reinterpret_cast<const half8_t*>(st + St::kR + u * St::kRStride + r_of), pop, lacc);
-#pragma unroll
-                for (int c = 0; c < HEAD_DIM / 32; ++c)
-                    acc[c] = mfma_32x32x16(op(st, St::kV + 2048 * c + 1024 * u), pop, acc[c]);
-            }
-        } else {
-            const half8_t rop = *reinterpret_cast<const half8_t*>(
-                st + St::kR + (n < 2 ? (grp >> 1) * St::kRStride + 128 * (grp & 1) + 16 * n : 256));
-            floatx4 sA = {0.f, 0.f, 0.f, 0.f}, sB = {0.f, 0.f, 0.f, 0.f};
-            // (dims 32k + 8 grp .. of token n)
-            const unsigned char* kop = st + St::kK + 1024 * (grp >> 1) + 512 * (grp & 1) + 16 * n;
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-                sA = mfma_16x16x32(*reinterpret_cast<const half8_t*>(kop + 2048 * k), qop[k], sA);
-                sB = mfma_16x16x32(*reinterpret_cast<const half8_t*>(kop + 2048 * k + 256), qop[k], sB);
-            }
-            floatx4 kscA = {scale, scale, scale, scale}, kscB = kscA;
-            floatx4 lvA = {0.f, 0.f, 0.f, 0.f}, lvB = lvA;              // log2 of a unit scale
+        for (int j = 0; j < 4; ++j) {
+            floatx4 ksc = {scale, scale, scale, scale}, lv = {0.f, 0.f, 0.f, 0.f};
             if constexpr (FP8) {
-                kscA = scales(st, 16 * grp);
-                kscB = scales(st, 64 + 16 * grp);
-                lvA = scales(st, 128 + 16 * grp);
-                lvB = scales(st, 192 + 16 * grp);
+                ksc = scales(st, 32 * j + 16 * h);
+                lv = scales(st, 128 + 32 * j + 16 * h);
             }
-            float z[8];
-            const int vis = limit - baseA - 4 * grp;
-            raise(tail ? tile_logits<true>(sA, sB, kscA, kscB, lvA, lvB, vis, vis - kBlock, z)
-                       : tile_logits<false>(sA, sB, kscA, kscB, lvA, lvB, 0, 0, z));
-            const half8_t pop = tile_weights(z, m);
-            lacc = mfma_16x16x32(rop, pop, lacc);
-#pragma unroll
-            for (int c = 0; c < HEAD_DIM / 16; ++c)
-                acc[c] = mfma_16x16x32(*reinterpret_cast<const half8_t*>(
-                                           st + St::kV + 2048 * (c >> 1) + 256 * (c & 1) + 512 * grp + 16 * n), pop, acc[c]);
+            bm = fmaxf(bm, tail ? wide_logits<true>(z, j, ksc, lv, limit - baseA - 8 * j - 4 * h)
+                                : wide_logits<false>(z, j, ksc, lv, 0));
         }
+        raise(bm);
+        const float mm = m - kPShift;
+        floatx4 sum = FP8 ? floatx4{} : lacc;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            half8_t pop;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const half2_t w = wide_weights(z, 4 * u + 2 * (i & 1) + 8 * (i >> 1), mm);
+                pop[2 * i] = w.x;
+                pop[2 * i + 1] = w.y;
+            }
+            sum = mfma_16x16x32(r_op(st, u), pop, sum);
+#pragma unroll
+            for (int c = 0; c < HEAD_DIM / 32; ++c)
+                acc[c] = mfma_32x32x16(op(st, St::kV + 2048 * c + 1024 * u), pop, acc[c]);
+        }
+        lacc = FP8 ? lacc + sum * norm_of(st) : sum;
     };
     // Groups live in a ring of slots; `ring` is that of stage si's first group.
     int ring = 0;
@@ -516,68 +492,15 @@ prefill_chunk_kernel(const PrefillArgs a)
                 produce_issue(s_lo * GPS + sub, id_of(ids, own_index(sub), 0), id_of(ids, own_index(sub), 1),
                               prs[own_index(sub)], pscs[own_index(sub)]);
     };
-    // the row-sum operands' rows without a token (a row of zeros for all of them), and the unused entries
-    for (int i = threadIdx.x; i < kPrefillSlots * (2 * St::kRStride / 16); i += 64 * kPrefillWaves) {
-        const int of = i / (2 * St::kRStride / 16);
-        *reinterpret_cast<u32x4*>(lds + of * St::kBytes + St::kR + 16 * (i - of * (2 * St::kRStride / 16))) = u32x4{0, 0, 0, 0};
+    // the zeros of every slot's row-sum operands; over an fp16 cache the others as well (every scale is 1)
+    if (threadIdx.x < 16 * kPrefillSlots) {
+        const int of = threadIdx.x & 15;                                   // 16 bytes of the 256 at kR
+        const bool zero = of == St::kZero / 16 || of == (St::kZero + St::kRStride) / 16;
+        const uint32_t w = zero || (of & 1) ? 0u : 0x1c001c00u;            // 2^-8, and no remainder
+        if (zero || (!FP8 && of < St::kZero / 16))
+            *reinterpret_cast<u32x4*>(lds + (threadIdx.x >> 4) * St::kBytes + St::kR + 16 * of) = u32x4{w, w, w, w};
     }
-    if constexpr (!FP8) __syncthreads();               // (else the barrier of the pass over the v_scales)
-    // ---- the pair's largest v_scale as a power of two.  The weights P * v_scale enter the second
-    // product as fp16 (5 exponent bits); value rows can be of any magnitude (an E5M2 cache's scales
-    // are 2^-7 of an E4M3 cache's, small value rows' smaller still), so every v_scale is divided by
-    // the power of two just above the largest one among the tokens this workgroup reads: the
-    // weights of the rows that matter then sit at fp16's upper end whatever the rows' magnitude.
-    // The row sum divides each weight by the same normalised scale, so the factor stays in the
-    // numerator alone and is taken out, exactly, in the final division.  One pass over the pair's
-    // scales (64 bytes per block) before the first stage is stored; its two dependent round trips
-    // (block numbers, scales) run beside the first stage's own two (block numbers, tiles), and a
-    // later batch's block numbers beside the scales of the one before.  (One kernel, d = 128 with two
-    // tiles per wave over an E5M2 pool of 64-bit addresses, has no registers for both: 12 spills.)
-    if constexpr (FP8) {
-        __shared__ float vmax_of_wave[kPrefillWaves];
-        float mx = 0.0f;
-        constexpr int kBatch = 4;                          // loads in flight per lane
-        constexpr int kPass = 16 * kPrefillWaves * kBatch; // blocks per pass of the workgroup
-        int id[kBatch];
-        auto batch_ids = [&](int b0) {
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {             // four lanes take a block, 4 tokens each
-                const int b = b0 + (u * kPrefillWaves + wave_id) * 16 + (lane >> 2);
-                id[u] = b < nblk ? bt[b] : -1;
-            }
-        };
-        const int in_cache = min(wg_max, t);
-        batch_ids(0);
-        for (int b0 = 0; b0 < nblk; b0 += kPass) {
-            floatx4 sc[kBatch];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                sc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-                if (id[u] >= 0)
-                    sc[u] = *reinterpret_cast<const floatx4*>(a.cv.v_scale + ((size_t)id[u] * a.H_k + g) * kBlock + 4 * (lane & 3));
-            }
-            if (b0 + kPass < nblk) batch_ids(b0 + kPass);
-            if (b0 == 0) issue_first_stage();
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int left = in_cache - ((b0 + (u * kPrefillWaves + wave_id) * 16 + (lane >> 2)) * kBlock + 4 * (lane & 3));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) mx = fmaxf(mx, i < left ? sc[u][i] : 0.0f);      // (fmaxf drops a NaN)
-            }
-        }
-        mx = wave_max(mx);
-        if (lane == 0) vmax_of_wave[wave_id] = mx;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kPrefillWaves; ++i) mx = fmaxf(mx, vmax_of_wave[i]);
-        // mx = f * 2^e with f in [1, 2): vnorm = 2^-(e+1), exact; nothing to normalise if no scale is positive
-        const uint32_t ebits = (__builtin_bit_cast(uint32_t, mx) >> 23) & 0xffu;
-        if (mx > 0.0f && ebits > 0u && ebits < 253u) {
-            vnorm = __builtin_bit_cast(float, (253u - ebits) << 23);
-            vdenorm = __builtin_bit_cast(float, (ebits + 1u) << 23);
-        }
-    }
-    if constexpr (!FP8) issue_first_stage();
+    issue_first_stage();
 #pragma unroll
     for (int sub = 0; sub < GPS; ++sub)
         if (owner(sub) == team && s_lo * GPS + sub < g_end)
@@ -617,14 +540,11 @@ prefill_chunk_kernel(const PrefillArgs a)
     // writes to it.
     constexpr int W = NQ / 2;                                  // operands in flight
     constexpr int PER = 8 / NQ;                                // d = 64 has half as many products for the same vector work
-    const int h16 = 16 * (grp >> 1);
+    const int h16 = 16 * h;
     half8_t ops[W];
     floatx16 z;
     auto k_op = [&](const unsigned char* st, int k) { return op(st, St::kK + 1024 * k); };
     auto v_op = [&](const unsigned char* st, int u, int c) { return op(st, St::kV + 2048 * c + 1024 * u); };
-    auto r_op = [&](const unsigned char* st, int u) {
-        return *reinterpret_cast<const half8_t*>(st + St::kR + u * St::kRStride + r_of);
-    };
     // The scores of four tokens scaled, and their maximum.  An fp16 cache's are left as they are (the
     // exponentials' multiply-adds scale them), its maximum scaled behind: the factor is not negative.
     auto ksc_of = [&](const unsigned char* st, int j) { return FP8 ? scales(st, 32 * j + h16) : floatx4{}; };
@@ -658,7 +578,7 @@ prefill_chunk_kernel(const PrefillArgs a)
     auto pipeline_stage = [&](int si, bool more) {            // more: the stage behind this one is such a stage, too
         static_assert(kOwn < GPS, "a stage is in LDS before the last group of the one in front of it");
 #pragma unroll
-        for (int sub = 0; WIDE && sub < GPS; ++sub) {
+        for (int sub = 0; sub < GPS; ++sub) {
             const unsigned char* st = slot(sub);
             const unsigned char* sn = slot(sub + 1);
             const float mm = m - kPShift;
@@ -666,6 +586,8 @@ prefill_chunk_kernel(const PrefillArgs a)
             floatx16 zn = {};
             floatx4 ksc, lv;
             half8_t rop;
+            floatx4 sum;
+            float norm;
             auto weights = [&](int u, int i) {                 // tokens 8u + 4h .. of block A, then of B
                 const int x = 4 * u + 2 * (i & 1) + 8 * (i >> 1);
                 const half2_t w = FP8 ? wide_weights(z, x, mm) : wide_weights(z, x, scale, mm);
@@ -691,10 +613,11 @@ prefill_chunk_kernel(const PrefillArgs a)
 #pragma unroll
             for (int c = 0; c < W; ++c) {
                 if (c == 0) {
-                    lacc = mfma_16x16x32(rop, pop[0], lacc);
+                    sum = mfma_16x16x32(rop, pop[0], FP8 ? floatx4{} : lacc);
                     rop = r_op(st, 1);
+                    norm = norm_of(st);
                 }
-                if constexpr (WIDE) acc[c] = mfma_32x32x16(ops[c], pop[0], acc[c]);
+                acc[c] = mfma_32x32x16(ops[c], pop[0], acc[c]);
                 ops[c] = v_op(st, 1, c);
                 if (c == W - 1) {
                     ksc = ksc_of(sn, 0);
@@ -707,8 +630,8 @@ prefill_chunk_kernel(const PrefillArgs a)
             float bm = -INFINITY;
 #pragma unroll
             for (int c = 0; c < W; ++c) {
-                if (c == 0) lacc = mfma_16x16x32(rop, pop[1], lacc);
-                if constexpr (WIDE) acc[c] = mfma_32x32x16(ops[c], pop[1], acc[c]);
+                if (c == 0) sum = mfma_16x16x32(rop, pop[1], sum);
+                acc[c] = mfma_32x32x16(ops[c], pop[1], acc[c]);
                 if (sub != GPS - 2) ops[c] = k_op(slot(sub + 2), c);
 #pragma unroll
                 for (int e = 0; e < PER; ++e) {
@@ -721,6 +644,7 @@ prefill_chunk_kernel(const PrefillArgs a)
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            lacc = FP8 ? lacc + sum * norm : sum;
             if (sub < kOwn) produce(si, sub);
             if (sub < GPS - 1 || more) raise(top(bm));
             z = zn;
@@ -731,14 +655,12 @@ prefill_chunk_kernel(const PrefillArgs a)
     // in one: the pipeline leaves no registers for what the two forms would share.  Waves may change
     // over at different stages; each passes one barrier per stage.)
     int si = s_lo;
-    if constexpr (WIDE) {
-        const int whole = min(active ? min(g_end, full_limit / (2 * kBlock)) / GPS : 0, s_hi);
-        if (si < whole) {
-            pipeline_start();
-            for (; si < whole; ++si) {
-                pipeline_stage(si, si + 1 < whole);
-                next_stage();
-            }
+    const int whole_stages = min(active ? min(g_end, full_limit / (2 * kBlock)) / GPS : 0, s_hi);
+    if (si < whole_stages) {
+        pipeline_start();
+        for (; si < whole_stages; ++si) {
+            pipeline_stage(si, si + 1 < whole_stages);
+            next_stage();
         }
     }
     for (; si < s_hi; ++si) {
@@ -752,34 +674,32 @@ prefill_chunk_kernel(const PrefillArgs a)
     }
 
     if (!active) return;
-    // the sums of the lane's column: rows 0 and 1 of lacc (wide: rows 2 and 3 for columns 16..31)
+    // the sums of the lane's column: rows 0 and 1 of lacc, rows 2 and 3 for columns 16..31
     const float sum_a = __shfl(lacc[0] + lacc[1], n), sum_b = __shfl(lacc[2] + lacc[3], n);
-    const float L = (WIDE && (grp & 1) ? sum_b : sum_a) * 256.0f;
+    const float L = (second ? sum_b : sum_a) * 256.0f;
     // The rows leave through LDS, so that a store instruction writes whole rows: a lane's registers are
-    // 4 dims of 8 each (register 4j + i of acc[c]: dim NCOL c + 8j + 4h + i; one column tile: 16c + 4 grp + i),
+    // 4 dims of 8 each (register 4j + i of acc[c]: dim 32c + 8j + 4h + i),
     // 16 bytes of 32 rows an instruction.  Every wave has a slot of its own: of the last stage only its
     // last group can still be read by others, and that is the ring's ninth.
-    constexpr int NJ = WIDE ? 4 : 1;
-    const int dim0 = 4 * (WIDE ? grp >> 1 : grp);
-    const int col = WIDE ? lane & 31 : n;
+    const int col = lane & 31;
     unsigned char* mine = slot(wave_id);
     static_assert(2 * GPS >= kPrefillWaves && 32 * (4 * HEAD_DIM + 16) <= St::kBytes, "a wave's rows fit its slot");
-    // (the 2^kPShift common to acc and l cancels; the normaliser of the v_scales is in acc alone)
+    // (the 2^kPShift common to acc and l cancels)
     if (parts > 1) {
         // this run's share of the tiles: reference, row sum and unnormalised sums per column
         constexpr int kRow = 4 * HEAD_DIM + 16;
 #pragma unroll
-        for (int c = 0; c < HEAD_DIM / NCOL; ++c)
+        for (int c = 0; c < HEAD_DIM / 32; ++c)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                *reinterpret_cast<floatx4*>(mine + col * kRow + 4 * (NCOL * c + 8 * j + dim0)) =
-                    floatx4{acc[c][4 * j], acc[c][4 * j + 1], acc[c][4 * j + 2], acc[c][4 * j + 3]} * vdenorm;
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<floatx4*>(mine + col * kRow + 4 * (32 * c + 8 * j + 4 * h)) =
+                    floatx4{acc[c][4 * j], acc[c][4 * j + 1], acc[c][4 * j + 2], acc[c][4 * j + 3]};
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             if (first + r >= count) break;
             float* dst = a.part + (((size_t)pair * a.tail_cap + head_of[r] * tiles_per_head + row0_of[r] / 16 - share.base) * parts + part) * (16 * (HEAD_DIM + 2));
-            if (dim0 == 0 && col >> 4 == r) {
+            if (h == 0 && col >> 4 == r) {
                 dst[n] = m;
                 dst[16 + n] = L;
             }
@@ -791,15 +711,15 @@ prefill_chunk_kernel(const PrefillArgs a)
         return;
     }
     constexpr int kRow = 2 * HEAD_DIM + 16;
-    const float inv = (1.0f / L) * vdenorm;
+    const float inv = 1.0f / L;
 #pragma unroll
-    for (int c = 0; c < HEAD_DIM / NCOL; ++c)
+    for (int c = 0; c < HEAD_DIM / 32; ++c)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
+        for (int j = 0; j < 4; ++j) {
             half4_t o;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = (half_t)(acc[c][4 * j + i] * inv);
-            *reinterpret_cast<half4_t*>(mine + col * kRow + 2 * (NCOL * c + 8 * j + dim0)) = o;
+            *reinterpret_cast<half4_t*>(mine + col * kRow + 2 * (32 * c + 8 * j + 4 * h)) = o;
         }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
@@ -839,6 +759,8 @@ prefill_split_merge_kernel(const PrefillArgs a)
     const int seq = pair / a.H_k;
     const int g = pair - seq * a.H_k;
     const int parts = a.split;
+    // (a branch of its own, taken where it can decide something: behind it the loads are one round trip)
+    if (a.whole_tokens > 0 && prefill_runs_whole(a, a.context_lens[seq])) return;
     // every load but the two row offsets' own lies inside the workspace whatever those say
     const float* p0 = a.part + (size_t)id * parts * kPart;
     float m[kPrefillMaxParts], l[kPrefillMaxParts];
@@ -940,6 +862,7 @@ static void launch_split_merge(PrefillArgs a, int num_seqs, hipStream_t stream)
         hipLaunchKernelGGL((prefill_split_merge_kernel<HEAD_DIM>), dim3((unsigned)(n * seq_wgs)), dim3(256), 0,
                            stream, a);
         a.query_start += n;
+        a.context_lens += n;
         a.part += (size_t)n * a.H_k * a.tail_cap * a.split * (16 * (HEAD_DIM + 2));
     }
 }
@@ -974,10 +897,11 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
 
     const PrefillLaunchPlan lp(sh, max_chunk_len, workspace != nullptr);
     const int pairs8 = lp.pairs8, a_per_pair = lp.a_per_pair, b_per_pair = lp.b_per_pair;
-    const bool split = lp.parts >= 2;
+    const bool split = lp.parts >= 2;                 // (and no merge if the table holds no sequence long enough)
     const int split_per_pair = lp.split_per_pair();
     a.set(lp, sh->num_seqs * sh->num_kv_heads);
     a.part = (float*)workspace;
+    const bool merge = split && a.whole_tokens < (long long)sh->max_blocks_per_seq * kBlock;
     // Turn by turn, so that the longest streams of all pairs start first and the launch ends evenly,
     // while the streams of all of an XCD's pairs can share its 4 MB L2; else pair after pair, whose
     // workgroups then read their stream together.  (8 pairs of 2.3 MB an XCD: 760 us a pass by
@@ -987,29 +911,40 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
     const long long token_bytes = (sh->kv_dtype == COOPT_KV_FP16 ? 4LL : 2LL) * sh->head_dim +
                                   (sh->kv_dtype == COOPT_KV_FP16 ? 0 : 8);
     a.by_pair = a.xcd_pairs * (long long)sh->max_blocks_per_seq * kBlock * token_bytes > kPrefillXcdL2;
-    if ((long long)pairs8 * (a_per_pair + b_per_pair + split_per_pair) > 0x7fffffffLL) return COOPT_ERR_SHAPE;
+    // Ragged batches in the order of their streams' lengths, over up to 64 pairs an XCD (one a lane).  A
+    // workgroup goes to the XCD's four shader engines in turn whether they have room or not, so a long
+    // stream behind a short one, or a workgroup without tiles, holds up all that come after it.  Finding
+    // one's rank takes a workgroup 1.2-2 us, so only where many workgroups follow each other on a CU and
+    // rows are missing: 16 prompts of 100 to 800 rows (8 a CU, 56 % of the rows) 139 -> 120 us, 6 of 200 to
+    // 1500 (d = 64, 4.7 a CU) 95 -> 89; 3 of 301 to 1777 (3.6 a CU) 90 -> 93, 8 of 352 rows each 80 -> 88.
+    const long long wgs = (long long)pairs8 * (a_per_pair + b_per_pair + split_per_pair);
+    if (!a.by_pair && a.xcd_pairs <= 64 && wgs >= 4 * kPrefillCUs &&
+        4LL * num_query_rows <= 3LL * sh->num_seqs * max_chunk_len)
+        while ((1LL << a.rank_bits) <= ((long long)sh->max_blocks_per_seq * kBlock + kPrefillStageTokens - 1) / kPrefillStageTokens)
+            ++a.rank_bits;
+    if (wgs > 0x7fffffffLL) return COOPT_ERR_SHAPE;
     const dim3 block(64 * kPrefillWaves);
     const size_t lds = kPrefillSlots *
                        (size_t)(sh->head_dim == 128 ? PrefillStage<128>::kBytes : PrefillStage<64>::kBytes);
     hipStream_t stream = (hipStream_t)hip_stream;
     const bool big = !pool_fits_small(sh);
-#define COOPT_PREFILL_FULL(D, KV, BIG, NR)                                                          \
+#define COOPT_PREFILL_FULL(D, KV, BIG, TILES)                                                          \
     do {                                                                                            \
-        hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, NR, BIG>),                                  \
+        hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, TILES, BIG>),                                  \
                            dim3((unsigned)((long long)pairs8 * (a_per_pair + split_per_pair))), block, lds, \
                            stream, a);                                                              \
-        if (split)                                                                                  \
+        if (merge)                                                                                  \
             launch_split_merge<D>(a, sh->num_seqs, stream);                                         \
     } while (0)
 #define COOPT_PREFILL(D, KV, BIG)                                                                   \
     do {                                                                                            \
         if (lp.nr == 1) {                                                                           \
-            COOPT_PREFILL_FULL(D, KV, BIG, 1);                                                      \
+            COOPT_PREFILL_FULL(D, KV, BIG, 8);                                                      \
         } else {                                                                                    \
-            COOPT_PREFILL_FULL(D, KV, BIG, 2);                                                      \
+            COOPT_PREFILL_FULL(D, KV, BIG, 16);                                                      \
             if (!split && b_per_pair) {                                                             \
                 a.set_rest(lp);                                                                     \
-                hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, 1, BIG>),                           \
+                hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, 8, BIG>),                           \
                                    dim3((unsigned)((long long)pairs8 * b_per_pair)), block, lds, stream, a); \
             }                                                                                       \
         }                                                                                           \

@@ -13,6 +13,7 @@ namespace coopt {
 
 constexpr int kPrefillWaves = 8;                // two teams of four producer roles
 constexpr int kPrefillMaxParts = 8;             // runs a split launch cuts a stream into, at most
+constexpr int kPrefillStageTokens = 128;        // between two barriers of the stream
 constexpr int kPrefillCUs = 256;                // MI355X: the launch shape is planned for its CU count
 
 // A divisor that the host knows: a quotient of wave-uniform values is then a product on the scalar unit
@@ -46,25 +47,25 @@ __device__ __forceinline__ int quotient(int x, int y)
 // How the tiles of every pair are dealt to launches.  One workgroup (8 waves, 2 tiles each) fills
 // a CU, so a launch runs in rounds of one workgroup per CU, and a last round that is mostly empty
 // costs a full one.  Where that happens the last tiles of every pair go to a launch of half-size
-// workgroups behind it (one tile per wave), which takes about 0.65-0.8 of a round -- or, when the
+// workgroups behind it (8 tiles), which takes about 0.65-0.8 of a round -- or, when the
 // caller brings a workspace, to full-size workgroups of the same launch, `parts` per 16 tiles, that
 // each stream one of `parts` equal runs of the pair's stages, with `parts` (2 to 8) chosen so that
 // the round is as short as it gets (a launch of fewer workgroups than CUs is all "last round": a
 // single sequence's chunk is spread over the chip this way); the parts are combined by
-// prefill_split_merge_kernel.  (The rounds are counted as if all streams were equally long, which
-// short prompts' are not: 8 fresh prompts of 352 rows take 79 us split and 41 whole.)
+// prefill_split_merge_kernel.  (The rounds are counted as if a workgroup cost nothing but its stream,
+// which is not so for short ones: the device, which sees the lengths, has those run whole after all,
+// prefill_runs_whole.)
 struct PrefillLaunchPlan {
     int tiles, pairs8, a_per_pair, b_per_pair, rest, parts;
-    int nr;          // tiles per wave of the full-size workgroups: 2, or 1 where a pair has at most 8 tiles
+    int nr;          // tiles per 64 lanes of the full-size workgroups: 2, or 1 where a pair has at most 8 tiles
     int wg_tiles;    // = 8 nr
     PrefillLaunchPlan(const coopt_shape* sh, int max_chunk_len, bool with_workspace)
     {
         const int G = sh->num_q_heads / sh->num_kv_heads;
         tiles = G * ((max_chunk_len + 15) / 16);
         pairs8 = (sh->num_seqs * sh->num_kv_heads + 7) / 8 * 8;
-        // (a short chunk -- 16 rows of a five-head group, say -- gives every wave one tile at
-        // most: the one-tile kernel then does the same work with fewer registers and 0.78 of the
-        // round time)
+        // (a short chunk -- 16 rows of a five-head group, say -- fills half the waves at most: the kernel
+        // of 8 tiles then has the other half bring the stream, 0.85 of the time)
         nr = tiles <= kPrefillWaves ? 1 : 2;
         wg_tiles = nr * kPrefillWaves;
         const int full_per_pair = (tiles + wg_tiles - 1) / wg_tiles;
@@ -105,9 +106,9 @@ struct PrefillLaunchPlan {
                 return;
             }
         }
-        // What a workspace would split runs whole, but behind the same cut: which rows share a
-        // workgroup decides the normaliser of their v_scales, and the tiles in front of the cut are
-        // to have the same bits with and without a workspace.
+        // What a workspace would split runs whole, but behind the same cut: which rows share a wavefront
+        // decides when their references are raised, and the tiles in front of the cut are to have the
+        // same bits with and without a workspace.
         if (best >= 2) {
             a_per_pair = cand;
             rest = r;
@@ -138,6 +139,7 @@ struct PrefillDeal {
     int32_t split;            // parts (0: no such workgroups; 1: whole streams, rows written to out)
     int32_t split_blocks;     // runs of 16 tiles per pair they cover
     int32_t tail_cap;         // tiles per pair they cover (sizes the workspace)
+    int32_t whole_tokens;     // sequences up to this length have their split streams run whole after all
     Divisor pairs_of_xcd, whole_of_pair, split_of_pair, split_parts;     // (at least 1 each)
 
     // The first launch of a plan (its only one but for a plan's half-size workgroups).
@@ -151,6 +153,19 @@ struct PrefillDeal {
         split = lp.parts;
         split_blocks = lp.parts > 0 ? lp.split_per_pair() / lp.parts : 0;
         tail_cap = lp.parts > 0 ? lp.rest : 0;
+        // A workgroup costs its n stages and the time of 2.3 on top: its start, its rows, the change to the
+        // CU's next (9 us; a stage takes 4).  In R rounds of whole streams, or S rounds of p parts, whole
+        // ones are the faster where R (2.3 + n) <= S (2.3 + n / p): 8 fresh prompts of 352 rows, 3 rounds of
+        // quarters of 3 stages, take 79 us split and 64 whole, 3 x 777 rows behind 500 tokens, 3 rounds
+        // of fifths of 10 stages, 117 and 104.
+        whole_tokens = 0;
+        if (split > 1) {
+            const long long last = (long long)lp.pairs8 * split_blocks;
+            const double R = (double)((last + kPrefillCUs - 1) / kPrefillCUs);
+            const double S = (double)((last * split + kPrefillCUs - 1) / kPrefillCUs);
+            const double stages = R * split > S ? 2.3 * (S - R) / (R - S / split) : 1e6;
+            whole_tokens = kPrefillStageTokens * (int)(stages < 1e6 ? stages : 1e6);
+        }
         set_divisors();
     }
     // ... and the one of half-size workgroups behind it: the tiles that it left.
@@ -193,6 +208,22 @@ __device__ __forceinline__ int prefill_pair(const PrefillDeal& a, unsigned wg, i
     return xcd_pair * 8 + (wg & 7);
 }
 
+// Whether a sequence of t tokens has its split streams run whole (by the workgroup of their first part;
+// the others have nothing to do, nor has the merge).
+__device__ __forceinline__ bool prefill_runs_whole(const PrefillDeal& a, int t) { return t <= a.whole_tokens; }
+
+// How many whole-stream workgroups of a pair start before those behind the cut: all of them where these are
+// runs of about t / split tokens and the history is longer than that, none where they are whole streams;
+// and those of longer streams in front of the first rows of a fresh prompt.  (In binary32, the same for
+// every workgroup of the pair: it only places them.)
+__device__ __forceinline__ int prefill_ahead(const PrefillDeal& a, int t, int C)
+{
+    if (a.split * a.split_blocks == 0 || a.by_pair) return a.blocks_per_pair;
+    const int tokens = prefill_runs_whole(a, t) ? t : a.split_parts.quotient(t);
+    const int shorter = (int)((float)(tokens - (t - C)) * (float)a.blocks_per_pair / (float)C);
+    return a.blocks_per_pair - min(max(shorter, 0), a.blocks_per_pair);
+}
+
 // A workgroup's tiles: positions block * WG .. of the range [base, end) in TileOrder, as one of `parts`
 // runs of their stream.
 struct PrefillShare {
@@ -201,19 +232,12 @@ struct PrefillShare {
 };
 
 // The pair's workgroups by the length of their streams: whole streams from the last rows down, and the
-// split ones (about t / split tokens each) where that length has its place -- behind all whole ones once
-// the history is longer than that, in front of the first rows of a fresh prompt.  t: the sequence's
-// tokens, C of them new rows, total_tiles tiles.  C comes from the device and may be more than the
+// split ones where their length has its place (prefill_ahead).  t: the sequence's tokens, C of them new rows, total_tiles tiles.  C comes from the device and may be more than the
 // host was told: tiles beyond those that the launch and its workspace were sized for are left out.
 __device__ __forceinline__ PrefillShare prefill_share(const PrefillDeal& a, int turn, int t, int C, int total_tiles)
 {
     const int num_split = a.split * a.split_blocks;
-    int ahead = a.blocks_per_pair;                     // whole-stream workgroups before the split ones
-    if (num_split > 0 && !a.by_pair) {
-        // (in binary32, the same for every workgroup of the pair: it only places them)
-        const int shorter = wave_uniform((int)((float)(a.split_parts.quotient(t) - (t - C)) * (float)a.blocks_per_pair / (float)C));
-        ahead -= min(max(shorter, 0), a.blocks_per_pair);
-    }
+    const int ahead = wave_uniform(prefill_ahead(a, t, C));
     PrefillShare s;
     s.tail = turn >= ahead && turn < ahead + num_split;
     const int nth = s.tail ? turn - ahead : (turn < ahead ? turn : turn - num_split);
@@ -234,11 +258,21 @@ struct TileOrder {
     int T, base, end, hb, ib, he, ie;
     __device__ __forceinline__ TileOrder(int tiles_per_head, int b, int e) : T(tiles_per_head), base(b), end(e)
     {
-        // (wave_uniform: the quotients are made on the vector ALU; this keeps them out of its registers)
-        hb = wave_uniform(quotient(b, T));
+        hb = quotient(b, T);
         ib = b - hb * T;
-        he = wave_uniform(quotient(e, T));
+        he = quotient(e, T);
         ie = e - he * T;
+    }
+    // (where both ends are known as head and row already)
+    __device__ __forceinline__ TileOrder(int tiles_per_head, int b, int b_head, int e, int e_head)
+        : T(tiles_per_head), base(b), end(e), hb(b_head), ib(b - b_head * T), he(e_head), ie(e - e_head * T) {}
+    // (quotients are made on the vector ALU; where they are the same in every lane this takes them off it)
+    __device__ __forceinline__ void to_scalar()
+    {
+        hb = wave_uniform(hb);
+        ib = wave_uniform(ib);
+        he = wave_uniform(he);
+        ie = wave_uniform(ie);
     }
     __device__ __forceinline__ int count() const { return end - base; }
     // Position p (0 .. count-1) -> first row / 16 and head.  Row i has he - hb tiles of this range,
@@ -251,8 +285,82 @@ struct TileOrder {
         // (one division whatever the lane's third of the rows; max: a divisor even where nothing divides)
         const bool mid = p >= n1 && p < n2;
         i = (p < n1 ? 0 : mid ? b1 : b2) + quotient(p - (p < n1 ? 0 : mid ? n1 : n2), max(mid ? c2 : N, 1));
-        h = p - (i * N + min(i, ie) - min(i, ib)) + hb + (i < ib ? 1 : 0);
+        h = p - below(i) + hb + (i < ib ? 1 : 0);
+    }
+    // Tiles of the range in the rows in front of row i.
+    __device__ __forceinline__ int below(int i) const { return i * (he - hb) + min(i, ie) - min(i, ib); }
+};
+
+// What a pair gives a launch to do, for an order of the workgroups over several pairs (whose sequences
+// differ in length): its workgroups that have tiles at all, whole-stream ones and those behind the cut,
+// each kind longest stream first.
+struct PairItems {
+    int whole, split, step;    // of either kind; turns from one of the latter to the next
+    int ahead, num_split, empty_whole, t, t_ctx, rows, tail_tokens, wg_tiles;
+    bool runs;                 // behind the cut: runs of a stream, all about tail_tokens long (else whole streams)
+    TileOrder order, tail;
+    __device__ __forceinline__ PairItems(const PrefillDeal& a, int tokens, int C, int G, int wg_tiles_)
+        : whole(0), split(0), step(1), ahead(0), num_split(a.split * a.split_blocks), empty_whole(0), t(tokens), t_ctx(tokens - C),
+          rows((max(C, 1) + 15) / 16), tail_tokens(0), wg_tiles(wg_tiles_), runs(a.split > 1 && !prefill_runs_whole(a, tokens)),
+          order(range(a.tile_base, min(G * rows, a.tile_limit), G)),
+          tail(range(a.tile_limit, G * rows, G))
+    {
+        // (a sequence longer than announced: tiles that nobody takes)
+        if (a.tail_cap < tail.count()) tail = TileOrder(rows, tail.base, tail.base + a.tail_cap);
+        if (C <= 0) return;
+        whole = min(blocks(order.count()), a.blocks_per_pair);
+        split = (runs ? a.split : 1) * blocks(tail.count());
+        step = runs ? 1 : a.split;
+        ahead = prefill_ahead(a, t, C);
+        empty_whole = a.blocks_per_pair - whole;
+        tail_tokens = a.split_parts.quotient(t);
+    }
+    // Tiles [b, e) of G heads, none if e <= b.  (Most ends are the last head's: no quotient.)
+    __device__ __forceinline__ TileOrder range(int b, int e, int G) const
+    {
+        if (e <= b) return TileOrder(rows, 0, 0, 0, 0);
+        const int b_head = b == 0 ? 0 : quotient(b, rows);
+        return TileOrder(rows, b, b_head, e, e == G * rows ? G : quotient(e, rows));
+    }
+    __device__ __forceinline__ int blocks(int tiles) const { return wg_tiles == 16 ? (tiles + 15) >> 4 : (tiles + 7) >> 3; }
+    // Of `have` workgroups over a range those whose stream is longer than `tokens`.
+    __device__ __forceinline__ int longer(const TileOrder& o, int have, int tokens) const
+    {
+        const int row = max(tokens - t_ctx, 0) >> 4;                         // tiles from this row on
+        const int pos = row < rows && tokens < t ? o.below(row) : o.count();
+        return pos < o.count() ? max(have - (wg_tiles == 16 ? pos >> 4 : pos >> 3), 0) : 0;
+    }
+    // Those of at least so many stages, as far as it decides an order: all at 1, never more with more stages.
+    __device__ __forceinline__ int whole_at_least(int stages) const
+    {
+        return stages <= 1 ? whole : longer(order, whole, (stages - 1) * kPrefillStageTokens);
+    }
+    __device__ __forceinline__ int split_at_least(int stages) const
+    {
+        if (stages <= 1 || split == 0) return split;
+        const int tokens = (stages - 1) * kPrefillStageTokens;
+        return !runs ? longer(tail, split, tokens) : tail_tokens >= tokens ? split : 0;
+    }
+    __device__ __forceinline__ int at_least(int stages) const { return whole_at_least(stages) + split_at_least(stages); }
+    // The turn (prefill_share) of the k-th item of exactly so many stages.
+    __device__ __forceinline__ int turn(int stages, int k) const
+    {
+        const int w = whole_at_least(stages + 1), of_whole = whole_at_least(stages) - w;
+        if (k >= of_whole) return ahead + num_split - (split - split_at_least(stages + 1) - k + of_whole) * step;
+        const int nth = empty_whole + w + k;
+        return nth < ahead ? nth : nth + num_split;
     }
 };
+
+// The most stages that more than `rank` items have, 0 if there are not so many items: the length of the
+// item at that rank.  total(stages): PairItems::at_least over the pairs; lengths are below 2^bits.
+template <class Total>
+__device__ __forceinline__ int stages_of_rank(int rank, int bits, Total total)
+{
+    int stages = 0;
+    for (int bit = 1 << (bits - 1); bit > 0; bit >>= 1)
+        if (total(stages + bit) > rank) stages += bit;
+    return stages;
+}
 
 }  // namespace coopt
