@@ -96,13 +96,12 @@ struct PrefillStage {
 };
 
 // The weights enter the second product rounded to fp16, w~ = fp16(P * v_scale): one token's weight
-// is then off by up to 2^-10 relative, which shows in the output when that token carries the row
-// (an fp16 output near |x| = 3 moves by 1.5e-3).  So the row sum is taken from the SAME rounded
+// is then off by up to 2^-11 relative, which shows in the output when that token carries the row
+// (an fp16 output near |x| = 3 moves by 0.7e-3).  So the row sum is taken from the SAME rounded
 // weights, l = sum_j w~_j / v_scale_j: numerator and denominator then describe one softmax with
-// weights perturbed by at most 2^-10 relative, whose result differs from the exact one by at most
+// weights perturbed by at most 2^-11 relative, whose result differs from the exact one by at most
 // that times the weighted mean deviation of the value rows from the result -- nothing for one
-// token or a dominant one.  (For the same reason the convert may truncate: a common bias of the
-// weights cancels.)  The sum runs on the matrix cores: `rop` is a 16-row operand whose row 0
+// token or a dominant one.  The sum runs on the matrix cores: `rop` is a 16-row operand whose row 0
 // holds 2^-8 / v_scale of the group's 32 tokens, times a power of two that the sum is freed of again, cut
 // to fp16 and row 1 the remainder (the producers write it), so one more 16x16x32 product per tile accumulates it in rows 0 and 1 of `lacc`,
 // which replaces eight vector additions.
@@ -134,17 +133,17 @@ __device__ __forceinline__ float wide_logits(floatx16& z, int j, floatx4 ksc, fl
     return fmaxf(fmaxf(z[4 * j], z[4 * j + 1]), fmaxf(z[4 * j + 2], z[4 * j + 3]));
 }
 
-// Two weights, registers k and k + 1 of z, as fp16 (cut: a common bias cancels, see above).
+// Two weights, registers k and k + 1 of z, rounded to fp16 (one instruction, as cutting them is: errors
+// against 64 bits of 2.5e-4 to 2.9e-4 of the norm instead of 2.9e-4 to 3.2e-4).
 __device__ __forceinline__ half2_t wide_weights(const floatx16& z, int k, float mm)
 {
-    return __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(__builtin_amdgcn_exp2f(z[k] - mm),
-                                                                  __builtin_amdgcn_exp2f(z[k + 1] - mm)));
+    return half2_t{(half_t)__builtin_amdgcn_exp2f(z[k] - mm), (half_t)__builtin_amdgcn_exp2f(z[k + 1] - mm)};
 }
 // The same from scores that are not scaled yet (an fp16 cache: one factor for all tokens).
 __device__ __forceinline__ half2_t wide_weights(const floatx16& s, int k, float scale, float mm)
 {
-    return __builtin_bit_cast(half2_t, __builtin_amdgcn_cvt_pkrtz(__builtin_amdgcn_exp2f(__builtin_fmaf(s[k], scale, -mm)),
-                                                                  __builtin_amdgcn_exp2f(__builtin_fmaf(s[k + 1], scale, -mm))));
+    return half2_t{(half_t)__builtin_amdgcn_exp2f(__builtin_fmaf(s[k], scale, -mm)),
+                   (half_t)__builtin_amdgcn_exp2f(__builtin_fmaf(s[k + 1], scale, -mm))};
 }
 
 // TILES: of a workgroup, 16 or, where a pair has no more, 8 (whose first four waves alone consume).
