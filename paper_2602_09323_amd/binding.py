@@ -135,10 +135,46 @@ def _call(name: str, *args) -> None:
 
 # ---------------------------------------------------------------- argument checks (host, no launch)
 
-# A decode step of a short batch takes the GPU some 13 us, and its dozen tensors are checked on the
-# way: the checks below read each attribute once, build no message until one is refused and hand
-# plain integers to ctypes, so that the host stays ahead of the GPU (one such step, single sequence:
-# 20.6 us a step before, 14.0 us now).
+# A decode step of a short batch takes the GPU some 10 us, and its dozen tensors are checked on the
+# way.  The entry points of a serving loop go through csrc/binding_native.cpp, which makes the same
+# checks and enters the library in native code (a fused step of one short sequence 14.2 us before, 10.1
+# so, of which the library's two launches are 7.4); whatever it does not take as it is -- anything
+# wrong above all -- comes back here, where the checks below say what it is.
+
+_native = None
+
+
+def _fast():
+    """The native entry points once the library is loaded, None until then or where they are not built."""
+    global _native
+    if _native is None and isinstance(_lib, ctypes.CDLL):
+        _native = _bind_native() or False
+    return _native or None
+
+
+def _bind_native():
+    import importlib.util
+    if importlib.util.find_spec("._binding", __package__) is None:
+        return None
+    c = _th()._C
+    device, raw = getattr(c, "_cuda_getDevice", None), getattr(c, "_cuda_getCurrentRawStream", None)
+    if device is None or raw is None:
+        return None
+    from . import _binding
+    names = ("kv_cache_write_fp8", "kv_cache_write_fp16", "paged_gqa_decode", "paged_gqa_decode_step",
+             "decode_schedule_prepare", "paged_gqa_decode_scheduled", "paged_gqa_decode_partitioned",
+             "paged_gqa_reduce", "paged_gqa_prefill_chunk_ws", "gather_cached_kv", "decode_workspace_bytes",
+             "decode_schedule_bytes", "prefill_workspace_bytes")
+    _binding.bind(tuple(ctypes.cast(getattr(_lib, "coopt_" + n), ctypes.c_void_p).value for n in names),
+                  Shape, DecodePlan, device, raw)
+    return _binding
+
+
+def _entered(status: Optional[int], name: str) -> bool:
+    """Whether a native entry point took the call (None: it did not); raises if the library refused."""
+    if status:
+        _check(status, name)
+    return status is not None
 
 def _nbytes(t) -> int:
     return t.numel() * t.element_size()
@@ -261,6 +297,9 @@ def make_decode_plan(**fields) -> DecodePlan:
 
 def kv_cache_write_fp8(k, v, slot_mapping, k_cache, v_cache, k_scale, v_scale, shape: Shape,
                        stream=None) -> None:
+    fast = _fast()
+    if fast is not None and _entered(fast.write_fp8(k, v, slot_mapping, k_cache, v_cache, k_scale, v_scale, shape, stream), "coopt_kv_cache_write_fp8"):
+        return
     z = _sizes(shape)
     pk, pv, ps, T = _new_rows(k, v, slot_mapping, z, "kv_cache_write_fp8")
     _call("coopt_kv_cache_write_fp8",
@@ -295,6 +334,9 @@ def kv_cache_write_skipset(k, v, slot_mapping, skip_set, k_cache, v_cache, k_sca
 
 
 def kv_cache_write_fp16(k, v, slot_mapping, k_cache, v_cache, shape: Shape, stream=None) -> None:
+    fast = _fast()
+    if fast is not None and _entered(fast.write_fp16(k, v, slot_mapping, k_cache, v_cache, shape, stream), "coopt_kv_cache_write_fp16"):
+        return
     z = _sizes(shape)
     pk, pv, ps, T = _new_rows(k, v, slot_mapping, z, "kv_cache_write_fp16")
     pkc, pvc, _, _ = _cache_ptrs(k_cache, v_cache, None, None, z)
@@ -324,6 +366,9 @@ def _workspace(workspace, shape: Shape, plan, what: str, optional: bool = False)
 
 def paged_gqa_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out,
                      workspace, shape: Shape, plan: Optional[DecodePlan] = None, stream=None) -> None:
+    fast = _fast()
+    if fast is not None and _entered(fast.decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, workspace, shape, plan, stream), "coopt_paged_gqa_decode"):
+        return
     what = "paged_gqa_decode"
     z = _sizes(shape)
     ins = _decode_inputs(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, z, what)
@@ -351,6 +396,10 @@ def paged_gqa_decode_noalloc(q, k_cache, v_cache, k_scale, v_scale, block_tables
 def paged_gqa_decode_step(k, v, slot_mapping, q, k_cache, v_cache, k_scale, v_scale, block_tables,
                           context_lens, out, workspace, shape: Shape,
                           plan: Optional[DecodePlan] = None, stream=None) -> None:
+    fast = _fast()
+    if fast is not None and _entered(fast.step(k, v, slot_mapping, q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, workspace,
+                                              shape, plan, stream), "coopt_paged_gqa_decode_step"):
+        return
     what = "paged_gqa_decode_step"
     z = _sizes(shape)
     pk, pv, ps, T = _new_rows(k, v, slot_mapping, z, what)
@@ -396,6 +445,10 @@ def paged_gqa_decode_partitioned(q, k_cache, v_cache, k_scale, v_scale, block_ta
                                  context_lens, partition_size: int, tmp_out, max_logits, exp_sums,
                                  max_parts: int, shape: Shape, plan: Optional[DecodePlan] = None,
                                  stream=None) -> None:
+    fast = _fast()
+    if fast is not None and _entered(fast.partitioned(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, partition_size,
+                                                     tmp_out, max_logits, exp_sums, max_parts, shape, plan, stream), "coopt_paged_gqa_decode_partitioned"):
+        return
     what = "paged_gqa_decode_partitioned"
     z = _sizes(shape)
     ins = _decode_inputs(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, z, what)
@@ -406,6 +459,10 @@ def paged_gqa_decode_partitioned(q, k_cache, v_cache, k_scale, v_scale, block_ta
 
 def paged_gqa_reduce(tmp_out, max_logits, exp_sums, context_lens, partition_size: int,
                      max_parts: int, out, shape: Shape, stream=None) -> None:
+    fast = _fast()
+    if fast is not None and _entered(fast.reduce(tmp_out, max_logits, exp_sums, context_lens, partition_size, max_parts, out,
+                                                shape, stream), "coopt_paged_gqa_reduce"):
+        return
     what = "paged_gqa_reduce"
     z = _sizes(shape)
     _call("coopt_paged_gqa_reduce",
@@ -440,6 +497,10 @@ def paged_gqa_prefill_chunk_ws(q, k_cache, v_cache, k_scale, v_scale, block_tabl
                                shape: Shape, stream=None) -> None:
     """workspace: a device buffer of at least prefill_workspace_bytes(shape, max_chunk_len) bytes
     (None where that is 0)."""
+    fast = _fast()
+    if fast is not None and _entered(fast.prefill_ws(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, query_start,
+                                                    num_query_rows, max_chunk_len, out, workspace, shape, stream), "coopt_paged_gqa_prefill_chunk_ws"):
+        return
     what = "paged_gqa_prefill_chunk_ws"
     z = _sizes(shape)
     rows_bytes = int(num_query_rows) * shape.num_q_heads * shape.head_dim * 2
@@ -464,6 +525,9 @@ def decode_schedule_bytes(shape: Shape, plan: Optional[DecodePlan] = None) -> in
 def decode_schedule_prepare(block_tables, context_lens, slot_mapping, schedule, shape: Shape,
                             plan: Optional[DecodePlan] = None, stream=None) -> None:
     """Write the decode schedule (``slot_mapping`` None: plain decode; else the fused step)."""
+    fast = _fast()
+    if fast is not None and _entered(fast.prepare(block_tables, context_lens, slot_mapping, schedule, shape, plan, stream), "coopt_decode_schedule_prepare"):
+        return
     what = "decode_schedule_prepare"
     z = _sizes(shape)
     _call("coopt_decode_schedule_prepare",
@@ -479,6 +543,10 @@ def paged_gqa_decode_scheduled(k, v, slot_mapping, q, k_cache, v_cache, k_scale,
                                plan: Optional[DecodePlan] = None, stream=None) -> None:
     """Decode (k, v, slot_mapping None) or fused step from a prepared schedule; ``out`` None stops
     after the partial results."""
+    fast = _fast()
+    if fast is not None and _entered(fast.scheduled(k, v, slot_mapping, q, k_cache, v_cache, k_scale, v_scale, context_lens, out,
+                                                   workspace, schedule, shape, plan, stream), "coopt_paged_gqa_decode_scheduled"):
+        return
     what = "paged_gqa_decode_scheduled"
     z = _sizes(shape)
     if k is None and v is None and slot_mapping is None:
@@ -499,6 +567,10 @@ def paged_gqa_decode_scheduled(k, v, slot_mapping, q, k_cache, v_cache, k_scale,
 
 def gather_cached_kv(k_cache, v_cache, k_scale, v_scale, block_tables, seq: int, tok_begin: int,
                      tok_end: int, k_out, v_out, shape: Shape, stream=None) -> None:
+    fast = _fast()
+    if fast is not None and _entered(fast.gather(k_cache, v_cache, k_scale, v_scale, block_tables, seq, tok_begin, tok_end, k_out, v_out, shape,
+                                                stream), "coopt_gather_cached_kv"):
+        return
     what = "gather_cached_kv"
     z = _sizes(shape)
     rows = max(int(tok_end) - int(tok_begin), 0) * z["row"]

@@ -1,4 +1,5 @@
-"""Builds libcoopt_attn.so and the benchmark's libcoopt_probe.so (HIP, gfx950 only) in-tree with hipcc.
+"""Builds libcoopt_attn.so and the benchmark's libcoopt_probe.so (HIP, gfx950 only) in-tree with hipcc,
+and the Python binding's native part with g++.
 
     python -m paper_2602_09323_amd.build [--force]
 
@@ -11,6 +12,7 @@ import concurrent.futures
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -20,6 +22,8 @@ LIB = os.path.join(HERE, "libcoopt_attn.so")
 PROBE_LIB = os.path.join(HERE, "libcoopt_probe.so")      # measurement aid, not the product
 SOURCES = ["kv_write.hip", "decode.hip", "decode_flat.hip", "prefill.hip", "gather.hip"]
 PROBE_SOURCES = ["probe.hip"]
+BINDING = os.path.join(HERE, "_binding" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+BINDING_SOURCE = "binding_native.cpp"                    # host code: tensors to pointers, no kernel
 HEADERS = [os.path.join(CSRC, h) for h in ("common.hpp", "attn_tile.hpp", "kv_quant.hpp",
                                           "decode_internal.hpp", "launch_grid.hpp", "prefill_deal.hpp")] + [
     os.path.join(ROOT, "include", "coopt_attn.h"), os.path.join(ROOT, "include", "coopt_probe.h")]
@@ -50,12 +54,25 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_binding() -> None:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(root, "include"),
+           "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, BINDING_SOURCE), "-o", BINDING,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed for {BINDING_SOURCE}:\n{res.stderr}")
+
+
 def needs_build() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(PROBE_LIB):
+    if not all(os.path.exists(p) for p in (LIB, PROBE_LIB, BINDING)):
         return True
     newest = max(os.path.getmtime(p)
-                 for p in [os.path.join(CSRC, s) for s in SOURCES + PROBE_SOURCES] + HEADERS)
-    return min(os.path.getmtime(LIB), os.path.getmtime(PROBE_LIB)) < newest
+                 for p in [os.path.join(CSRC, s) for s in SOURCES + PROBE_SOURCES + [BINDING_SOURCE]] + HEADERS)
+    return min(os.path.getmtime(p) for p in (LIB, PROBE_LIB, BINDING)) < newest
 
 
 def build(force: bool = True) -> str:
@@ -64,7 +81,9 @@ def build(force: bool = True) -> str:
         return LIB
     os.makedirs(BUILD, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=6) as pool:
+        binding = pool.submit(_build_binding)
         objs = list(pool.map(_compile, SOURCES + PROBE_SOURCES))
+        binding.result()
     for lib, n in ((LIB, objs[:len(SOURCES)]), (PROBE_LIB, objs[len(SOURCES):])):
         cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", "-o", lib, *n]
         res = subprocess.run(cmd, capture_output=True, text=True)
