@@ -471,6 +471,12 @@ extern "C" int coopt_paged_gqa_decode(const void* q, const void* k_cache, const 
     if (st != COOPT_OK) return st;
     if (!out) return COOPT_ERR_NULL;
     hipStream_t stream = (hipStream_t)hip_stream;
+    if (workspace) {
+        st = check_balanced(sh, given, &plan, workspace, workspace_bytes);
+        if (st != COOPT_OK) return st;
+    }
+    if (!given && pair_decode_fits(sh))
+        return launch_pair_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, sh, stream);
     if (!workspace) {
         // one workgroup per (sequence, KV head) covers the whole context and writes `out`
         DecodeArgs a = make_args(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, sh);
@@ -481,8 +487,6 @@ extern "C" int coopt_paged_gqa_decode(const void* q, const void* k_cache, const 
         launch_decode(a, sh, 8, plan.pipeline_depth, stream);
         return launch_status();
     }
-    st = check_balanced(sh, given, &plan, workspace, workspace_bytes);
-    if (st != COOPT_OK) return st;
     st = launch_flat_split(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens,
                            workspace, sh, flat_plan(plan), stream);
     if (st != COOPT_OK) return st;
@@ -542,6 +546,8 @@ extern "C" int coopt_paged_gqa_decode_noalloc(const void* q, const void* k_cache
     st = builtin_workspace(&workspace);
     if (st != COOPT_OK) return st;
     hipStream_t stream = (hipStream_t)hip_stream;
+    if (!given && pair_decode_fits(sh))
+        return launch_pair_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, sh, stream);
     // nothing in the workspace has to start at zero: the split kernel writes the tag, every count
     // and every partial that the merge kernel reads
     st = launch_flat_split(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens,
@@ -569,6 +575,9 @@ extern "C" int coopt_paged_gqa_decode_step(const void* k, const void* v,
     hipStream_t stream = (hipStream_t)hip_stream;
     const FlatAppend append{k, v, slot_mapping};
     const FlatCacheW cache{k_cache, v_cache, k_scale, v_scale};
+    if (!given && pair_decode_fits(sh))
+        return launch_pair_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, sh, stream,
+                                  &append, &cache);
     st = launch_flat_split(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens,
                            workspace, sh, flat_plan(plan), stream, &append);
     if (st != COOPT_OK) return st;

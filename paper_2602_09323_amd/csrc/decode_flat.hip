@@ -1059,6 +1059,138 @@ flat_merge_kernel(const FlatArgs a)
     }
 }
 
+// ---- short contexts: one workgroup per (sequence, KV head) pair, the whole decode or fused step in one
+// launch.
+//
+// Bound by latency: a launch of a few pairs of a few hundred tokens is launches and memory round trips.
+// The split and the merge of the balanced form are two launches with partials in memory between them;
+// here a pair's eight wavefronts take its groups in turn, meet in LDS and write the rows.  The block
+// numbers of a wavefront's groups are asked for beside the length (they do not depend on it), so the
+// first tile load stands two round trips behind the launch.  The new row is attended over from
+// registers by the wavefront of the pair's last group, as in the balanced form, and stored by workgroups
+// of their own behind the pairs'.  One CU reads 30-35 GB/s, so the form ends where a pair's stream is
+// longer than the second launch takes (pair_decode_fits).
+constexpr int kPairWaves = 8;
+constexpr int kPairGroups = 32;         // two-block groups per wavefront: a lane for every block
+constexpr long long kPairBytes = 140000;    // of a pair's K and V, at most (pair_decode_fits)
+constexpr long long kPairs = 256;           // a workgroup holds a CU
+
+template <int HEAD_DIM, int KV, bool BIG, bool APPEND>
+__global__ void __launch_bounds__(64 * kPairWaves, 2)
+pair_decode_kernel(const FlatArgs a)
+{
+    constexpr int E = HEAD_DIM / 64;
+    constexpr int ES = BlockRegs<HEAD_DIM, KV>::ES;
+    constexpr int DEPTH = HEAD_DIM * ES > 128 ? 2 : 3;      // groups in flight: 256 registers
+    const int lane = threadIdx.x & 63;
+    const int wave = wave_uniform((int)(threadIdx.x >> 6));
+    const int pairs = a.num_seqs * a.H_k;
+    if (APPEND && (int)blockIdx.x >= pairs) {               // the grid's end: the new rows' stores
+        const int pair = ((int)blockIdx.x - pairs) * kPairWaves + wave;
+        const int at = min(pair, pairs - 1), seq = at / a.H_k;
+        uint16_t kb[E], vb[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            kb[e] = reinterpret_cast<const uint16_t*>(a.k_new)[(size_t)at * HEAD_DIM + lane * E + e];
+            vb[e] = reinterpret_cast<const uint16_t*>(a.v_new)[(size_t)at * HEAD_DIM + lane * E + e];
+        }
+        append_new_row<HEAD_DIM>(a, pair, lane, kb, vb, a.new_slots[seq], a.context_lens[seq]);
+        return;
+    }
+    const int n = lane & 15, grp = lane >> 4;
+    const int pair = blockIdx.x;
+    const int seq = pair / a.H_k, g = pair - seq * a.H_k;
+    // ---- everything that does not wait for the length
+    const int* bt = a.block_tables + (size_t)seq * a.max_blocks;
+    const int my_block = 2 * ((lane >> 1) * kPairWaves + wave) + (lane & 1);      // of group lane / 2 of this wavefront
+    const int ids = my_block < a.max_blocks ? bt[my_block] : 0;
+    half8_t q[HEAD_DIM / 32];
+    load_q_operand_rows<HEAD_DIM, KV>(q, a.q + (size_t)pair * a.G * HEAD_DIM, a.G, true, n, grp);
+    uint32_t row_k = 0, row_v = 0;
+    bool appends = false;
+    if constexpr (APPEND) {
+        const size_t at = (size_t)pair * HEAD_DIM + lane * E;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            row_k |= (uint32_t) reinterpret_cast<const uint16_t*>(a.k_new)[at + e] << (16 * e);
+            row_v |= (uint32_t) reinterpret_cast<const uint16_t*>(a.v_new)[at + e] << (16 * e);
+        }
+        appends = a.new_slots[seq] >= 0;
+    }
+    const int t = a.context_lens[seq];
+    const int nb = (t + kBlock - 1) / kBlock, ng = (nb + 1) >> 1;
+    const int count = min(max(ng - wave + kPairWaves - 1, 0) / kPairWaves, kPairGroups);      // groups of this wavefront
+
+    const TileLoader<HEAD_DIM, KV, BIG> loader(a.cv, lane, a.pool_tiles);
+    BlockRegs<HEAD_DIM, KV> regs[DEPTH][2];
+    auto issue = [&](BlockRegs<HEAD_DIM, KV> (&r)[2], int e) {
+        const int b = 2 * (e * kPairWaves + wave), ee = min(e, kPairGroups - 1);
+        loader.issue(r[0], __builtin_amdgcn_readlane(ids, 2 * ee) * a.H_k + g, e < count);
+        loader.issue(r[1], (b + 1 < nb ? __builtin_amdgcn_readlane(ids, 2 * ee + 1) : 0) * a.H_k + g, e < count && b + 1 < nb);
+    };
+    __shared__ __attribute__((aligned(16))) unsigned char sums[kPairWaves][HEAD_DIM / 16 * 1024 + 512];
+    float m = -INFINITY, l = 0.0f;
+    floatx4 acc[HEAD_DIM / 16];
+#pragma unroll
+    for (int c = 0; c < HEAD_DIM / 16; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+        issue(regs[u], u);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int j = 0; j < count; j += DEPTH) {
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            const int e = j + u;
+            if (e < count) {
+                const int gi = e * kPairWaves + wave, rem = t - 2 * kBlock * gi, vis = rem - 4 * grp;
+                if constexpr (APPEND) {
+                    // (the wavefront's place for its sums is free until the end)
+                    if (appends && gi == ng - 1)
+                        take_new_token<HEAD_DIM, KV>(regs[u][0], regs[u][1], row_k, row_v, rem - 1, sums[wave], lane);
+                }
+                group_update<HEAD_DIM, KV>(regs[u][0], regs[u][1], q, m, l, acc, rem < 2 * kBlock, vis, vis - kBlock,
+                                           vis, vis - kBlock, a.scale_log2e);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            issue(regs[u], e + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // ---- the wavefronts' sums meet: lane (n, grp) has dims 16c + 4 grp .. of head n
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    constexpr int kML = HEAD_DIM / 16 * 1024;
+#pragma unroll
+    for (int c = 0; c < HEAD_DIM / 16; ++c) *reinterpret_cast<floatx4*>(sums[wave] + 1024 * c + 16 * lane) = acc[c];
+    *reinterpret_cast<float*>(sums[wave] + kML + 4 * lane) = m;
+    *reinterpret_cast<float*>(sums[wave] + kML + 256 + 4 * lane) = l;
+    __syncthreads();
+    if (wave >= HEAD_DIM / 16 || n >= a.G) return;              // wavefront c: dims 16c .. +15 of every head
+    float ms[kPairWaves], M = -INFINITY, L = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kPairWaves; ++w) {
+        ms[w] = *reinterpret_cast<const float*>(sums[w] + kML + 4 * lane);
+        M = fmaxf(M, ms[w]);
+    }
+    floatx4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kPairWaves; ++w) {
+        // (a wavefront without groups is left out, not weighted by zero)
+        const bool had = w < ng;
+        const float x = __builtin_amdgcn_exp2f(ms[w] - M);
+        const floatx4 s = *reinterpret_cast<const floatx4*>(sums[w] + 1024 * wave + 16 * lane);
+        L += had ? *reinterpret_cast<const float*>(sums[w] + kML + 256 + 4 * lane) * x : 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] += had ? s[i] * x : 0.0f;
+    }
+    const float inv = t > 0 ? 1.0f / L : 0.0f;
+    // (the caller's rows may begin at any 2-byte boundary)
+    typedef _Float16 row_piece_t __attribute__((ext_vector_type(4), aligned(2)));
+    *reinterpret_cast<row_piece_t*>(a.out + ((size_t)pair * a.G + n) * HEAD_DIM + 16 * wave + 4 * grp) =
+        row_piece_t{(half_t)(o[0] * inv), (half_t)(o[1] * inv), (half_t)(o[2] * inv), (half_t)(o[3] * inv)};
+}
+
 template <int HEAD_DIM, int KV, bool BIG, int DEPTH, bool BLOCK_REDUCE, bool APPEND>
 static void launch_flat_kernel(const FlatArgs& a, dim3 grid, hipStream_t stream)
 {
@@ -1327,6 +1459,73 @@ int launch_flat_merge(const int32_t* context_lens, void* workspace, void* out, c
         else
             hipLaunchKernelGGL((flat_merge_kernel<64, false>), rgrid, rblock, 0, stream, a);
     }
+    return launch_status();
+}
+
+// The line, in us a fused step (balanced form / this one; 40 heads of 128 dims over 8, E4M3, unless said):
+//   one sequence     64 tokens 9.8 / 5.4, 256 11.4 / 7.6, 512 (135 KB) 11.5 / 8.9, 1024 11.8 / 12.1, 2048 12.5 / 17.0
+//   32 sequences     64 tokens 10.9 / 7.5, 512 16.3 / 12.7, 64 to 512 15.1 / 11.0
+//   64 sequences     (two workgroups a CU, one after the other) 64 tokens 12.4 / 12.3, 256 17.2 / 18.9
+//   fp16, 40 over 40 heads: 4 sequences of 256 tokens 12.6 / 9.8, 12 of 256 20.1 / 19.8
+// A batch of different lengths costs this form its longest, which the table's width bounds; where the width
+// is much more than the lengths a call stays with the balanced form, which is right, if slower.
+bool pair_decode_fits(const coopt_shape* sh)
+{
+    const long long tokens = (long long)sh->max_blocks_per_seq * kBlock;
+    const long long bytes = tokens * (sh->kv_dtype == COOPT_KV_FP16 ? 4LL * sh->head_dim : 2LL * sh->head_dim + 8);
+    return tokens <= 2 * kBlock * kPairWaves * kPairGroups && bytes <= kPairBytes &&
+           (long long)sh->num_seqs * sh->num_kv_heads <= kPairs;
+}
+
+int launch_pair_decode(const void* q, const void* k_cache, const void* v_cache, const float* k_scale,
+                       const float* v_scale, const int32_t* block_tables, const int32_t* context_lens, void* out,
+                       const coopt_shape* sh, hipStream_t stream, const FlatAppend* append, const FlatCacheW* cache)
+{
+    FlatArgs a{};
+    a.q = (const half_t*)q;
+    a.cv = CacheView{(const uint8_t*)k_cache, (const uint8_t*)v_cache, k_scale, v_scale};
+    a.block_tables = block_tables;
+    a.context_lens = context_lens;
+    a.out = (half_t*)out;
+    a.num_seqs = sh->num_seqs;
+    a.H_q = sh->num_q_heads;
+    a.H_k = sh->num_kv_heads;
+    a.G = sh->num_q_heads / sh->num_kv_heads;
+    a.max_blocks = sh->max_blocks_per_seq;
+    a.pool_tiles = sh->num_blocks * sh->num_kv_heads;
+    a.scale_log2e = sh->softmax_scale * kLog2e;
+    a.kv_dtype = sh->kv_dtype;
+    const int pairs = sh->num_seqs * sh->num_kv_heads;
+    int wgs = pairs;
+    if (append) {
+        a.new_slots = append->slot_mapping;
+        a.k_new = (const half_t*)append->k;
+        a.v_new = (const half_t*)append->v;
+        a.k_cache_w = (uint8_t*)cache->k_cache;
+        a.v_cache_w = (uint8_t*)cache->v_cache;
+        a.k_scale_w = cache->k_scale;
+        a.v_scale_w = cache->v_scale;
+        wgs += (pairs + kPairWaves - 1) / kPairWaves;
+    }
+    const dim3 grid((unsigned)wgs), block(64 * kPairWaves);
+    const bool big = !pool_fits_small(sh);
+    auto launch = [&](auto dim, auto kv) {
+        constexpr int D = decltype(dim)::value, KV = decltype(kv)::value;
+        if (big) {
+            if (append) hipLaunchKernelGGL((pair_decode_kernel<D, KV, true, true>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((pair_decode_kernel<D, KV, true, false>), grid, block, 0, stream, a);
+        } else {
+            if (append) hipLaunchKernelGGL((pair_decode_kernel<D, KV, false, true>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((pair_decode_kernel<D, KV, false, false>), grid, block, 0, stream, a);
+        }
+    };
+    auto of_dim = [&](auto kv) {
+        if (sh->head_dim == 128) launch(std::integral_constant<int, 128>{}, kv);
+        else launch(std::integral_constant<int, 64>{}, kv);
+    };
+    if (sh->kv_dtype == COOPT_KV_E4M3) of_dim(std::integral_constant<int, COOPT_KV_E4M3>{});
+    else if (sh->kv_dtype == COOPT_KV_E5M2) of_dim(std::integral_constant<int, COOPT_KV_E5M2>{});
+    else of_dim(std::integral_constant<int, COOPT_KV_FP16>{});
     return launch_status();
 }
 
