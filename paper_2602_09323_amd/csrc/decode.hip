@@ -475,9 +475,7 @@ extern "C" int coopt_paged_gqa_decode(const void* q, const void* k_cache, const 
         st = check_balanced(sh, given, &plan, workspace, workspace_bytes);
         if (st != COOPT_OK) return st;
     }
-    if (!given && pair_decode_fits(sh))
-        return launch_pair_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, sh, stream);
-    if (!workspace) {
+    if (!workspace && (given || !pair_decode_fits(sh))) {
         // one workgroup per (sequence, KV head) covers the whole context and writes `out`
         DecodeArgs a = make_args(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, sh);
         a.out = (half_t*)out;
@@ -487,10 +485,8 @@ extern "C" int coopt_paged_gqa_decode(const void* q, const void* k_cache, const 
         launch_decode(a, sh, 8, plan.pipeline_depth, stream);
         return launch_status();
     }
-    st = launch_flat_split(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens,
-                           workspace, sh, flat_plan(plan), stream);
-    if (st != COOPT_OK) return st;
-    return launch_flat_merge(context_lens, workspace, out, sh, flat_plan(plan), stream);
+    return launch_planned_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, workspace, sh,
+                         flat_plan(plan), given != nullptr, stream);
 }
 
 // ---- a decode entry point that allocates nothing and takes no workspace
@@ -546,14 +542,10 @@ extern "C" int coopt_paged_gqa_decode_noalloc(const void* q, const void* k_cache
     st = builtin_workspace(&workspace);
     if (st != COOPT_OK) return st;
     hipStream_t stream = (hipStream_t)hip_stream;
-    if (!given && pair_decode_fits(sh))
-        return launch_pair_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, sh, stream);
     // nothing in the workspace has to start at zero: the split kernel writes the tag, every count
     // and every partial that the merge kernel reads
-    st = launch_flat_split(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens,
-                           workspace, sh, flat_plan(plan), stream);
-    if (st != COOPT_OK) return st;
-    return launch_flat_merge(context_lens, workspace, out, sh, flat_plan(plan), stream);
+    return launch_planned_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, workspace, sh,
+                         flat_plan(plan), given != nullptr, stream);
 }
 
 extern "C" int coopt_paged_gqa_decode_step(const void* k, const void* v,
@@ -575,14 +567,8 @@ extern "C" int coopt_paged_gqa_decode_step(const void* k, const void* v,
     hipStream_t stream = (hipStream_t)hip_stream;
     const FlatAppend append{k, v, slot_mapping};
     const FlatCacheW cache{k_cache, v_cache, k_scale, v_scale};
-    if (!given && pair_decode_fits(sh))
-        return launch_pair_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, sh, stream,
-                                  &append, &cache);
-    st = launch_flat_split(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens,
-                           workspace, sh, flat_plan(plan), stream, &append);
-    if (st != COOPT_OK) return st;
-    return launch_flat_merge(context_lens, workspace, out, sh, flat_plan(plan), stream, nullptr, false,
-                             &append, &cache);
+    return launch_planned_decode(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, out, workspace, sh,
+                         flat_plan(plan), given != nullptr, stream, &append, &cache);
 }
 
 extern "C" size_t coopt_decode_schedule_bytes(const coopt_shape* sh, const coopt_decode_plan* given)

@@ -182,6 +182,7 @@ struct FlatArgs {
     int32_t pair_extra;   // cost units charged to a share for every pair that ends inside it
     int32_t pool_tiles;   // num_blocks * H_k
     int32_t decode_wgs;   // workgroups (= wavefronts) of the attention launch
+    int32_t parts;        // pair_decode_kernel: workgroups per (sequence, KV head) pair
     int32_t append_wgs;   // fused step: workgroups at the head of the merge launch's grid whose
                           // wavefronts store one new row each (0 otherwise)
     int32_t kv_dtype;     // cache type, for the merge launch's row stores
@@ -1071,21 +1072,30 @@ flat_merge_kernel(const FlatArgs a)
 // of their own behind the pairs'.  One CU reads 30-35 GB/s, so the form ends where a pair's stream is
 // longer than the second launch takes (pair_decode_fits).
 constexpr int kPairWaves = 8;
+constexpr int kPartWaves = 4;
 constexpr int kPairGroups = 32;         // two-block groups per wavefront: a lane for every block
 constexpr long long kPairBytes = 140000;    // of a pair's K and V, at most (pair_decode_fits)
+constexpr long long kPartsGroups = 5120;    // of all pairs, in parts (pair_parts)
 constexpr long long kPairs = 256;           // a workgroup holds a CU
 
-template <int HEAD_DIM, int KV, bool BIG, bool APPEND>
-__global__ void __launch_bounds__(64 * kPairWaves, 2)
+//
+// In parts: few pairs of longer contexts, whose groups would leave most CUs idle or one CU too many of
+// them, go to `parts` workgroups of four wavefronts a pair, four groups at a time in turn, each of which
+// leaves one partial for the merge launch (which then stores the new rows as well).  Against single
+// wavefronts with shares of at least four groups that derive the schedule of the whole batch first: no
+// scans in front of the block numbers, and a quarter of the groups in a row.
+template <int HEAD_DIM, int KV, bool BIG, bool APPEND, bool PARTS>
+__global__ void __launch_bounds__(64 * (PARTS ? kPartWaves : kPairWaves), PARTS ? 1 : 2)
 pair_decode_kernel(const FlatArgs a)
 {
+    constexpr int kWaves = PARTS ? kPartWaves : kPairWaves;
     constexpr int E = HEAD_DIM / 64;
     constexpr int ES = BlockRegs<HEAD_DIM, KV>::ES;
     constexpr int DEPTH = HEAD_DIM * ES > 128 ? 2 : 3;      // groups in flight: 256 registers
     const int lane = threadIdx.x & 63;
     const int wave = wave_uniform((int)(threadIdx.x >> 6));
     const int pairs = a.num_seqs * a.H_k;
-    if (APPEND && (int)blockIdx.x >= pairs) {               // the grid's end: the new rows' stores
+    if (APPEND && !PARTS && (int)blockIdx.x >= pairs) {               // the grid's end: the new rows' stores
         const int pair = ((int)blockIdx.x - pairs) * kPairWaves + wave;
         const int at = min(pair, pairs - 1), seq = at / a.H_k;
         uint16_t kb[E], vb[E];
@@ -1098,11 +1108,15 @@ pair_decode_kernel(const FlatArgs a)
         return;
     }
     const int n = lane & 15, grp = lane >> 4;
-    const int pair = blockIdx.x;
+    const int parts = PARTS ? a.parts : 1;
+    const int pair = PARTS ? (int)blockIdx.x / parts : (int)blockIdx.x, part = PARTS ? (int)blockIdx.x - pair * parts : 0;
     const int seq = pair / a.H_k, g = pair - seq * a.H_k;
+    if (PARTS && blockIdx.x == 0 && threadIdx.x == 0) a.ws_header[0] = a.ws_tag;
     // ---- everything that does not wait for the length
     const int* bt = a.block_tables + (size_t)seq * a.max_blocks;
-    const int my_block = 2 * ((lane >> 1) * kPairWaves + wave) + (lane & 1);      // of group lane / 2 of this wavefront
+    // group e of this wavefront, of the pair's groups kWaves at a time to its workgroups in turn
+    auto group_of = [&](int e) { return (e * parts + part) * kWaves + wave; };
+    const int my_block = 2 * group_of(lane >> 1) + (lane & 1);
     const int ids = my_block < a.max_blocks ? bt[my_block] : 0;
     half8_t q[HEAD_DIM / 32];
     load_q_operand_rows<HEAD_DIM, KV>(q, a.q + (size_t)pair * a.G * HEAD_DIM, a.G, true, n, grp);
@@ -1119,16 +1133,18 @@ pair_decode_kernel(const FlatArgs a)
     }
     const int t = a.context_lens[seq];
     const int nb = (t + kBlock - 1) / kBlock, ng = (nb + 1) >> 1;
-    const int count = min(max(ng - wave + kPairWaves - 1, 0) / kPairWaves, kPairGroups);      // groups of this wavefront
+    const int first = part * kWaves + wave;
+    const int count = first < ng ? min((ng - first - 1) / (kWaves * parts) + 1, kPairGroups) : 0;
+    if (PARTS && part * kWaves >= ng) return;
 
     const TileLoader<HEAD_DIM, KV, BIG> loader(a.cv, lane, a.pool_tiles);
     BlockRegs<HEAD_DIM, KV> regs[DEPTH][2];
     auto issue = [&](BlockRegs<HEAD_DIM, KV> (&r)[2], int e) {
-        const int b = 2 * (e * kPairWaves + wave), ee = min(e, kPairGroups - 1);
+        const int b = 2 * group_of(e), ee = min(e, kPairGroups - 1);
         loader.issue(r[0], __builtin_amdgcn_readlane(ids, 2 * ee) * a.H_k + g, e < count);
         loader.issue(r[1], (b + 1 < nb ? __builtin_amdgcn_readlane(ids, 2 * ee + 1) : 0) * a.H_k + g, e < count && b + 1 < nb);
     };
-    __shared__ __attribute__((aligned(16))) unsigned char sums[kPairWaves][HEAD_DIM / 16 * 1024 + 512];
+    __shared__ __attribute__((aligned(16))) unsigned char sums[kWaves][HEAD_DIM / 16 * 1024 + 512];
     float m = -INFINITY, l = 0.0f;
     floatx4 acc[HEAD_DIM / 16];
 #pragma unroll
@@ -1143,7 +1159,7 @@ pair_decode_kernel(const FlatArgs a)
         for (int u = 0; u < DEPTH; ++u) {
             const int e = j + u;
             if (e < count) {
-                const int gi = e * kPairWaves + wave, rem = t - 2 * kBlock * gi, vis = rem - 4 * grp;
+                const int gi = group_of(e), rem = t - 2 * kBlock * gi, vis = rem - 4 * grp;
                 if constexpr (APPEND) {
                     // (the wavefront's place for its sums is free until the end)
                     if (appends && gi == ng - 1)
@@ -1166,29 +1182,47 @@ pair_decode_kernel(const FlatArgs a)
     *reinterpret_cast<float*>(sums[wave] + kML + 4 * lane) = m;
     *reinterpret_cast<float*>(sums[wave] + kML + 256 + 4 * lane) = l;
     __syncthreads();
-    if (wave >= HEAD_DIM / 16 || n >= a.G) return;              // wavefront c: dims 16c .. +15 of every head
-    float ms[kPairWaves], M = -INFINITY, L = 0.0f;
+    if (n >= a.G) return;
+    float x[kWaves], M = -INFINITY, L = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kPairWaves; ++w) {
-        ms[w] = *reinterpret_cast<const float*>(sums[w] + kML + 4 * lane);
-        M = fmaxf(M, ms[w]);
+    for (int w = 0; w < kWaves; ++w) {
+        x[w] = *reinterpret_cast<const float*>(sums[w] + kML + 4 * lane);
+        M = fmaxf(M, x[w]);
     }
-    floatx4 o = {0.f, 0.f, 0.f, 0.f};
+    // (a wavefront without groups is left out, not weighted by zero)
+    const int had = min(ng - part * kWaves, kWaves);
 #pragma unroll
-    for (int w = 0; w < kPairWaves; ++w) {
-        // (a wavefront without groups is left out, not weighted by zero)
-        const bool had = w < ng;
-        const float x = __builtin_amdgcn_exp2f(ms[w] - M);
-        const floatx4 s = *reinterpret_cast<const floatx4*>(sums[w] + 1024 * wave + 16 * lane);
-        L += had ? *reinterpret_cast<const float*>(sums[w] + kML + 256 + 4 * lane) * x : 0.0f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] += had ? s[i] * x : 0.0f;
+    for (int w = 0; w < kWaves; ++w) {
+        x[w] = __builtin_amdgcn_exp2f(x[w] - M);
+        L += w < had ? *reinterpret_cast<const float*>(sums[w] + kML + 256 + 4 * lane) * x[w] : 0.0f;
     }
     const float inv = t > 0 ? 1.0f / L : 0.0f;
-    // (the caller's rows may begin at any 2-byte boundary)
-    typedef _Float16 row_piece_t __attribute__((ext_vector_type(4), aligned(2)));
-    *reinterpret_cast<row_piece_t*>(a.out + ((size_t)pair * a.G + n) * HEAD_DIM + 16 * wave + 4 * grp) =
-        row_piece_t{(half_t)(o[0] * inv), (half_t)(o[1] * inv), (half_t)(o[2] * inv), (half_t)(o[3] * inv)};
+    const size_t at = ((size_t)pair * a.G + n) * (PARTS ? a.max_slots : 1) + part;
+#pragma unroll
+    for (int c0 = 0; c0 < HEAD_DIM / 16; c0 += kWaves) {
+        const int c = c0 + wave;                                // dims 16c .. +15 of every head
+        if (c >= HEAD_DIM / 16) break;
+        floatx4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const floatx4 s = *reinterpret_cast<const floatx4*>(sums[w] + 1024 * c + 16 * lane);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] += w < had ? s[i] * x[w] : 0.0f;
+        }
+        if constexpr (PARTS) {
+            *reinterpret_cast<floatx4*>(a.tmp_out + at * HEAD_DIM + 16 * c + 4 * grp) = o * inv;
+        } else {
+            // (the caller's rows may begin at any 2-byte boundary)
+            typedef _Float16 row_piece_t __attribute__((ext_vector_type(4), aligned(2)));
+            *reinterpret_cast<row_piece_t*>(a.out + at * HEAD_DIM + 16 * c + 4 * grp) =
+                row_piece_t{(half_t)(o[0] * inv), (half_t)(o[1] * inv), (half_t)(o[2] * inv), (half_t)(o[3] * inv)};
+        }
+    }
+    if (PARTS && wave == 0 && grp == 0) {
+        a.max_logits[at] = M * kLn2;
+        a.exp_sums[at] = L * kPUnshiftOf<KV>;
+        if (part == 0 && n == 0) a.counts[pair] = min(parts, (ng + kWaves - 1) / kWaves);
+    }
 }
 
 template <int HEAD_DIM, int KV, bool BIG, int DEPTH, bool BLOCK_REDUCE, bool APPEND>
@@ -1477,46 +1511,35 @@ bool pair_decode_fits(const coopt_shape* sh)
            (long long)sh->num_seqs * sh->num_kv_heads <= kPairs;
 }
 
-int launch_pair_decode(const void* q, const void* k_cache, const void* v_cache, const float* k_scale,
-                       const float* v_scale, const int32_t* block_tables, const int32_t* context_lens, void* out,
-                       const coopt_shape* sh, hipStream_t stream, const FlatAppend* append, const FlatCacheW* cache)
+// Workgroups per pair of the form in parts, 0 where the balanced form is to run.  The line, in us a fused
+// step (balanced / in parts; 40 heads of 128 dims over 8, E4M3, unless said; groups: as many as the table holds):
+//   1 x 1789 tokens     (448 groups)  12.1 / 10.1      1 x 8000 (2000)               13.3 / 11.7
+//   4 x 298 .. 1789     (1792)        13.0 / 11.1      16 x 170 .. 1024 (4096)       15.2 / 14.0
+//   8 x 2500 (5056)                   17.6 / 15.4      8 x 416 .. 2500 (5056)        15.7 / 14.3
+//   8 x 4096 (8192)                   20.5 / 19.6      8 x 682 .. 4096 (8192)        16.5 / 17.1
+//   16 x 682 .. 4096    (16384)       23.0 / 24.7      fp16 over 40 heads, 2 x 666 .. 4000 (10000)  22.9 / 24.2
+// Beyond it equal shares of what the sequences really hold matter more than an early start.
+static int pair_parts(const coopt_shape* sh, const FlatPlan& plan)
 {
-    FlatArgs a{};
-    a.q = (const half_t*)q;
-    a.cv = CacheView{(const uint8_t*)k_cache, (const uint8_t*)v_cache, k_scale, v_scale};
-    a.block_tables = block_tables;
-    a.context_lens = context_lens;
-    a.out = (half_t*)out;
-    a.num_seqs = sh->num_seqs;
-    a.H_q = sh->num_q_heads;
-    a.H_k = sh->num_kv_heads;
-    a.G = sh->num_q_heads / sh->num_kv_heads;
-    a.max_blocks = sh->max_blocks_per_seq;
-    a.pool_tiles = sh->num_blocks * sh->num_kv_heads;
-    a.scale_log2e = sh->softmax_scale * kLog2e;
-    a.kv_dtype = sh->kv_dtype;
-    const int pairs = sh->num_seqs * sh->num_kv_heads;
-    int wgs = pairs;
-    if (append) {
-        a.new_slots = append->slot_mapping;
-        a.k_new = (const half_t*)append->k;
-        a.v_new = (const half_t*)append->v;
-        a.k_cache_w = (uint8_t*)cache->k_cache;
-        a.v_cache_w = (uint8_t*)cache->v_cache;
-        a.k_scale_w = cache->k_scale;
-        a.v_scale_w = cache->v_scale;
-        wgs += (pairs + kPairWaves - 1) / kPairWaves;
-    }
-    const dim3 grid((unsigned)wgs), block(64 * kPairWaves);
-    const bool big = !pool_fits_small(sh);
+    const int pairs = sh->num_seqs * sh->num_kv_heads, groups = (sh->max_blocks_per_seq + 1) / 2;
+    if ((long long)pairs * groups > kPartsGroups) return 0;
+    const int chunks = (groups + kPartWaves - 1) / kPartWaves;
+    return std::max(1, std::min({chunks, (int)kPairs / pairs, flat_max_slots(sh, plan)}));
+}
+
+template <bool PARTS>
+static int launch_pairs(const FlatArgs& a, const coopt_shape* sh, unsigned wgs, hipStream_t stream)
+{
+    const dim3 grid(wgs), block(64 * (PARTS ? kPartWaves : kPairWaves));
+    const bool big = !pool_fits_small(sh), append = a.new_slots != nullptr;
     auto launch = [&](auto dim, auto kv) {
         constexpr int D = decltype(dim)::value, KV = decltype(kv)::value;
         if (big) {
-            if (append) hipLaunchKernelGGL((pair_decode_kernel<D, KV, true, true>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((pair_decode_kernel<D, KV, true, false>), grid, block, 0, stream, a);
+            if (append) hipLaunchKernelGGL((pair_decode_kernel<D, KV, true, true, PARTS>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((pair_decode_kernel<D, KV, true, false, PARTS>), grid, block, 0, stream, a);
         } else {
-            if (append) hipLaunchKernelGGL((pair_decode_kernel<D, KV, false, true>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((pair_decode_kernel<D, KV, false, false>), grid, block, 0, stream, a);
+            if (append) hipLaunchKernelGGL((pair_decode_kernel<D, KV, false, true, PARTS>), grid, block, 0, stream, a);
+            else hipLaunchKernelGGL((pair_decode_kernel<D, KV, false, false, PARTS>), grid, block, 0, stream, a);
         }
     };
     auto of_dim = [&](auto kv) {
@@ -1527,6 +1550,43 @@ int launch_pair_decode(const void* q, const void* k_cache, const void* v_cache, 
     else if (sh->kv_dtype == COOPT_KV_E5M2) of_dim(std::integral_constant<int, COOPT_KV_E5M2>{});
     else of_dim(std::integral_constant<int, COOPT_KV_FP16>{});
     return launch_status();
+}
+
+int launch_planned_decode(const void* q, const void* k_cache, const void* v_cache, const float* k_scale, const float* v_scale,
+                  const int32_t* block_tables, const int32_t* context_lens, void* out, void* workspace,
+                  const coopt_shape* sh, const FlatPlan& plan, bool own_plan, hipStream_t stream,
+                  const FlatAppend* append, const FlatCacheW* cache)
+{
+    const bool one = !own_plan && pair_decode_fits(sh);
+    const int parts = own_plan || one ? 0 : pair_parts(sh, plan);
+    if (!one && parts == 0) {
+        const int st = launch_flat_split(q, k_cache, v_cache, k_scale, v_scale, block_tables, context_lens, workspace, sh,
+                                         plan, stream, append);
+        if (st != COOPT_OK) return st;
+        return launch_flat_merge(context_lens, workspace, out, sh, plan, stream, nullptr, false, append, cache);
+    }
+    FlatArgs a = flat_args(sh, plan, workspace);
+    a.q = (const half_t*)q;
+    a.cv = CacheView{(const uint8_t*)k_cache, (const uint8_t*)v_cache, k_scale, v_scale};
+    a.block_tables = block_tables;
+    a.context_lens = context_lens;
+    a.out = (half_t*)out;
+    a.parts = parts;
+    a.kv_dtype = sh->kv_dtype;
+    const int pairs = sh->num_seqs * sh->num_kv_heads;
+    if (append) {
+        a.new_slots = append->slot_mapping;
+        a.k_new = (const half_t*)append->k;
+        a.v_new = (const half_t*)append->v;
+        a.k_cache_w = (uint8_t*)cache->k_cache;
+        a.v_cache_w = (uint8_t*)cache->v_cache;
+        a.k_scale_w = cache->k_scale;
+        a.v_scale_w = cache->v_scale;
+    }
+    if (one) return launch_pairs<false>(a, sh, pairs + (append ? (pairs + kPairWaves - 1) / kPairWaves : 0), stream);
+    const int st = launch_pairs<true>(a, sh, pairs * parts, stream);
+    if (st != COOPT_OK) return st;
+    return launch_flat_merge(context_lens, workspace, out, sh, plan, stream, nullptr, false, append, cache);
 }
 
 }  // namespace coopt

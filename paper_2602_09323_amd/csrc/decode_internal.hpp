@@ -60,12 +60,13 @@ int launch_flat_prepare(const int32_t* block_tables, const int32_t* context_lens
                         const int64_t* slot_mapping, void* schedule, const coopt_shape* sh,
                         const FlatPlan& plan, hipStream_t stream);
 
-// Few pairs of short contexts: decode, or the fused step, as one launch without a workspace.  Whether a
-// shape is one of these (judged by what bounds its contexts, the table's width), and the launch.
+// Decode, or with `append` and `cache` the fused step, in the form that suits the shape: the two launches
+// above, or -- where the plan is the library's own -- for few pairs one launch without a workspace
+// (pair_decode_fits, judged by what bounds the contexts, the table's width), or two with simpler shares.
 bool pair_decode_fits(const coopt_shape* sh);
-int launch_pair_decode(const void* q, const void* k_cache, const void* v_cache, const float* k_scale,
-                       const float* v_scale, const int32_t* block_tables, const int32_t* context_lens, void* out,
-                       const coopt_shape* sh, hipStream_t stream, const FlatAppend* append = nullptr,
-                       const FlatCacheW* cache = nullptr);
+int launch_planned_decode(const void* q, const void* k_cache, const void* v_cache, const float* k_scale, const float* v_scale,
+                  const int32_t* block_tables, const int32_t* context_lens, void* out, void* workspace,
+                  const coopt_shape* sh, const FlatPlan& plan, bool own_plan, hipStream_t stream,
+                  const FlatAppend* append = nullptr, const FlatCacheW* cache = nullptr);
 
 }  // namespace coopt

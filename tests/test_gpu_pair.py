@@ -1,7 +1,8 @@
-"""GPU parity: short contexts without a plan, where decode and the fused step are one launch of a workgroup
-per (sequence, KV head) pair.  Against the oracle, at the edges of blocks, two-block groups and of the
-eight wavefronts that share a pair's groups; the step's cache bytes bit for bit; and the shapes at which
-the balanced form takes over again."""
+"""GPU parity: few pairs without a plan, where decode and the fused step are one launch of a workgroup
+per (sequence, KV head) pair, or, for longer contexts, one of several workgroups per pair and the merge.
+Against the oracle, at the edges of blocks, two-block groups and of the wavefronts and workgroups that
+share a pair's groups; the step's cache bytes bit for bit; and the shapes at which one form takes over
+from the other."""
 import numpy as np
 import pytest
 import torch
@@ -79,6 +80,43 @@ def test_step(oracle_mod, kv_dtype, H_q, H_k, d):
     for name, got, want in zip(("k_cache", "v_cache", "k_scale", "v_scale"), dev_cache_to_host(w, dcache), cache):
         if want is not None:
             assert np.array_equal(got.reshape(-1).view(np.uint8), want.reshape(-1).view(np.uint8)), name
+
+
+PART_LENS = [0, 1, 17, 33, 127, 128, 129, 256, 257, 545, 900, 1025]
+
+
+@pytest.mark.parametrize("step", [False, True], ids=["decode", "step"])
+@pytest.mark.parametrize("kv_dtype,H_q,H_k,d,lens,max_blocks", [
+    ("e4m3", 40, 8, 128, [1789], 112),                   # 14 parts of four groups
+    ("e4m3", 40, 8, 128, PART_LENS, 80),                 # 96 pairs: two parts of five turns
+    ("e5m2", 32, 2, 64, PART_LENS, 130),                 # ten parts, two turns
+    ("fp16", 10, 2, 64, PART_LENS, 66),
+    ("fp16", 5, 1, 128, [3000, 1, 2999, 0, 1500], 188),
+    ("e4m3", 16, 16, 64, PART_LENS[1:] * 2, 66)])        # 352 pairs: more groups than the form takes
+def test_in_parts(oracle_mod, kv_dtype, H_q, H_k, d, lens, max_blocks, step):
+    w = _workload(kv_dtype, H_q, H_k, d, lens, max_blocks)
+    groups = len(lens) * H_k * ((max_blocks + 1) // 2)
+    assert groups <= 5120 or H_k == 16
+    cache = oracle_fill(oracle_mod, w)
+    ref = _oracle(oracle_mod, w, cache, kv_dtype)
+    shape, out = shape_of(w), _out(w)
+    ws = torch.full((coopt.decode_workspace_bytes(shape) // 4,), float("nan"), device="cuda")     # what is read was written
+    tail = dev(w.block_tables), dev(w.context_lens), out, ws, shape
+    if not step:
+        coopt.paged_gqa_decode(dev(w.q.view(np.uint16)), *cache_to_dev(cache), *tail)
+    else:
+        new = np.maximum(np.cumsum(lens) - 1, 0)
+        slots = np.where(np.asarray(lens) == 0, -1, w.slots[new])
+        dcache = alloc_dev_cache(w, fill_byte=0)
+        hip_write(w, dcache, idx=np.asarray(sorted(set(range(len(w.slots))) - set(new[slots >= 0]))))
+        coopt.paged_gqa_decode_step(dev(w.k_ctx[new].view(np.uint16)), dev(w.v_ctx[new].view(np.uint16)), dev(slots),
+                                    dev(w.q.view(np.uint16)), *dcache, *tail)
+        torch.cuda.synchronize()
+        for name, got, want in zip(("k_cache", "v_cache", "k_scale", "v_scale"), dev_cache_to_host(w, dcache), cache):
+            if want is not None:
+                assert np.array_equal(got.reshape(-1).view(np.uint8), want.reshape(-1).view(np.uint8)), name
+    torch.cuda.synchronize()
+    assert_close(out.cpu().numpy().astype(np.float64), ref, f"parts {kv_dtype} {H_q}/{H_k} x {d}")
 
 
 @pytest.mark.parametrize("S,H_q,H_k,d,max_blocks,one_launch", [(32, 8, 8, 128, 33, True), (33, 8, 8, 128, 33, False),
