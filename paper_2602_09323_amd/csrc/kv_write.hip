@@ -354,8 +354,21 @@ kv_write_fp16_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict_
 
 using namespace coopt;
 
-// From this many tokens per call on, the bulk kernel (a call of a decode step has one per sequence).
+// The bulk kernel: from this many tokens per call on, and from as many rows (tokens times heads) as keep
+// one wavefront a row from being the faster form, whatever the slots (a decode step of a large batch has
+// scattered ones).  us, bulk / a wavefront per row, 8 heads x 128 dims:
+//              64 tokens, run   scattered   256, run    scattered    512, run    scattered
+//   E4M3       3.4 / 2.5        4.4 / 2.5   3.4 / 2.9   4.8 / 2.9    3.5 / 3.8   5.2 / 3.9
+//   fp16       2.8 / 2.1        3.0 / 2.1   2.7 / 2.9   3.7 / 2.8    3.0 / 4.0   5.4 / 3.9
+// and 40 heads: E4M3 64 tokens 3.5 / 3.3 and 4.9 / 3.2, 96 tokens 3.6 / 3.8 and 5.1 / 3.8; fp16 64 tokens
+// 3.0 / 3.2 and 3.9 / 3.1; 128 tokens of 8 heads 2.8 / 2.3 and 3.2 / 2.3.
 constexpr int kBulkWriteTokens = 64;
+template <int KV> constexpr long long kRowWriteRows = kIsFp8<KV> ? 2560 : 1536;
+template <int KV>
+static bool takes_bulk(int32_t num_tokens, long long rows)
+{
+    return num_tokens >= kBulkWriteTokens && rows > kRowWriteRows<KV>;
+}
 
 template <int HEAD_DIM, int KV>
 static void launch_write_bulk(const void* k, const void* v, const int64_t* slot_mapping,
@@ -383,12 +396,12 @@ static void launch_write_fp8(const void* k, const void* v, const int64_t* slot_m
                              hipStream_t stream)
 {
     const dim3 block(256);
-    if (num_tokens >= kBulkWriteTokens && scale_mode == COOPT_SCALE_TOKEN) {
+    const long long rows = (long long)num_tokens * H_k;
+    if (takes_bulk<KV>(num_tokens, rows) && scale_mode == COOPT_SCALE_TOKEN) {
         launch_write_bulk<HEAD_DIM, KV>(k, v, slot_mapping, skip_set, num_tokens, H_k, k_cache, v_cache,
                                         k_scale, v_scale, stream);
         return;
     }
-    const long long rows = (long long)num_tokens * H_k;
     const dim3 grid((unsigned)((rows + 3) / 4));
     hipLaunchKernelGGL((kv_write_fp8_kernel<HEAD_DIM, KV>), grid, block, 0, stream, (const half_t*)k,
                        (const half_t*)v, slot_mapping, skip_set, (int)rows, H_k, k_cache, v_cache,
@@ -443,7 +456,7 @@ static int write_fp16(const void* k, const void* v, const int64_t* slot_mapping,
     if (rows > 0x7fffffffLL) return COOPT_ERR_SHAPE;
     hipStream_t stream = (hipStream_t)hip_stream;
     const dim3 block(256);
-    if (num_tokens >= kBulkWriteTokens) {
+    if (takes_bulk<COOPT_KV_FP16>(num_tokens, rows)) {
         if (shape->head_dim == 128)
             launch_write_bulk<128, COOPT_KV_FP16>(k, v, slot_mapping, skip_set, num_tokens,
                                                   shape->num_kv_heads, (uint8_t*)k_cache, (uint8_t*)v_cache,
