@@ -73,15 +73,13 @@ struct PrefillArgs : PrefillDeal {
 constexpr int kPrefillGroupsPerStage = kPrefillStageTokens / (2 * kBlock);      // two-block groups between two barriers
 constexpr int kPrefillSlots = 2 * kPrefillGroupsPerStage + 1;      // groups in LDS: two stages and one more (below)
 // Groups of a stage produced by the first team (waves 0-3); the second team takes the rest.
-// ... of a workgroup of 8 tiles, whose first team alone consumes.
-constexpr int kPrefillFirstTeamGroupsOf8 = 1;
 constexpr int kPrefillFirstTeamGroups = 3;
+constexpr int kPrefillFirstTeamGroupsOf8 = 1;      // of a workgroup of 8 tiles, whose first team alone consumes
 constexpr float kNoReference = -1.0e30f;        // a running reference below every score
 constexpr long long kPrefillXcdL2 = 4LL << 20;   // bytes of L2 per XCD
 
 // Byte offsets inside one LDS stage (one group = blocks A and B of one KV head, 32 tokens).  Operands
-// are in the order in which a 32x32x16 product takes them, lane 32h + r 16 bytes at 16 (32h + r); the
-// 16x16x32 products of the one-tile kernel find theirs in the same bytes.
+// are in the order in which a 32x32x16 product takes them, lane 32h + r 16 bytes at 16 (32h + r).
 template <int HEAD_DIM>
 struct PrefillStage {
     static constexpr int kOps = HEAD_DIM / 16;          // operands of K, and of V
@@ -101,10 +99,11 @@ struct PrefillStage {
 // weights, l = sum_j w~_j / v_scale_j: numerator and denominator then describe one softmax with
 // weights perturbed by at most 2^-11 relative, whose result differs from the exact one by at most
 // that times the weighted mean deviation of the value rows from the result -- nothing for one
-// token or a dominant one.  The sum runs on the matrix cores: `rop` is a 16-row operand whose row 0
-// holds 2^-8 / v_scale of the group's 32 tokens, times a power of two that the sum is freed of again, cut
-// to fp16 and row 1 the remainder (the producers write it), so one more 16x16x32 product per tile accumulates it in rows 0 and 1 of `lacc`,
-// which replaces eight vector additions.
+// token or a dominant one.  The sum runs on the matrix cores: one more operand (kR) has in row 0
+// 2^-8 / v_scale of the group's 32 tokens, times a power of two that the sum is freed of again, cut to
+// fp16, in row 1 the remainder (the producers write both).  A 16x16x32 product takes the weight operand of
+// a 32x32x16 one as it is, with columns 16..31 as further k-slots, for which the operand has the same in
+// rows 2 and 3; two such products per group accumulate both tiles' sums instead of sixteen vector additions.
 //
 // v_scale reaches the weight through the exponent: the producers leave lv = log2(v_scale) beside
 // k_scale, the score of a token is z' = s * ksc + lv in
