@@ -104,10 +104,10 @@ kv_write_fp8_kernel(const half_t* __restrict__ k, const half_t* __restrict__ v,
 // step of 64 sequences has them, 7.1 against 4.5 (fp16: 6.3 against 3.1).
 //
 // The stores are non-temporal wherever they come in runs: they pass the L2, where the rows' second
-// readers find theirs.  16 384 tokens x 8 heads x 128 dims in turn to enough buffers to be new to the
-// caches: fp16 23.7 us against 28.9 with plain stores, E4M3 23.4 against 24.1.  (65 504 tokens to E4M3 in
-// 32 ragged sequences, 407 MB, more than the last-level cache holds: 76 against 86 us to the same
-// buffers again and again, but 92 against 86 to six sets of them in turn.)  A token whose neighbours in
+// readers find theirs, and what follows the call still finds its own data there.  A LARGE call's K stores
+// are plain: a window's are pieces of 128 bytes, of which the L2 makes longer runs (kLargeWriteBytes has
+// both sides; V pieces are 256 bytes and stay non-temporal: both plain 108.7 us where K alone takes 107.2
+// and neither 128.2).  A token whose neighbours in
 // the call are not its neighbours in the cache would pass the L2 in 16-byte pieces; its K stores are
 // plain (16 384 tokens in random slots, fp16, 8 heads: 102 us non-temporal, 60 us so).
 
@@ -117,6 +117,7 @@ struct BulkWindow {
     static constexpr int CH = HEAD_DIM * ES / 16;           // 16-byte cache chunks, and lanes, per row
     static constexpr int kRows = 256 / CH;                  // rows a workgroup holds
     static constexpr int kOwn = kRows - 3;                  // ... of which this many are its own
+    static constexpr int kRowTraffic = HEAD_DIM * (4 + 2 * ES) + (kIsFp8<KV> ? 8 : 0);    // bytes read and written
 };
 
 typedef unsigned int wu32x4 __attribute__((ext_vector_type(4)));
@@ -191,7 +192,7 @@ __device__ __forceinline__ wu32x4 quantise_chunk(wu32x4 lo, wu32x4 hi, float& sc
     return codes;
 }
 
-template <int HEAD_DIM, int KV>
+template <int HEAD_DIM, int KV, bool LARGE>
 __global__ void __launch_bounds__(256)
 kv_write_bulk_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                      const int64_t* __restrict__ slot_mapping, const uint32_t* __restrict__ skip_set,
@@ -280,7 +281,10 @@ kv_write_bulk_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict_
     __syncthreads();
     // (here, behind the barrier: in the other arm of the plain store the compiler makes one plain
     // store of the two)
-    if (mine && !alone) __builtin_nontemporal_store(kc, kdst);
+    if (mine && !alone) {
+        if constexpr (LARGE) *kdst = kc;
+        else __builtin_nontemporal_store(kc, kdst);
+    }
 
     // ---- V quads.  Their first tokens are at least four rows apart: at most one in rows 4b .. 4b+3.
     // Sixteen lanes (n) take one 64-byte piece (cq) per token of the quad of one b; four neighbouring
@@ -354,6 +358,16 @@ kv_write_fp16_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict_
 
 using namespace coopt;
 
+// From this many bytes read and written on, a bulk call's K stores go through the L2.  us, past it / through
+// it, to buffers that are new to the caches:
+//              62-75 MB      83-88         100           125-134       150-167       201-268       402-536
+//   E4M3 128   15.7 / 16.2   20.3 / 20.3   24.5 / 23.5   29.4 / 28.6   32.8 / 32.0   46.2 / 43.8   91.3 / 84.4
+//   E4M3 64    19.6 / 20.5                 24.2 / 25.4   29.3 / 30.2   34.8 / 35.5   48.0 / 47.9   93.9 / 92.6
+//   fp16 128   14.3 / 16.1   19.5 / 19.4   22.8 / 22.3   32.8 / 29.5   39.9 / 36.1   64.4 / 56.0   128.2 / 107.2
+//   fp16 64    14.3 / 16.6                 23.5 / 23.4   32.8 / 30.7
+template <int HEAD_DIM, int KV>
+constexpr long long kLargeWriteBytes = kIsFp8<KV> && HEAD_DIM == 64 ? 200000000 : 120000000;
+
 // The bulk kernel: from this many tokens per call on, and from as many rows (tokens times heads) as keep
 // one wavefront a row from being the faster form, whatever the slots (a decode step of a large batch has
 // scattered ones).  us, bulk / a wavefront per row, 8 heads x 128 dims:
@@ -377,14 +391,15 @@ static void launch_write_bulk(const void* k, const void* v, const int64_t* slot_
 {
     constexpr int kOwn = BulkWindow<HEAD_DIM, KV>::kOwn;
     const long long step = tokens_per_launch(num_tokens, kOwn, H_k);
+    const auto kernel = (long long)num_tokens * H_k * BulkWindow<HEAD_DIM, KV>::kRowTraffic >= kLargeWriteBytes<HEAD_DIM, KV>
+                            ? kv_write_bulk_kernel<HEAD_DIM, KV, true> : kv_write_bulk_kernel<HEAD_DIM, KV, false>;
     for (long long first = 0; first < num_tokens; first += step) {
         const int n = (int)(step < num_tokens - first ? step : num_tokens - first);
         const size_t at = (size_t)first * H_k * HEAD_DIM;
         // one workgroup per window and head
-        hipLaunchKernelGGL((kv_write_bulk_kernel<HEAD_DIM, KV>), dim3((unsigned)((n - 1) / kOwn + 1) * H_k),
-                           dim3(256), 0, stream, (const uint16_t*)k + at, (const uint16_t*)v + at,
-                           slot_mapping + first, skip_set ? skip_set + first / 32 : nullptr, n, H_k, k_cache,
-                           v_cache, k_scale, v_scale);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n - 1) / kOwn + 1) * H_k), dim3(256), 0,
+                           stream, (const uint16_t*)k + at, (const uint16_t*)v + at, slot_mapping + first,
+                           skip_set ? skip_set + first / 32 : nullptr, n, H_k, k_cache, v_cache, k_scale, v_scale);
     }
 }
 

@@ -44,3 +44,28 @@ def test_either_side_of_the_line(kv_dtype, H_k, T):
         torch.cuda.synchronize()
         got.append(c)
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("kv_dtype,d,H_k,T", [("e4m3", 128, 40, 3865), ("e4m3", 128, 40, 3866), ("e5m2", 64, 40, 12755),
+                                              ("e5m2", 64, 40, 12756), ("fp16", 128, 40, 2929), ("fp16", 128, 40, 2930),
+                                              ("fp16", 64, 24, 9766)])
+def test_either_side_of_a_large_call(kv_dtype, d, H_k, T):
+    """... 120 MB read and written (one byte a code, 64 dims: 200 MB): one call against calls of 32 tokens, a
+    wavefront per row; runs of every alignment, single tokens, tokens that are filtered."""
+    kv = {"e4m3": coopt.COOPT_KV_E4M3, "e5m2": coopt.COOPT_KV_E5M2, "fp16": coopt.COOPT_KV_FP16}[kv_dtype]
+    NB, fp8 = T // 16 + 40, kv_dtype != "fp16"
+    shape = coopt.Shape(1, H_k, H_k, d, 16, NB, NB, kv, 1.0)
+    rng = np.random.default_rng(T)
+    slots = np.concatenate([np.arange(5, 5 + T // 2), T // 2 + 8 + rng.permutation(T // 4),
+                            3 * T // 4 + 27 + np.arange(T - T // 2 - T // 4)])
+    slots[rng.permutation(T)[:T // 8]] = -1
+    k, v = (torch.randn(T, H_k, d, device="cuda").half() for _ in range(2))
+    ds, got = dev(slots), []
+    for step in (T, 32):
+        c = [torch.zeros(NB, H_k, 16 * d * (1 if fp8 else 2), dtype=torch.uint8, device="cuda") for _ in range(2)]
+        c += [torch.zeros(NB, H_k, 16, device="cuda") for _ in range(2)] if fp8 else []
+        for i in range(0, T, step):
+            (coopt.kv_cache_write_fp8 if fp8 else coopt.kv_cache_write_fp16)(k[i:i + step], v[i:i + step], ds[i:i + step], *c, shape)
+        torch.cuda.synchronize()
+        got.append(c)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
