@@ -1,7 +1,8 @@
 // How a prefill launch deals the query tiles of a batch to its workgroups: the host's plan, the order
 // of a pair's tiles, and what the workgroup of a given number takes.  Plain C++ but for wave_uniform (a
-// value that is the same in every lane) and the two function qualifiers, so that a host program which
-// defines those can walk a launch and look at every index that the kernel stores through.
+// value that is the same in every lane), the two function qualifiers and a reciprocal that only device
+// code takes from its builtin, so that a host program which defines the former can walk a launch
+// and look at every index that the kernel stores through.
 #pragma once
 
 #include <stddef.h>
@@ -232,8 +233,9 @@ struct PrefillShare {
 };
 
 // The pair's workgroups by the length of their streams: whole streams from the last rows down, and the
-// split ones where their length has its place (prefill_ahead).  t: the sequence's tokens, C of them new rows, total_tiles tiles.  C comes from the device and may be more than the
-// host was told: tiles beyond those that the launch and its workspace were sized for are left out.
+// split ones where their length has its place (prefill_ahead).  t: the sequence's tokens, C of them new
+// rows, total_tiles tiles.  C comes from the device and may be more than the host was told: tiles
+// beyond those that the launch and its workspace were sized for are left out.
 __device__ __forceinline__ PrefillShare prefill_share(const PrefillDeal& a, int turn, int t, int C, int total_tiles)
 {
     const int num_split = a.split * a.split_blocks;
