@@ -104,6 +104,9 @@ struct PrefillStage {
 // fp16, in row 1 the remainder (the producers write both).  A 16x16x32 product takes the weight operand of
 // a 32x32x16 one as it is, with columns 16..31 as further k-slots, for which the operand has the same in
 // rows 2 and 3; two such products per group accumulate both tiles' sums instead of sixteen vector additions.
+// Column 16 + n's weights are thus multiplied by zeros for column n, and zero times NaN is NaN: a wave that ends
+// with such a sum goes over its keys once more for the sums alone, in additions that keep columns apart.  (To
+// keep NaN out of the products, group by group, costs every launch 1.5 % to 4.5 % of 8 x 512 rows over 8192 tokens.)
 //
 // v_scale reaches the weight through the exponent: the producers leave lv = log2(v_scale) beside
 // k_scale, the score of a token is z' = s * ksc + lv in
@@ -674,7 +677,58 @@ prefill_chunk_kernel(const PrefillArgs a)
     if (!active) return;
     // the sums of the lane's column: rows 0 and 1 of lacc, rows 2 and 3 for columns 16..31
     const float sum_a = __shfl(lacc[0] + lacc[1], n), sum_b = __shfl(lacc[2] + lacc[3], n);
-    const float L = (second ? sum_b : sum_a) * 256.0f;
+    // (a NaN weight in either column of a lane is in all four of its registers; asked of those, not of the
+    // sums, whose way through LDS the hot path need not wait for here)
+    const bool once_more = __builtin_amdgcn_ballot_w64(lacc[0] != lacc[0]) != 0;
+    float again = 0.0f;
+    if (__builtin_expect(once_more, 0)) {
+        // The weights once more, under the last reference, straight from the cache: lane 32h + r brings token r of a
+        // group, dims 16k + 8h ..
+        // (The launch's arguments, and what follows from them, once more, too: kept through the stream they push its
+        // scalars out of their registers, 1.5 % of three fresh prompts.)
+        const PrefillArgs* args = (const PrefillArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(args));
+        const PrefillArgs& a = *args;
+        const int* bt = a.block_tables + (size_t)a.kv_heads.quotient(pair) * a.max_blocks;
+        const int stages = (((nblk + 1) >> 1) + GPS - 1) / GPS;
+        constexpr int ES = FP8 ? 1 : 2;
+        const float mm = m - kPShift, scale = fabsf(a.scale_log2e);
+#pragma unroll 1
+        for (int gi = parts == 1 ? 0 : quotient(stages * part, parts) * GPS; gi < g_end && 2 * gi * kBlock < my_max; ++gi) {
+            auto tile_of = [&](int b) {                        // (no read beyond the table or the pool)
+                const int tile = bt[min(min(2 * gi + b + 1, nblk), a.max_blocks) - 1] * a.H_k + g;
+                return (uint32_t)tile < (uint32_t)a.pool_tiles ? tile : 0;
+            };
+            const uint8_t* row = a.cv.k_cache + (size_t)tile_of((lane >> 4) & 1) * (kBlock * HEAD_DIM * ES) + 16 * n;
+            floatx16 z = {};
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) {
+                half8_t kop;
+                if constexpr (FP8) {
+                    const uint2 x = *reinterpret_cast<const uint2*>(row + 256 * k + 8 * h);
+                    kop = fp8x8_to_half8<KV>(x.x, x.y);
+                } else {
+                    kop = *reinterpret_cast<const half8_t*>(row + 512 * k + 256 * h);
+                }
+                z = mfma_32x32x16(kop, qop[k], z);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const size_t at = (size_t)tile_of(j >> 1) * kBlock + 8 * (j & 1) + 4 * h;
+                const int vis = limit - 2 * gi * kBlock - 8 * j - 4 * h;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float vs = FP8 ? a.cv.v_scale[at + i] : 1.0f;
+                    const float x = FP8 ? __builtin_fmaf(z[4 * j + i], a.cv.k_scale[at + i] * scale, __builtin_amdgcn_logf(vs))
+                                        : z[4 * j + i] * scale;
+                    const float w = (float)(half_t)__builtin_amdgcn_exp2f(x - mm);
+                    again += i < vis ? (vs > 0.0f ? w * __builtin_amdgcn_rcpf(vs) : w * 0.0f) : 0.0f;
+                }
+            }
+        }
+        again += __shfl_xor(again, 32);
+    }
+    const float L = once_more ? again : (second ? sum_b : sum_a) * 256.0f;
     // The rows leave through LDS, so that a store instruction writes whole rows: a lane's registers are
     // 4 dims of 8 each (register 4j + i of acc[c]: dim 32c + 8j + 4h + i),
     // 16 bytes of 32 rows an instruction.  Every wave has a slot of its own: of the last stage only its
