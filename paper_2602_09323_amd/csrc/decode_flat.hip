@@ -1145,7 +1145,8 @@ pair_decode_kernel(const FlatArgs a)
         loader.issue(r[1], (b + 1 < nb ? __builtin_amdgcn_readlane(ids, 2 * ee + 1) : 0) * a.H_k + g, e < count && b + 1 < nb);
     };
     __shared__ __attribute__((aligned(16))) unsigned char sums[kWaves][HEAD_DIM / 16 * 1024 + 512];
-    float m = -INFINITY, l = 0.0f;
+    // (finite, not -inf: all scores of a wavefront's first group may be -inf, which is then often its only one)
+    float m = -0x1.fffffep127f, l = 0.0f;
     floatx4 acc[HEAD_DIM / 16];
 #pragma unroll
     for (int c = 0; c < HEAD_DIM / 16; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1196,7 +1197,8 @@ pair_decode_kernel(const FlatArgs a)
         x[w] = __builtin_amdgcn_exp2f(x[w] - M);
         L += w < had ? *reinterpret_cast<const float*>(sums[w] + kML + 256 + 4 * lane) * x[w] : 0.0f;
     }
-    const float inv = t > 0 ? 1.0f / L : 0.0f;
+    // (a part without weights leaves zeros of weight zero)
+    const float inv = t > 0 && !(PARTS && L == 0.0f) ? 1.0f / L : 0.0f;
     const size_t at = ((size_t)pair * a.G + n) * (PARTS ? a.max_slots : 1) + part;
 #pragma unroll
     for (int c0 = 0; c0 < HEAD_DIM / 16; c0 += kWaves) {

@@ -119,6 +119,27 @@ def test_in_parts(oracle_mod, kv_dtype, H_q, H_k, d, lens, max_blocks, step):
     assert_close(out.cpu().numpy().astype(np.float64), ref, f"parts {kv_dtype} {H_q}/{H_k} x {d}")
 
 
+@pytest.mark.parametrize("lens,max_blocks", [([33, 65, 257, 20], 17), ([1025, 129, 33], 130)], ids=["whole", "parts"])
+def test_infinite_key(oracle_mod, lens, max_blocks):
+    """Every sequence's last key has an infinite element: no weight for the heads whose query is negative there,
+    also where a wavefront sees no other token; no number for the others."""
+    H_q, H_k, d = 10, 2, 64
+    w = _workload("fp16", H_q, H_k, d, lens, max_blocks)
+    cache = oracle_fill(oracle_mod, w)
+    for s, t in enumerate(lens):                        # K blocks: [dim / 8][token][8]
+        cache[0].reshape(w.NB, H_k, d // 8, 16, 8)[w.block_tables[s, (t - 1) // 16], :, 3, (t - 1) % 16, 2] = np.inf
+    w.q[:, :, 26] = np.where(np.arange(H_q) % 2, 1, -1)
+    with np.errstate(invalid="ignore"):
+        ref = _oracle(oracle_mod, w, cache, "fp16")
+    shape, out = shape_of(w), _out(w)
+    ws = torch.full((coopt.decode_workspace_bytes(shape) // 4,), float("nan"), device="cuda")
+    coopt.paged_gqa_decode(dev(w.q.view(np.uint16)), *cache_to_dev(cache), dev(w.block_tables), dev(w.context_lens), out, ws, shape)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.isnan(ref[:, 1::2]).all() and np.isnan(got[:, 1::2]).all()
+    assert_close(got[:, ::2], ref[:, ::2], f"infinite keys, {max_blocks} blocks")
+
+
 @pytest.mark.parametrize("S,H_q,H_k,d,max_blocks,one_launch", [(32, 8, 8, 128, 33, True), (33, 8, 8, 128, 33, False),
                                                                (2, 4, 2, 128, 33, True), (2, 4, 2, 128, 34, False),
                                                                (2, 4, 2, 64, 64, True), (2, 4, 2, 64, 65, False)])
