@@ -261,8 +261,10 @@ int coopt_paged_gqa_decode_merge(const int32_t* context_lens, const void* worksp
  * else.  The rows are stored into the cache by extra wavefronts of the second (merge) launch.  Without a
  * plan, short contexts (256 pairs at most, a block table that bounds a pair's K and V at 140 000
  * bytes) are one launch that leaves the workspace alone, here as in coopt_paged_gqa_decode and
- * coopt_paged_gqa_decode_noalloc, and small batches (5120 two-block groups by the table) cut every pair
- * into equal numbers of groups.
+ * coopt_paged_gqa_decode_noalloc, and small batches (256 pairs, 512 of 64 dims, and at most 5120
+ * two-block groups by the table) cut every pair into equal numbers of groups.  Which form runs follows
+ * from the shape alone, its max_blocks_per_seq above all and not the lengths, and so do the last bits of
+ * `out`: a table far wider than the contexts keeps the balanced form.
  *   k, v          device, fp16 [num_seqs][num_kv_heads][head_dim]: token s is the LAST token of
  *                 sequence s, i.e. position context_lens[s]-1
  *   slot_mapping  device, int64 [num_seqs]: negative = write nothing for this sequence and attend

@@ -1075,7 +1075,7 @@ constexpr int kPairWaves = 8;
 constexpr int kPartWaves = 4;
 constexpr int kPairGroups = 32;         // two-block groups per wavefront: a lane for every block
 constexpr long long kPairBytes = 140000;    // of a pair's K and V, at most (pair_decode_fits)
-constexpr long long kPartsGroups = 5120;    // of all pairs, in parts (pair_parts)
+constexpr long long kPartsGroups = 5120;    // of all pairs, in parts, at most (pair_parts)
 constexpr long long kPairs = 256;           // a workgroup holds a CU
 
 //
@@ -1514,19 +1514,34 @@ bool pair_decode_fits(const coopt_shape* sh)
 }
 
 // Workgroups per pair of the form in parts, 0 where the balanced form is to run.  The line, in us a fused
-// step (balanced / in parts; 40 heads of 128 dims over 8, E4M3, unless said; groups: as many as the table holds):
-//   1 x 1789 tokens     (448 groups)  12.1 / 10.1      1 x 8000 (2000)               13.3 / 11.7
-//   4 x 298 .. 1789     (1792)        13.0 / 11.1      16 x 170 .. 1024 (4096)       15.2 / 14.0
-//   8 x 2500 (5056)                   17.6 / 15.4      8 x 416 .. 2500 (5056)        15.7 / 14.3
-//   8 x 4096 (8192)                   20.5 / 19.6      8 x 682 .. 4096 (8192)        16.5 / 17.1
-//   16 x 682 .. 4096    (16384)       23.0 / 24.7      fp16 over 40 heads, 2 x 666 .. 4000 (10000)  22.9 / 24.2
-// Beyond it equal shares of what the sequences really hold matter more than an early start.
+// step (balanced / in parts; 40 heads of 128 dims over 8, E4M3, unless said; groups: as many as the table holds;
+// ragged: evenly from a sixth of the length up):
+//   up to 64 pairs, four parts and more:
+//     1 x 1789 (448)  12.1 / 10.1      4 x 2048 (2048)  ragged 13.6 / 11.2     8 x 2048 (4096)  16.9 / 14.7, ragged 15.3 / 13.7
+//     8 x 2500 (5056)  17.6 / 15.4, ragged 15.5 / 14.5                         8 x 3200 (6400)  19.9 / 20.1, ragged 16.2 / 16.3
+//   up to 256:
+//     12 x 1344 (4032)  ragged 15.1 / 14.3     12 x 1696 (5088)  17.4 / 16.6, ragged 15.1 / 15.6
+//     16 x 1024 (4096)  ragged 14.9 / 14.1     28 x 576 (4032)   ragged 15.1 / 14.8
+//   ... one workgroup a pair, whose turns of four groups count:
+//     20 x 768 (24 groups a pair)  15.9 / 15.0, ragged 15.0 / 14.5             20 x 800 (25)  ragged 14.9 / 15.3
+//     fp16 over 40 heads, 4 x 640 (20)  17.4 / 16.0, ragged 15.4 / 15.0        4 x 800 (25)   ragged 16.0 / 16.8
+//   of 64 dims (32 heads over 8), whose workgroups share a CU:
+//     8 x 2496 (4992)  13.4 / 11.7, ragged 12.5 / 11.3                         fp16, 32 x 576 (4608)  14.5 / 13.2, ragged 12.9 / 12.0
+//     33 x 128 (264 pairs, 1056)  11.3 / 10.1   64 x 160 (512 pairs, 2560)  12.5 / 12.0, ragged 12.3 / 11.4
+//     40 x 512 (320 pairs, 5120)  14.4 / 14.9, ragged 12.8 / 13.4              96 x 32 (768 pairs)  12.9 / 13.6
+//   of 128 dims beyond 256 pairs, which a CU takes one after the other:
+//     33 x 256  14.3 / 17.9     128 x 64  17.3 / 29.2     480 x 32  41 / 90
+// Beyond the lines equal shares of what the sequences really hold matter more than an early start.
 static int pair_parts(const coopt_shape* sh, const FlatPlan& plan)
 {
-    const int pairs = sh->num_seqs * sh->num_kv_heads, groups = (sh->max_blocks_per_seq + 1) / 2;
-    if ((long long)pairs * groups > kPartsGroups) return 0;
-    const int chunks = (groups + kPartWaves - 1) / kPartWaves;
-    return std::max(1, std::min({chunks, (int)kPairs / pairs, flat_max_slots(sh, plan)}));
+    const long long pairs = (long long)sh->num_seqs * sh->num_kv_heads, groups = (sh->max_blocks_per_seq + 1) / 2;
+    const bool alone = sh->head_dim == 128;                    // a workgroup has its CU to itself
+    const long long most = pairs > kPairs ? kPartsGroups / 2 : alone && pairs > kPairs / 4 ? kPartsGroups * 4 / 5 : kPartsGroups;
+    if (pairs > (alone ? kPairs : 2 * kPairs) || pairs * groups > most) return 0;
+    const int each = std::max(1, (int)(kPairs / pairs));
+    if (alone && each == 1 && groups > 6 * kPartWaves) return 0;
+    const int chunks = ((int)groups + kPartWaves - 1) / kPartWaves;
+    return std::max(1, std::min({chunks, each, flat_max_slots(sh, plan)}));
 }
 
 template <bool PARTS>

@@ -92,7 +92,9 @@ PART_LENS = [0, 1, 17, 33, 127, 128, 129, 256, 257, 545, 900, 1025]
     ("e5m2", 32, 2, 64, PART_LENS, 130),                 # ten parts, two turns
     ("fp16", 10, 2, 64, PART_LENS, 66),
     ("fp16", 5, 1, 128, [3000, 1, 2999, 0, 1500], 188),
-    ("e4m3", 16, 16, 64, PART_LENS[1:] * 2, 66)])        # 352 pairs: more groups than the form takes
+    ("e4m3", 16, 16, 64, PART_LENS[1:] * 2, 66),         # 352 pairs: more groups than the form takes
+    ("e4m3", 16, 8, 64, [0, 1, 33, 150, 160, 17] * 10, 10),     # 480 pairs of 64 dims: one workgroup each, beyond the CUs
+    ("fp16", 8, 8, 64, [129, 0, 255, 31] * 9, 16)])
 def test_in_parts(oracle_mod, kv_dtype, H_q, H_k, d, lens, max_blocks, step):
     w = _workload(kv_dtype, H_q, H_k, d, lens, max_blocks)
     groups = len(lens) * H_k * ((max_blocks + 1) // 2)
@@ -117,6 +119,22 @@ def test_in_parts(oracle_mod, kv_dtype, H_q, H_k, d, lens, max_blocks, step):
                 assert np.array_equal(got.reshape(-1).view(np.uint8), want.reshape(-1).view(np.uint8)), name
     torch.cuda.synchronize()
     assert_close(out.cpu().numpy().astype(np.float64), ref, f"parts {kv_dtype} {H_q}/{H_k} x {d}")
+
+
+@pytest.mark.parametrize("S,H_q,H_k,d,max_blocks", [(33, 8, 8, 128, 6), (65, 8, 8, 64, 4), (40, 8, 8, 64, 18), (12, 8, 8, 128, 88),
+                                                    (20, 8, 8, 128, 50)])
+def test_beyond_the_line_of_parts(S, H_q, H_k, d, max_blocks):
+    """More pairs, groups or turns than the form in parts is the faster for: what the default plan, passed as a
+    plan, gives, bit for bit."""
+    w = _workload("e4m3", H_q, H_k, d, [(37 * s) % (16 * max_blocks) + 1 for s in range(S)], max_blocks)
+    shape, dcache = shape_of(w), alloc_dev_cache(w)
+    hip_write(w, dcache)
+    ws = torch.empty(coopt.decode_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    outs = [_out(w) for _ in range(2)]
+    for out, plan in zip(outs, (None, coopt.default_decode_plan())):
+        coopt.paged_gqa_decode(dev(w.q.view(np.uint16)), *dcache, dev(w.block_tables), dev(w.context_lens), out, ws, shape, plan=plan)
+    torch.cuda.synchronize()
+    assert torch.equal(*outs)
 
 
 @pytest.mark.parametrize("lens,max_blocks", [([33, 65, 257, 20], 17), ([1025, 129, 33], 130)], ids=["whole", "parts"])
