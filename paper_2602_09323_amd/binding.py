@@ -145,7 +145,8 @@ _native = None
 
 
 def _fast():
-    """The native entry points once the library is loaded, None until then or where they are not built."""
+    """The native entry points once the library is loaded, None until then or where they are not built for
+    this torch."""
     global _native
     if _native is None and isinstance(_lib, ctypes.CDLL):
         _native = _bind_native() or False
@@ -154,13 +155,23 @@ def _fast():
 
 def _bind_native():
     import importlib.util
+    import warnings
     if importlib.util.find_spec("._binding", __package__) is None:
         return None
     c = _th()._C
     device, raw = getattr(c, "_cuda_getDevice", None), getattr(c, "_cuda_getCurrentRawStream", None)
     if device is None or raw is None:
         return None
-    from . import _binding
+    # (it reads torch's tensors by the layout of the headers that it was compiled with)
+    try:
+        _binding = importlib.import_module("._binding", __package__)
+        why = f"it was built for torch {_binding.built_for}" if _binding.built_for != _torch.__version__ else None
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    if why is not None:
+        warnings.warn(f"the binding's native part is left out ({why}, this is torch {_torch.__version__}): every call goes "
+                      "through ctypes; run `python -m paper_2602_09323_amd.build`", RuntimeWarning, stacklevel=4)
+        return None
     names = ("kv_cache_write_fp8", "kv_cache_write_fp16", "paged_gqa_decode", "paged_gqa_decode_step",
              "decode_schedule_prepare", "paged_gqa_decode_scheduled", "paged_gqa_decode_partitioned",
              "paged_gqa_reduce", "paged_gqa_prefill_chunk_ws", "gather_cached_kv", "decode_workspace_bytes",

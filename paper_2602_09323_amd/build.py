@@ -58,6 +58,7 @@ def _build_binding() -> None:
     import torch
     root = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DCOOPT_TORCH_VERSION="{torch.__version__}"',
            "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(root, "include"),
            "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, BINDING_SOURCE), "-o", BINDING,

@@ -403,4 +403,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }
+// built_for: the torch whose headers these are.
+PyMODINIT_FUNC PyInit__binding()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", COOPT_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}
