@@ -1,5 +1,6 @@
 """Builds libcoopt_attn.so and the benchmark's libcoopt_probe.so (HIP, gfx950 only) in-tree with hipcc,
-and the Python binding's native part with g++.
+and the Python binding's native part with g++ and torch's headers.  The libraries need hipcc alone: where the
+native part does not compile, that is said and the binding's ctypes path takes its calls.
 
     python -m paper_2602_09323_amd.build [--force]
 
@@ -9,6 +10,7 @@ library lands beside the Python binding so that it travels with the source tree.
 from __future__ import annotations
 
 import concurrent.futures
+import importlib.metadata
 import os
 import subprocess
 import sys
@@ -24,6 +26,7 @@ SOURCES = ["kv_write.hip", "decode.hip", "decode_flat.hip", "prefill.hip", "gath
 PROBE_SOURCES = ["probe.hip"]
 BINDING = os.path.join(HERE, "_binding" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 BINDING_SOURCE = "binding_native.cpp"                    # host code: tensors to pointers, no kernel
+BINDING_STAMP = os.path.join(HERE, "_binding.built_for")   # the torch that it was last compiled against, or did not compile
 HEADERS = [os.path.join(CSRC, h) for h in ("common.hpp", "attn_tile.hpp", "kv_quant.hpp",
                                           "decode_internal.hpp", "launch_grid.hpp", "prefill_deal.hpp")] + [
     os.path.join(ROOT, "include", "coopt_attn.h"), os.path.join(ROOT, "include", "coopt_probe.h")]
@@ -54,6 +57,13 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _torch_version() -> str:
+    try:
+        return importlib.metadata.version("torch")
+    except importlib.metadata.PackageNotFoundError:
+        return "none"
+
+
 def _build_binding() -> None:
     import torch
     root = os.path.dirname(torch.__file__)
@@ -68,12 +78,27 @@ def _build_binding() -> None:
         raise RuntimeError(f"g++ failed for {BINDING_SOURCE}:\n{res.stderr}")
 
 
+def _try_binding() -> None:
+    if os.path.exists(BINDING):
+        os.remove(BINDING)                               # (one of older sources, if the compiler fails)
+    try:
+        _build_binding()
+    except (RuntimeError, OSError, ImportError) as e:
+        sys.stderr.write(f"the binding's native part was not built, ctypes takes its calls: {e}\n")
+    with open(BINDING_STAMP, "w") as f:
+        f.write(_torch_version())
+
+
 def needs_build() -> bool:
-    if not all(os.path.exists(p) for p in (LIB, PROBE_LIB, BINDING)):
+    """Whether a source is newer than what was made of it, or torch is another than the native part was made for."""
+    if not all(os.path.exists(p) for p in (LIB, PROBE_LIB, BINDING_STAMP)):
         return True
     newest = max(os.path.getmtime(p)
                  for p in [os.path.join(CSRC, s) for s in SOURCES + PROBE_SOURCES + [BINDING_SOURCE]] + HEADERS)
-    return min(os.path.getmtime(p) for p in (LIB, PROBE_LIB, BINDING)) < newest
+    if min(os.path.getmtime(p) for p in (LIB, PROBE_LIB, BINDING_STAMP)) < newest:
+        return True
+    with open(BINDING_STAMP) as f:
+        return f.read() != _torch_version()
 
 
 def build(force: bool = True) -> str:
@@ -82,7 +107,7 @@ def build(force: bool = True) -> str:
         return LIB
     os.makedirs(BUILD, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=6) as pool:
-        binding = pool.submit(_build_binding)
+        binding = pool.submit(_try_binding)
         objs = list(pool.map(_compile, SOURCES + PROBE_SOURCES))
         binding.result()
     for lib, n in ((LIB, objs[:len(SOURCES)]), (PROBE_LIB, objs[len(SOURCES):])):

@@ -1,5 +1,6 @@
 """The binding's native part is an accelerator: where it cannot be loaded, or was built for another torch, the
 ctypes path takes every call.  (No GPU needed.)"""
+import subprocess
 import sys
 import types
 
@@ -59,3 +60,29 @@ def test_does_not_import(unbound, monkeypatch):
     monkeypatch.setattr(sys, "meta_path", [Finder] + sys.meta_path)
     with pytest.warns(RuntimeWarning, match="undefined symbol"):
         assert binding._fast() is None
+
+
+def test_libraries_need_no_torch_headers(monkeypatch, tmp_path, capsys):
+    """The C libraries are linked, and count as built, where the native part does not compile; another torch does not."""
+    from paper_2602_09323_amd import build
+    empty = tmp_path / "empty.cpp"
+    empty.write_text("")
+
+    def compiled(src):
+        obj = str(tmp_path / (src + ".o"))
+        subprocess.run(["g++", "-fPIC", "-c", str(empty), "-o", obj], check=True)
+        return obj
+
+    def fails():
+        raise RuntimeError("no headers")
+    for name in ("LIB", "PROBE_LIB", "BINDING", "BINDING_STAMP", "BUILD"):
+        monkeypatch.setattr(build, name, str(tmp_path / name), raising=False)
+    monkeypatch.setattr(build, "_compile", compiled)
+    monkeypatch.setattr(build, "_build_binding", fails)
+    (tmp_path / "BINDING").write_text("of older sources")
+    assert build.build(force=True) == str(tmp_path / "LIB")
+    assert (tmp_path / "LIB").exists() and (tmp_path / "PROBE_LIB").exists() and not (tmp_path / "BINDING").exists()
+    assert "ctypes takes its calls: no headers" in capsys.readouterr().err
+    assert not build.needs_build()
+    monkeypatch.setattr(build, "_torch_version", lambda: "0.0.0")
+    assert build.needs_build()
