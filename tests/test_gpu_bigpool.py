@@ -93,10 +93,10 @@ def test_gather(big, oracle_mod):
         assert np.array_equal(got.cpu().numpy().view(np.uint16), want.view(np.uint16))
 
 
-def test_fused_step(oracle_mod):
-    lens = [300, 1025, 47, 1]
+@pytest.mark.parametrize("lens,max_blocks", [([300, 1025, 47, 1], 80), ([300, 528, 47, 1], 33)], ids=["parts", "one launch"])
+def test_fused_step(oracle_mod, lens, max_blocks):
     w = workloads.make_custom("bigstep", seed=72, S=len(lens), H_q=40, H_k=8, d=128, B=16, NB=NB_BIG,
-                              context_lens=lens, max_blocks=80)
+                              context_lens=lens, max_blocks=max_blocks)
     cache = oracle_fill(oracle_mod, w)
     ref = oracle_mod.paged_gqa_decode(w.q, *cache, w.block_tables, w.context_lens, H_q=w.H_q, H_k=w.H_k,
                                       d=w.d, B=w.B, softmax_scale=w.softmax_scale)
@@ -111,6 +111,7 @@ def test_fused_step(oracle_mod):
                                 dev(w.context_lens), out, ws, shape)
     torch.cuda.synchronize()
     assert_close(out.cpu().numpy().astype(np.float64), ref, "big pool fused step")
+    assert_close(hip_decode(w, dcache), ref, "big pool decode of the same")
     used = torch.from_numpy(w.block_tables[w.block_tables >= 0].astype(np.int64)).cuda()
     for name, host, devt in zip(("k_cache", "v_cache", "k_scale", "v_scale"), cache, dcache):
         assert np.array_equal(devt[used].cpu().numpy().reshape(len(used), -1).view(np.uint8),

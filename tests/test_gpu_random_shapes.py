@@ -88,6 +88,12 @@ def _decode_case(orc, seed):
         out = new_out()
         planned.paged_gqa_decode(q, *full, bt, dl, out, workspace, shape)
         assert_close(host(out), ref, f"decode, workspace={workspace is not None}, {what}")
+    # (without a plan the library chooses the form by the shape)
+    own_ws = torch.full((max(16, coopt.decode_workspace_bytes(shape)) // 4,), float("nan"), device="cuda")
+    for workspace in (own_ws, None):
+        out = new_out()
+        coopt.paged_gqa_decode(q, *full, bt, dl, out, workspace, shape)
+        assert_close(host(out), ref, f"decode without a plan, workspace={workspace is not None}, {what}")
     sched = torch.zeros(planned.decode_schedule_bytes(shape), dtype=torch.uint8, device="cuda")
     planned.decode_schedule_prepare(bt, dl, None, sched, shape)
     out = new_out()
@@ -105,11 +111,13 @@ def _decode_case(orc, seed):
     whole = alloc_dev_cache(w, fill_byte=0)
     hip_write(w, whole)
     want_bytes = dev_cache_to_host(w, whole)
-    for prepared in (False, True):
+    for prepared in (False, True, "no plan"):
         dcache = alloc_dev_cache(w, fill_byte=0)
         hip_write(w, dcache, idx=before)
         out = new_out()
-        if prepared:
+        if prepared == "no plan":
+            coopt.paged_gqa_decode_step(k_new, v_new, dslots, q, *dcache, bt, dl, out, own_ws, shape)
+        elif prepared:
             planned.decode_schedule_prepare(bt, dl, dslots, sched, shape)
             planned.paged_gqa_decode_scheduled(k_new, v_new, dslots, q, *dcache, dl, out, ws, sched, shape)
         else:

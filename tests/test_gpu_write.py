@@ -142,9 +142,10 @@ def test_explicit_skip_set(oracle_mod, kv_dtype):
 
 
 @pytest.mark.parametrize("kv_dtype", ["e4m3", "fp16"])
-@pytest.mark.parametrize("d,H_k", [(128, 2), (64, 3)])
+@pytest.mark.parametrize("d,H_k", [(128, 41), (64, 42), (128, 2), (64, 3)])
 def test_bulk_calls_with_every_slot_pattern(oracle_mod, d, H_k, kv_dtype):
-    """Calls of 64 tokens and more take the bulk kernel, whose V stores depend on how four
+    """Calls of 64 tokens and more and enough rows (here: of the 41 or 42 heads; few heads stay with a
+    wavefront per row) take the bulk kernel, whose V stores depend on how four
     consecutive tokens' slots lie: aligned runs, runs that start off a multiple of four, runs cut
     by skipped tokens, slots scattered at random -- all against the oracle, and the same tokens
     again through calls small enough for the row kernel."""
@@ -176,7 +177,7 @@ def test_bulk_calls_with_every_slot_pattern(oracle_mod, d, H_k, kv_dtype):
     for name, slots in patterns.items():
         host, devc = _roundtrip(w)
         o_write(w.k_ctx, w.v_ctx, slots, *(host if fp8 else host[:2]), H_k=H_k, d=d, B=16)
-        d_write(dk, dv, dev(slots), *(devc if fp8 else devc[:2]), shape)       # one bulk call
+        d_write(dk, dv, dev(slots), *(devc if fp8 else devc[:2]), shape)       # one call
         torch.cuda.synchronize()
         _compare_caches(w, host, devc, f"bulk {kv_dtype} d={d}: {name}")
         _, devr = _roundtrip(w)
@@ -188,9 +189,9 @@ def test_bulk_calls_with_every_slot_pattern(oracle_mod, d, H_k, kv_dtype):
 
 
 @pytest.mark.parametrize("kv_dtype", ["e4m3", "e5m2", "fp16"])
-@pytest.mark.parametrize("d,H_k", [(128, 3), (64, 2)])
+@pytest.mark.parametrize("d,H_k", [(128, 41), (64, 42)])
 def test_bulk_windows_equal_rows(d, H_k, kv_dtype):
-    """The bulk kernel takes windows of 13, 29 or 61 tokens (cache type and head size) and completes the
+    """The bulk kernel (64 tokens of 41 heads are enough rows for it) takes windows of 13, 29 or 61 tokens (cache type and head size) and completes the
     last quad of a window from the next one's rows; its quotients come from a reciprocal.  Call lengths
     around the windows' edges, runs from every slot offset in ragged pieces with lone tokens between,
     over every kind of fp16 pattern (zeros of both signs, subnormals, infinities, NaN): the bytes of the
@@ -222,6 +223,7 @@ def test_bulk_windows_equal_rows(d, H_k, kv_dtype):
                 r[1::5] &= 0x8fff                   # ... of small values, subnormals among them
                 r[2::5, :, ::3] = 0x8000
                 r[3] = 0x8000                       # ... of nothing but zeros
+            assert T * H_k > 2560                   # of a one-byte cache (fp16: 1536)
             k, v, ds = dev(rows[0]), dev(rows[1]), dev(slots)
             got = []
             for step in (T, 40):                    # one bulk call; calls that take the row kernel
