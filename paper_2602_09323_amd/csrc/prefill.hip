@@ -949,11 +949,10 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
 
     const PrefillLaunchPlan lp(sh, max_chunk_len, workspace != nullptr);
     const int pairs8 = lp.pairs8, a_per_pair = lp.a_per_pair, b_per_pair = lp.b_per_pair;
-    const bool split = lp.parts >= 2;                 // (and no merge if the table holds no sequence long enough)
-    const int split_per_pair = lp.split_per_pair();
-    a.set(lp, sh->num_seqs * sh->num_kv_heads);
+    a.set(lp, sh->num_seqs * sh->num_kv_heads, (long long)sh->max_blocks_per_seq * kBlock);
     a.part = (float*)workspace;
-    const bool merge = split && a.whole_tokens < (long long)sh->max_blocks_per_seq * kBlock;
+    const bool split = a.split >= 2;                  // (the table may hold no sequence long enough)
+    const int split_per_pair = a.split * a.split_blocks;
     // Turn by turn, so that the longest streams of all pairs start first and the launch ends evenly,
     // while the streams of all of an XCD's pairs can share its 4 MB L2; else pair after pair, whose
     // workgroups then read their stream together.  (8 pairs of 2.3 MB an XCD: 760 us a pass by
@@ -985,7 +984,7 @@ static int prefill_chunk(const void* q, const void* k_cache, const void* v_cache
         hipLaunchKernelGGL((prefill_chunk_kernel<D, KV, TILES, BIG>),                                  \
                            dim3((unsigned)((long long)pairs8 * (a_per_pair + split_per_pair))), block, lds, \
                            stream, a);                                                              \
-        if (merge)                                                                                  \
+        if (split)                                                                                  \
             launch_split_merge<D>(a, sh->num_seqs, stream);                                         \
     } while (0)
 #define COOPT_PREFILL(D, KV, BIG)                                                                   \

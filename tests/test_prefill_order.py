@@ -1,7 +1,9 @@
 """The order of a prefill launch's workgroups over sequences of different lengths (csrc/prefill_deal.hpp,
 compiled here for the CPU): the workgroup of every rank, found as the kernel finds it, takes a turn of its
 own; every turn that has tiles is taken and none that has not; lengths never grow by more than the one
-stage that the split streams' rounded length may be off.  And the quotients that the deal is made of."""
+stage that the split streams' rounded length may be off.  Where split streams run whole after all,
+the workgroups without work lie behind all others, and where every sequence's do there are none.  And the quotients that the
+deal is made of."""
 import subprocess
 from pathlib import Path
 
@@ -60,6 +62,15 @@ static void launch(const PrefillDeal& a, int G, int H_k, int nr, int per_pair, i
             for (int turn = 0; turn < per_pair; ++turn) expected += stages_of(a, turn, t[s], c, G, wg_tiles) > 0;
         }
         auto total = [&](int l) { int n = 0; for (auto& i : items) n += i.at_least(l); return n; };
+        // (a workgroup with work in every second or fourth place is one or two shader engines' work)
+        for (int p = 0; p < a.xcd_pairs; ++p) {
+            const int pair = 8 * p + xcd;
+            if (pair >= a.num_pairs || a.split < 2 || C[seq[p]] <= 0 || !prefill_runs_whole(a, t[seq[p]])) continue;
+            for (int turn = 0; turn < per_pair; ++turn) {
+                const PrefillShare s = prefill_share(a, turn, t[seq[p]], C[seq[p]], G * ((C[seq[p]] + 15) / 16));
+                CHECK((s.part > 0) == (turn >= a.blocks_per_pair + a.split_blocks));
+            }
+        }
         std::set<std::pair<int, int>> taken;
         int previous = 1 << 30;
         for (int rank = 0; rank < a.xcd_pairs * per_pair; ++rank) {
@@ -127,6 +138,14 @@ int main()
                             int bits = 0;
                             while ((1 << bits) <= (longest + kPrefillStageTokens - 1) / kPrefillStageTokens) ++bits;
                             launch(a, hh[0] / hh[1], hh[1], lp.nr, lp.a_per_pair + lp.split_per_pair(), bits, C, t);
+                            if (lp.parts > 1) {
+                                const int line = a.whole_tokens;
+                                a.set(lp, S * hh[1], line);
+                                CHECK(line == 0 || (a.split == 1 && a.split_blocks == lp.split_per_pair() / lp.parts));
+                                launch(a, hh[0] / hh[1], hh[1], lp.nr, lp.a_per_pair + a.split * a.split_blocks, bits, C, t);
+                                a.set(lp, S * hh[1], line + 1LL);
+                                CHECK(a.split == lp.parts);
+                            }
                             if (lp.parts < 2 && lp.b_per_pair) {
                                 a.set_rest(lp);
                                 launch(a, hh[0] / hh[1], hh[1], 1, lp.b_per_pair, bits, C, t);
