@@ -109,10 +109,6 @@ __device__ __forceinline__ floatx4 mfma_16x16x32(half8_t a, half8_t b, floatx4 c
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ floatx4 mfma_16x16x16(half4_t a, half4_t b, floatx4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0);
-}
 
 // Inclusive prefix sum over the 64 lanes on the vector ALU (DPP row shifts, then the two row
 // broadcasts that carry a row's total into the following rows); no LDS round trips.

@@ -375,7 +375,9 @@ constexpr long long kLargeWriteBytes = kIsFp8<KV> && HEAD_DIM == 64 ? 200000000 
 //   E4M3       3.4 / 2.5        4.4 / 2.5   3.4 / 2.9   4.8 / 2.9    3.5 / 3.8   5.2 / 3.9
 //   fp16       2.8 / 2.1        3.0 / 2.1   2.7 / 2.9   3.7 / 2.8    3.0 / 4.0   5.4 / 3.9
 // and 40 heads: E4M3 64 tokens 3.5 / 3.3 and 4.9 / 3.2, 96 tokens 3.6 / 3.8 and 5.1 / 3.8; fp16 64 tokens
-// 3.0 / 3.2 and 3.9 / 3.1; 128 tokens of 8 heads 2.8 / 2.3 and 3.2 / 2.3.
+// 3.0 / 3.2 and 3.9 / 3.1; 128 tokens of 8 heads 2.8 / 2.3 and 3.2 / 2.3.  64 dims, whose rows are half as
+// long, at both ends of the line: E4M3, 8 heads 64 tokens 3.6 / 2.7 and 4.8 / 2.7, 320 tokens 3.6 / 3.1 and 4.9 / 3.1; fp16
+// 64 tokens 2.9 / 2.3 and 3.2 / 2.3, 192 tokens 2.9 / 2.5 and 3.4 / 2.5.
 constexpr int kBulkWriteTokens = 64;
 template <int KV> constexpr long long kRowWriteRows = kIsFp8<KV> ? 2560 : 1536;
 template <int KV>

@@ -148,7 +148,7 @@ int main(int argc, char** argv)
                                     if (tail) CHECK(whole == 0 && parts == ((int)i < w.limit + w.cap ? w.parts : 0));
                                     else if (C[p / hh[1]] <= announced) CHECK(whole == 1 && parts == 0);
                                     else CHECK(whole <= 1 && parts == 0);
-                                    // vnorm, and with it the rounding of a tile, is its workgroup's
+                                    // (the same neighbours: when their references are raised, and so the rounding, depends on them)
                                     if (!tail && whole) CHECK(w.group[p][i] == plain.group[p][i]);
                                 }
                         }
