@@ -264,7 +264,9 @@ int coopt_paged_gqa_decode_merge(const int32_t* context_lens, const void* worksp
  * coopt_paged_gqa_decode_noalloc, and small batches (256 pairs, 512 of 64 dims, and at most 5120
  * two-block groups by the table) cut every pair into equal numbers of groups.  Which form runs follows
  * from the shape alone, its max_blocks_per_seq above all and not the lengths, and so do the last bits of
- * `out`: a table far wider than the contexts keeps the balanced form.
+ * `out`: a table far wider than the contexts keeps the balanced form.  In the one launch the new rows are
+ * stored beside the reads of other sequences, so none of these may have a position that the call writes among
+ * its own tokens (in two launches such a sequence reads what was there before, not what the two calls give).
  *   k, v          device, fp16 [num_seqs][num_kv_heads][head_dim]: token s is the LAST token of
  *                 sequence s, i.e. position context_lens[s]-1
  *   slot_mapping  device, int64 [num_seqs]: negative = write nothing for this sequence and attend
