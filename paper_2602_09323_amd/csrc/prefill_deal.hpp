@@ -141,7 +141,7 @@ struct PrefillDeal {
     int32_t split_blocks;     // runs of 16 tiles per pair they cover
     int32_t tail_cap;         // tiles per pair they cover (sizes the workspace)
     int32_t whole_tokens;     // sequences up to this length have their split streams run whole after all
-    Divisor pairs_of_xcd, whole_of_pair, split_of_part, split_parts, blocks_of_part;     // (at least 1 each)
+    Divisor pairs_of_xcd, whole_of_pair, rest_of_pair, split_parts, blocks_of_part;     // (at least 1 each)
 
     // The first launch of a plan (its only one but for a plan's half-size workgroups).  most_tokens: no
     // sequence is longer.
@@ -185,10 +185,10 @@ struct PrefillDeal {
     }
     void set_divisors()
     {
-        const int of_part = xcd_pairs * split_blocks;
+        const int rest = (split - 1) * split_blocks;
         pairs_of_xcd = Divisor(xcd_pairs > 0 ? xcd_pairs : 1);
         whole_of_pair = Divisor(blocks_per_pair > 0 ? blocks_per_pair : 1);
-        split_of_part = Divisor(of_part > 0 ? of_part : 1);
+        rest_of_pair = Divisor(rest > 0 ? rest : 1);
         split_parts = Divisor(split > 0 ? split : 1);
         blocks_of_part = Divisor(split_blocks > 0 ? split_blocks : 1);
     }
@@ -196,19 +196,21 @@ struct PrefillDeal {
 
 // The pair of workgroup `wg`, and `turn`: which of the pair's workgroups it is, longest stream first.
 // All workgroups of a pair sit on one XCD (ids go round-robin over 8 XCDs).  By pair: an XCD's
-// whole-stream workgroups pair after pair, then its split ones, pair after pair of one part (which read the
-// same run) and part after part; otherwise turn after turn of all its pairs.  A pair >= num_pairs is none.
+// whole-stream workgroups pair after pair, then of its split ones as many as there would be of whole streams
+// (prefill_share), then the rest of them; otherwise turn after turn of all its pairs.  A pair >= num_pairs is none.
 __device__ __forceinline__ int prefill_pair(const PrefillDeal& a, unsigned wg, int& turn)
 {
     const int k8 = wg >> 3;
     const int whole = a.xcd_pairs * a.blocks_per_pair;           // whole-stream workgroups per XCD
     int xcd_pair;
     if (a.by_pair) {
-        const int part = k8 < whole ? 0 : a.split_of_part.quotient(k8 - whole);
-        const int k = k8 < whole ? k8 : k8 - whole - part * a.xcd_pairs * a.split_blocks;
-        const int per = k8 < whole ? a.blocks_per_pair : a.split_blocks;
-        xcd_pair = k8 < whole ? a.whole_of_pair.quotient(k) : a.blocks_of_part.quotient(k);
-        turn = k - xcd_pair * per + (k8 < whole ? 0 : a.blocks_per_pair + part * a.split_blocks);
+        const int first = whole + a.xcd_pairs * a.split_blocks;
+        const int k = k8 < whole ? k8 : k8 < first ? k8 - whole : k8 - first;
+        Divisor per = a.rest_of_pair;
+        if (k8 < first) per = a.blocks_of_part;
+        if (k8 < whole) per = a.whole_of_pair;
+        xcd_pair = per.quotient(k);
+        turn = k - xcd_pair * (int)per.d + (k8 < whole ? 0 : a.blocks_per_pair + (k8 < first ? 0 : a.split_blocks));
     } else {
         turn = a.pairs_of_xcd.quotient(k8);
         xcd_pair = k8 - turn * a.xcd_pairs;
@@ -241,27 +243,28 @@ struct PrefillShare {
 
 // The pair's workgroups by the length of their streams: whole streams from the last rows down, and the
 // split ones where their length has its place (prefill_ahead): all parts of a block's stream one after the
-// other (by pair: part after part), but where whole streams run after all, those of the first parts, and the
-// workgroups that have nothing to do behind everything.  (Ids go round-robin over an XCD's four shader engines:
-// with work in every second or fourth alone, two engines or one had all of it: 8 x 352 rows behind 1500 tokens
-// of a table for 7400 took 236 us, so 132; 2 x 777 of 64 dims behind 4000, 199 and 123.)  t: the sequence's tokens, C of them new
-// rows, total_tiles tiles.  C comes from the device and may be more than the host was told: tiles
+// other, but where whole streams run after all, first the workgroups that have nothing to do, then those of
+// the first parts (by pair the other way round, which puts the latter of all pairs together).  Ids go
+// round-robin over an XCD's four shader engines, so with work in every second or fourth alone two engines or
+// one had all of it: 8 x 352 rows behind 1500 tokens of a table for 7400 took 228 us, so 129; 2 x 777 of 64
+// dims behind 4000, 196 and 113.  (Idle ones behind everything instead: 3 fresh prompts of 301 to 1777 rows,
+// the short ones whole, 48.7 against 44.6 us, since short streams then start ahead of long ones.)
+// t: the sequence's tokens, C of them new rows, total_tiles tiles.  C comes from the device and may be more than the host was told: tiles
 // beyond those that the launch and its workspace were sized for are left out.
 __device__ __forceinline__ PrefillShare prefill_share(const PrefillDeal& a, int turn, int t, int C, int total_tiles)
 {
-    const bool whole = prefill_runs_whole(a, t);
-    const int ahead = wave_uniform(prefill_ahead(a, t, C)), live = (whole ? 1 : a.split) * a.split_blocks;
+    const int num_split = a.split * a.split_blocks;
+    const int ahead = wave_uniform(prefill_ahead(a, t, C));
     PrefillShare s;
-    const bool idle = turn >= a.blocks_per_pair + live;          // (whole after all: the other parts' workgroups)
-    s.tail = idle || (turn >= ahead && turn < ahead + live);
-    const int nth = idle ? turn - a.blocks_per_pair : s.tail ? turn - ahead : (turn < ahead ? turn : turn - live);
+    s.tail = turn >= ahead && turn < ahead + num_split;
+    const int nth = s.tail ? turn - ahead : (turn < ahead ? turn : turn - num_split);
     s.parts = s.tail ? a.split : 1;
-    const bool by_part = s.tail && (whole || a.by_pair);
+    const bool whole = s.tail && prefill_runs_whole(a, t);
     Divisor by = a.split_parts;
-    if (by_part) by = a.blocks_of_part;
+    if (whole) by = a.blocks_of_part;
     const int q = s.tail ? by.quotient(nth) : nth, rest = s.tail ? nth - q * (int)by.d : 0;
-    const int split_block = by_part ? rest : q;
-    s.part = by_part ? q : rest;                       // which run of the pair's stages is mine
+    const int split_block = whole ? rest : q;
+    s.part = !whole ? rest : a.by_pair ? q : s.parts - 1 - q;    // which run of the pair's stages is mine
     s.block = (s.tail ? a.split_blocks : a.blocks_per_pair) - 1 - split_block;
     s.base = s.tail ? a.tile_limit : a.tile_base;
     s.end = min(total_tiles, s.tail ? a.tile_limit + a.tail_cap : a.tile_limit);
@@ -314,11 +317,11 @@ struct TileOrder {
 // each kind longest stream first.
 struct PairItems {
     int whole, split;          // of either kind
-    int ahead, live, empty_whole, t, t_ctx, rows, tail_tokens, wg_tiles;    // live: turns of the latter, with and without tiles
+    int ahead, num_split, empty_whole, t, t_ctx, rows, tail_tokens, wg_tiles;
     bool runs;                 // behind the cut: runs of a stream, all about tail_tokens long (else whole streams)
     TileOrder order, tail;
     __device__ __forceinline__ PairItems(const PrefillDeal& a, int tokens, int C, int G, int wg_tiles_)
-        : whole(0), split(0), ahead(0), live(0), empty_whole(0), t(tokens), t_ctx(tokens - C),
+        : whole(0), split(0), ahead(0), num_split(a.split * a.split_blocks), empty_whole(0), t(tokens), t_ctx(tokens - C),
           rows((max(C, 1) + 15) / 16), tail_tokens(0), wg_tiles(wg_tiles_), runs(a.split > 1 && !prefill_runs_whole(a, tokens)),
           order(range(a.tile_base, min(G * rows, a.tile_limit), G)),
           tail(range(a.tile_limit, G * rows, G))
@@ -329,7 +332,6 @@ struct PairItems {
         whole = min(blocks(order.count()), a.blocks_per_pair);
         split = (runs ? a.split : 1) * blocks(tail.count());
         ahead = prefill_ahead(a, t, C);
-        live = (runs ? a.split : 1) * a.split_blocks;
         empty_whole = a.blocks_per_pair - whole;
         tail_tokens = a.split_parts.quotient(t);
     }
@@ -364,9 +366,9 @@ struct PairItems {
     __device__ __forceinline__ int turn(int stages, int k) const
     {
         const int w = whole_at_least(stages + 1), of_whole = whole_at_least(stages) - w;
-        if (k >= of_whole) return ahead + live - (split - split_at_least(stages + 1) - k + of_whole);
+        if (k >= of_whole) return ahead + num_split - (split - split_at_least(stages + 1) - k + of_whole);
         const int nth = empty_whole + w + k;
-        return nth < ahead ? nth : nth + live;
+        return nth < ahead ? nth : nth + num_split;
     }
 };
 

@@ -2,7 +2,7 @@
 compiled here for the CPU): the workgroup of every rank, found as the kernel finds it, takes a turn of its
 own; every turn that has tiles is taken and none that has not; lengths never grow by more than the one
 stage that the split streams' rounded length may be off.  Where split streams run whole after all,
-the workgroups without work lie behind all others, and where every sequence's do there are none.  And the quotients that the
+the workgroups without work lie together in front of those, and where every sequence's do there are none.  And the quotients that the
 deal is made of."""
 import subprocess
 from pathlib import Path
@@ -66,9 +66,11 @@ static void launch(const PrefillDeal& a, int G, int H_k, int nr, int per_pair, i
         for (int p = 0; p < a.xcd_pairs; ++p) {
             const int pair = 8 * p + xcd;
             if (pair >= a.num_pairs || a.split < 2 || C[seq[p]] <= 0 || !prefill_runs_whole(a, t[seq[p]])) continue;
+            int first = -1;
             for (int turn = 0; turn < per_pair; ++turn) {
                 const PrefillShare s = prefill_share(a, turn, t[seq[p]], C[seq[p]], G * ((C[seq[p]] + 15) / 16));
-                CHECK((s.part > 0) == (turn >= a.blocks_per_pair + a.split_blocks));
+                if (s.tail && first < 0) first = turn;
+                if (s.tail) CHECK((s.part > 0) == (turn - first < (a.split - 1) * a.split_blocks));
             }
         }
         std::set<std::pair<int, int>> taken;
